@@ -1085,7 +1085,7 @@ __global__ __launch_bounds__(DG_WG) void k_num_dg(NumArgs<VT> a) {
         const int64_t ab = a.arp[i], ae = a.arp[i + 1];
         dg_flat(ab, ae, a.aci, a.brp, st_off, st_bs, red, [&](int k, int64_t e, int64_t cb) {
             const VT av = a.aval[cb + k];
-            A::add(&gv[a.bci[e] - colbase], av, a.bval[e]);
+            A::add_hbm(&gv[a.bci[e] - colbase], av, a.bval[e]);
         });
         __threadfence();  // the HBM atomics above complete before any lane reads a slot
         __syncthreads();

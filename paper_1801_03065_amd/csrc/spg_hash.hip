@@ -532,7 +532,7 @@ __global__ __launch_bounds__(WG_BIG) void k_num_hl(NumArgs<VT> a) {
             if (h >= 0)
                 A::add(&vals[h], av, bv);
             else
-                A::add(&vals2[l2_find_or_insert(keys2, mask2, c)], av, bv);
+                A::add_hbm(&vals2[l2_find_or_insert(keys2, mask2, c)], av, bv);
         });
         // merge level 1 into level 2 as one more accumulation of each entry
         for (int s = t; s < l1; s += WG_BIG) {
@@ -542,8 +542,8 @@ __global__ __launch_bounds__(WG_BIG) void k_num_hl(NumArgs<VT> a) {
                 if constexpr (ACC == ACC_COMP) {
                     // fold the (s, c) pair in as two compensated additions of value*1
                     const S v = vals[s];
-                    A::add(dst, __uint_as_float((uint32_t)v), 1.0f);
-                    A::add(dst, __uint_as_float((uint32_t)(v >> 32)), 1.0f);
+                    A::add_hbm(dst, __uint_as_float((uint32_t)v), 1.0f);
+                    A::add_hbm(dst, __uint_as_float((uint32_t)(v >> 32)), 1.0f);
                 } else {
                     atomicAdd(dst, vals[s]);
                 }
