@@ -149,7 +149,8 @@ typedef struct {
     int32_t compressed;             /* 1 if the symbolic phase used compressed B */
     int32_t n_kinds;                /* kinds in use: 0 empty, 1 bit window (wavefront),
                                        2 hash (wavefront), 3 bit window (workgroup),
-                                       4 two-level hash, 5 word hash (numeric),
+                                       4 two-level hash, 5 word hash or, for
+                                       scattered rows, column buckets (numeric),
                                        6 short rows (a team of lanes per row),
                                        7 stored structure (numeric on the (word, bits)
                                        pairs the symbolic phase kept) */

@@ -11,7 +11,6 @@ namespace spg {
 namespace {
 
 constexpr int BLK = 256;
-constexpr int CL_GRID = 512;  // classify workgroups (rows per lane grow beyond)
 
 __device__ __forceinline__ unsigned long long ull(long long v) { return (unsigned long long)v; }
 
@@ -314,7 +313,7 @@ constexpr int RI_GRID = 2048;
 constexpr int RI_F = 7;  // rowinfo partial fields: fm, fmc, max, max compressed, fm and fmc of long rows,
                          // longest row of A
 __host__ __device__ constexpr bool ri_is_max(int f) { return f == 2 || f == 3 || f == 6; }
-static_assert(RI_F * RI_GRID <= RED_ELEMS && 4 * NK * CL_GRID <= RED_ELEMS, "analysis partials exceed scratch");
+static_assert(RI_F * RI_GRID <= RED_ELEMS, "analysis partials exceed scratch");
 
 // Compression rule of the Compression subsection, taken on the device from
 // the folded flop counts: compress when it removes more than (1 - thr) of the
@@ -468,14 +467,29 @@ __global__ __launch_bounds__(BLK) void k_rowinfo_fin(int nb, const long long *pa
     }
 }
 
+// Inclusive max-scan over the 64 lanes (values >= 0) with DPP lane moves;
+// lane 63 holds the wavefront maximum.
+__device__ __forceinline__ int wave_maxscan_dpp(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return v;
+}
+
 // ------------------------------------------------------------------ classify
-// One row per lane, CB rows per workgroup (contiguous, so the per-workgroup
-// kind counts are the counts of the stable partition).  Each workgroup writes
+// CL_R rows per lane, CR rows per workgroup (contiguous, so the per-workgroup
+// kind counts are the counts of the stable partition).  Two rows per lane: the
+// partition's workgroups each read every workgroup's counts, which two rows
+// cut to a quarter (partition of 1M rows: 8.8 us, 13.8 with one row), and up
+// to 2M rows need no separate fold of them (23 us).  Each workgroup writes
 // per kind: max window words, max bound, max touched words and its row count
 // (int32 x 4), and the row counts again compactly (int32 per kind); the
 // partition kernel folds them into the phase's statistics and the partition's
 // offsets (kinds in order, workgroups in row order within a kind).
-constexpr int CB = 1024;
+constexpr int CB = 1024, CL_R = 2, CR = CB * CL_R;
 
 __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflops, const int64_t *rflopsc,
                                                   const int2 *rwin, const int32_t *row_nnz,
@@ -495,8 +509,10 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
     const bool compressed = p.comp_flag ? (*p.comp_flag != 0) : (p.compressed != 0);
     const bool sg = p.sg && (p.unsorted == nullptr || *p.unsorted == 0);
     __syncthreads();
-    {
-        const int64_t i = (int64_t)blockIdx.x * CB + t;
+    int rk[CL_R], ra[CL_R], rb[CL_R], rt[CL_R];  // per row: kind, window words, bound, touched words
+#pragma unroll
+    for (int h = 0; h < CL_R; ++h) {
+        const int64_t i = (int64_t)blockIdx.x * CR + h * CB + t;
         const bool valid = i < m;
         const bool sampled = p.sample_stride <= 1 || (i % p.sample_stride) == 0;
         long long f = (valid && sampled) ? rflops[i] : 0;
@@ -541,7 +557,17 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                     else if (p.plan_cap > 0 && p.sym_kind[i] == K_DW && words <= p.plan_len[i] &&
                              nw <= PL_NW_MAX && bound <= PL_R_MAX)
                         k = K_PL;  // the symbolic phase stored this row's structure
-                    else
+                    // Scattered rows (at most two products per entry, A entries
+                    // for one wavefront) are sorted in column buckets: that
+                    // costs in proportion to the products, the other kernels
+                    // to entries, tables, sorts or segments.  Above two
+                    // products per entry the buckets fill with repeats and the
+                    // accumulators win.  Batch of 48 (400 products a row), FP64
+                    // numeric: the others 45.0 ms, buckets 5.6 ms.
+                    else if (p.bk && f <= BK_F_MAX && f <= 2 * bound && p.arp[i + 1] - p.arp[i] <= WAVE) {
+                        k = K_BK0;
+                        for (long long top = BK_F0; top < f; top <<= 1) ++k;
+                    } else
                         k = wh_fit ? K_WH : (hw_fit ? K_HW : (dg_fit ? K_DG : K_HL));
             }
             // heavy rows in segments: the symbolic bit window of a workgroup
@@ -569,17 +595,40 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
         }
         if (valid) kind[i] = (uint8_t)k;
         if (valid && p.words_out) p.words_out[i] = 0;  // the structure kernels fill it for their rows
-        for (int kk = 0; kk < NK; ++kk) {
-            const unsigned long long bal = __ballot(k == kk);
-            if (!bal) continue;
-            const int ma = wave_max(k == kk ? a : 0), mb = wave_max(k == kk ? bnd : 0);
-            const int mc = wave_max(k == kk ? tw : 0);
-            if (l == 0) {
-                atomicMax(&smax[kk][0], ma);
-                atomicMax(&smax[kk][1], mb);
-                atomicMax(&smax[kk][2], mc);
-                atomicAdd(&scnt[kk], __popcll(bal));
-            }
+        rk[h] = k;
+        ra[h] = a;
+        rb[h] = bnd;
+        rt[h] = tw;
+    }
+    // the kinds present in the wavefront, one at a time (usually one or two)
+    unsigned long long left[CL_R], any = 0;
+#pragma unroll
+    for (int h = 0; h < CL_R; ++h) any |= left[h] = __ballot(rk[h] >= 0);
+    while (any) {
+        int kk = 0;
+#pragma unroll
+        for (int h = 0; h < CL_R; ++h)
+            if (left[h]) kk = __builtin_amdgcn_readlane(rk[h], __ffsll((long long)left[h]) - 1);
+        int c = 0, ma = 0, mb = 0, mc = 0;
+        any = 0;
+#pragma unroll
+        for (int h = 0; h < CL_R; ++h) {
+            const bool is = rk[h] == kk;
+            const unsigned long long bal = __ballot(is);
+            any |= left[h] &= ~bal;
+            c += __popcll(bal);
+            ma = max(ma, is ? ra[h] : 0);
+            mb = max(mb, is ? rb[h] : 0);
+            mc = max(mc, is ? rt[h] : 0);
+        }
+        ma = __builtin_amdgcn_readlane(wave_maxscan_dpp(ma), 63);
+        mb = __builtin_amdgcn_readlane(wave_maxscan_dpp(mb), 63);
+        mc = __builtin_amdgcn_readlane(wave_maxscan_dpp(mc), 63);
+        if (l == 0) {
+            atomicMax(&smax[kk][0], ma);
+            atomicMax(&smax[kk][1], mb);
+            atomicMax(&smax[kk][2], mc);
+            atomicAdd(&scnt[kk], c);
         }
     }
     __syncthreads();
@@ -589,20 +638,8 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
         q[1] = smax[t][1];
         q[2] = smax[t][2];
         q[3] = scnt[t];
-        blk[4 * gridDim.x * NK + (int64_t)blockIdx.x * NK + t] = scnt[t];  // compact counts, read by every partition workgroup
+        blk[4 * gridDim.x * NK + (int64_t)blockIdx.x * NK_PAD + t] = scnt[t];  // compact counts, read by every partition workgroup
     }
-}
-
-// Inclusive max-scan over the 64 lanes (values >= 0) with DPP lane moves;
-// lane 63 holds the wavefront maximum.
-__device__ __forceinline__ int wave_maxscan_dpp(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
-    return v;
 }
 
 // One workgroup over the nb classify workgroups: per kind the row total and
@@ -629,7 +666,7 @@ __global__ __launch_bounds__(CB) void k_part_fold(int64_t nb, int32_t *cnt) {
         int c[NK], inc[NK];
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
-            c[k] = u < nb ? cnt[u * NK + k] : 0;
+            c[k] = u < nb ? cnt[u * NK_PAD + k] : 0;
             inc[k] = wave_scan_dpp(c[k]);
             if (l == WAVE - 1) wsum[k][wv] = inc[k];
         }
@@ -638,7 +675,7 @@ __global__ __launch_bounds__(CB) void k_part_fold(int64_t nb, int32_t *cnt) {
         for (int k = 0; k < NK; ++k) {
             int off = carry[k];
             for (int w = 0; w < wv; ++w) off += wsum[k][w];
-            if (u < nb) cnt[u * NK + k] = off + inc[k] - c[k];
+            if (u < nb) cnt[u * NK_PAD + k] = off + inc[k] - c[k];
         }
         __syncthreads();
         if (t < NK) {
@@ -648,7 +685,7 @@ __global__ __launch_bounds__(CB) void k_part_fold(int64_t nb, int32_t *cnt) {
         }
         __syncthreads();
     }
-    if (t < NK) cnt[nb * NK + t] = carry[t];
+    if (t < NK) cnt[nb * NK_PAD + t] = carry[t];
 }
 
 // Stable partition of rows by kind.  Every workgroup folds the classify
@@ -658,57 +695,63 @@ __global__ __launch_bounds__(CB) void k_part_fold(int64_t nb, int32_t *cnt) {
 // maxima and counts into the phase's statistics and writes the kind offsets.
 // A row lands at base + offset + its rank among the same kind in the
 // workgroup (wavefront ballots).
-static_assert(NK == 8, "the partition reads a workgroup's kind counts as two int4");
+static_assert(NK == 13 && NK_PAD == 16, "the partition reads a workgroup's kind counts as three int4 and an int");
 
 __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, const uint8_t *kind, const int32_t *blk,
                                                       int32_t *perm, int64_t *koff, int phase, int heavy,
                                                       DevStats *st) {
     constexpr int NW = CB / WAVE;
-    __shared__ int wcnt[NW][NK];
+    static_assert(CL_R * NW * NK <= CB, "one thread clears each count");
+    __shared__ int wcnt[CL_R * NW][NK];
     __shared__ int wtot[NK][NW], wpre[NK][NW];
     __shared__ int stot[NK], spre[NK], sbase[NK];
     __shared__ int smax[NK][3];
     const int t = threadIdx.x, l = lane_id(), wv = t / WAVE;
     const int64_t b = blockIdx.x;
     const int32_t *cnt = blk + 4 * nb * NK;
-    // kind totals over all classify workgroups and over the ones before this
-    int tot[NK], pre[NK];
-#pragma unroll
-    for (int k = 0; k < NK; ++k) tot[k] = pre[k] = 0;
+    // kind totals over all classify workgroups and over the ones before this.
+    // Beyond PF_FEW workgroups k_part_fold has folded them: exclusive prefixes
+    // per workgroup, kind totals after them.  Wavefronts without a count of
+    // their own, and kinds without rows, skip the sums (a scan of the
+    // wavefront each; summing everywhere, 1.6M rows took 31 us instead of 16).
     if (nb > PF_FEW) {
-        // folded beforehand by k_part_fold: exclusive prefixes per workgroup,
-        // kind totals after them (the per-kind sums below see them in lane 0)
-        if (t == 0) {
+        if (t < NK) {
+            wtot[t][0] = cnt[nb * NK_PAD + t];
+            wpre[t][0] = cnt[b * NK_PAD + t];
+        }
+    } else if ((int64_t)wv * WAVE < nb) {
+        const int64_t u = t;
+        int c[NK];
 #pragma unroll
-            for (int k = 0; k < NK; ++k) {
-                tot[k] = cnt[nb * NK + k];
-                pre[k] = cnt[b * NK + k];
+        for (int k = 0; k < NK; ++k) c[k] = 0;
+        if (u < nb) {
+            const int4 c0 = *(const int4 *)(cnt + u * NK_PAD), c1 = *(const int4 *)(cnt + u * NK_PAD + 4),
+                       c2 = *(const int4 *)(cnt + u * NK_PAD + 8);
+            const int v[NK] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w, c2.x, c2.y, c2.z, c2.w,
+                               cnt[u * NK_PAD + 12]};
+#pragma unroll
+            for (int k = 0; k < NK; ++k) c[k] = v[k];
+        }
+#pragma unroll
+        for (int k = 0; k < NK; ++k) {
+            int ts = 0, ps = 0;
+            if (__ballot(c[k] != 0)) {  // most kinds have no rows
+                ts = __builtin_amdgcn_readlane(wave_scan_dpp(c[k]), 63);
+                ps = __builtin_amdgcn_readlane(wave_scan_dpp(u < b ? c[k] : 0), 63);
+            }
+            if (l == 0) {
+                wtot[k][wv] = ts;
+                wpre[k][wv] = ps;
             }
         }
     }
-    for (int64_t u = t; nb <= PF_FEW && u < nb; u += CB) {
-        const int4 c0 = *(const int4 *)(cnt + u * NK), c1 = *(const int4 *)(cnt + u * NK + 4);
-        const int c[NK] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-#pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            tot[k] += c[k];
-            pre[k] += u < b ? c[k] : 0;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-        const int ts = __builtin_amdgcn_readlane(wave_scan_dpp(tot[k]), 63);
-        const int ps = __builtin_amdgcn_readlane(wave_scan_dpp(pre[k]), 63);
-        if (l == 0) {
-            wtot[k][wv] = ts;
-            wpre[k][wv] = ps;
-        }
-    }
+    const int nwt = nb > PF_FEW ? 1 : (int)((nb + WAVE - 1) / WAVE);  // wavefronts with sums
     if (t < NK) smax[t][0] = smax[t][1] = smax[t][2] = 0;
+    if (t < CL_R * NW * NK) (&wcnt[0][0])[t] = 0;
     __syncthreads();
     if (t < NK) {
         int T = 0, P = 0;
-        for (int u = 0; u < NW; ++u) {
+        for (int u = 0; u < nwt; ++u) {
             T += wtot[t][u];
             P += wpre[t][u];
         }
@@ -741,6 +784,7 @@ __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, cons
         }
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
+            if (!__ballot((mx[k][0] | mx[k][1] | mx[k][2]) != 0)) continue;
             const int m0 = __builtin_amdgcn_readlane(wave_maxscan_dpp(mx[k][0]), 63);
             const int m1 = __builtin_amdgcn_readlane(wave_maxscan_dpp(mx[k][1]), 63);
             const int m2 = __builtin_amdgcn_readlane(wave_maxscan_dpp(mx[k][2]), 63);
@@ -761,20 +805,38 @@ __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, cons
         long long *gc = phase == 0 ? &st->kcount_sym[k] : heavy ? &st->kcount_heavy[k] : &st->kcount_num[k];
         *gc += stot[k];
     }
-    // rows of this workgroup, stable within each kind
-    const int64_t i = b * CB + t;
-    const int k = i < m ? kind[i] : -1;
-    int rank = 0;
-    for (int kk = 0; kk < NK; ++kk) {
-        const unsigned long long bal = __ballot(k == kk);
-        if (kk == k) rank = mbcnt(bal);
-        if (l == 0) wcnt[wv][kk] = __popcll(bal);
+    // rows of this workgroup, stable within each kind: counts per wavefront
+    // and row of the lane, their prefix per kind, then each row's place
+    int k[CL_R], rank[CL_R];
+#pragma unroll
+    for (int h = 0; h < CL_R; ++h) {
+        const int64_t i = b * CR + h * CB + t;
+        k[h] = i < m ? kind[i] : -1;
+        rank[h] = 0;
+        for (unsigned long long left = __ballot(k[h] >= 0); left;) {
+            const int kk = __builtin_amdgcn_readlane(k[h], __ffsll((long long)left) - 1);
+            const unsigned long long bal = __ballot(k[h] == kk);
+            left &= ~bal;
+            if (kk == k[h]) rank[h] = mbcnt(bal);
+            if (l == 0) wcnt[h * NW + wv][kk] = __popcll(bal);
+        }
     }
     __syncthreads();
-    if (i < m) {
-        int off = 0;
-        for (int u = 0; u < wv; ++u) off += wcnt[u][k];
-        perm[sbase[k] + spre[k] + off + rank] = (int32_t)i;
+    if (t < NK) {
+        int c[CL_R * NW], run = sbase[t] + spre[t];
+#pragma unroll
+        for (int u = 0; u < CL_R * NW; ++u) c[u] = wcnt[u][t];
+#pragma unroll
+        for (int u = 0; u < CL_R * NW; ++u) {
+            wcnt[u][t] = run;
+            run += c[u];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < CL_R; ++h) {
+        const int64_t i = b * CR + h * CB + t;
+        if (i < m) perm[wcnt[h * NW + wv][k[h]] + rank[h]] = (int32_t)i;
     }
 }
 
@@ -1009,7 +1071,7 @@ hipError_t launch_store_rp(int64_t n1, const int64_t *src, void *dst, int is64, 
 hipError_t launch_classify(int64_t m, const int64_t *rflops, const int64_t *rflopsc, const int2 *rwin,
                            const int32_t *row_nnz, const int32_t *row_words, ClassParams p, uint8_t *kind,
                            int32_t *row_nnz_out, DevStats *st, int64_t *tmp, int64_t *koff, hipStream_t s) {
-    const int64_t nb = (m + CB - 1) / CB;
+    const int64_t nb = (m + CR - 1) / CR;
     if (nb == 0) {
         if (koff) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, (int32_t *)koff, (int64_t)(2 * (NK + 1)), 0);
         return hipGetLastError();
@@ -1023,11 +1085,11 @@ hipError_t launch_classify(int64_t m, const int64_t *rflops, const int64_t *rflo
 // offset), int32
 // per classify workgroup: NK int4 records (maxima, count), then NK compact counts
 // (and NK kind totals after them when k_part_fold runs)
-int64_t part_tmp_elems(int64_t m) { return (5 * ((m + CB - 1) / CB) * NK + NK + 1) / 2 + 1; }
+int64_t part_tmp_elems(int64_t m) { return (((m + CR - 1) / CR) * (4 * NK + NK_PAD) + NK + 1) / 2 + 1; }
 
 hipError_t launch_partition(int64_t m, const uint8_t *kind, int32_t *perm, const int64_t *tmp, int64_t *koff,
                             int phase, int heavy, DevStats *st, hipStream_t s) {
-    const int64_t nb = (m + CB - 1) / CB;
+    const int64_t nb = (m + CR - 1) / CR;
     if (nb == 0) return hipSuccess;
     if (nb > PF_FEW)
         hipLaunchKernelGGL(k_part_fold, dim3(1), dim3(CB), 0, s, nb, (int32_t *)tmp + 4 * nb * NK);

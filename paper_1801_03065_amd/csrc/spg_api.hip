@@ -428,10 +428,12 @@ static spg_status plan_buffers(spg_handle h, int64_t m, int64_t n, int64_t nnzb)
 static void rows_numeric_stats(spg_stats &o, const DevStats &hs, bool split, const long long *main) {
     if (!main) main = hs.kcount_num;
     long long heavy = 0;
+    for (int kk = 0; kk < NK_PUBLIC; ++kk) o.rows_numeric[kk] = 0;
     for (int kk = 0; kk < NK; ++kk) {
-        o.rows_numeric[kk] = main[kk];
+        const int pk = kk < NK_PUBLIC ? kk : K_WH;  // column-bucket rows count with the word hash
+        o.rows_numeric[pk] += main[kk];
         if (split && kk != K_EMPTY) {
-            o.rows_numeric[kk] += hs.kcount_heavy[kk];
+            o.rows_numeric[pk] += hs.kcount_heavy[kk];
             heavy += hs.kcount_heavy[kk];
         }
     }
@@ -639,6 +641,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     cp.heavy_flops = thr > 0 ? thr : 0;
     cp.heavy_alen = tmax > 0 ? tmax : 0;
     cp.arp = arp;
+    cp.bk = nnzb < (int64_t(1) << 29) ? 1 : 0;  // 32-bit byte offsets into B
     cp.split = split ? 1 : 0;
     cp.heavy = 0;
     HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
@@ -679,10 +682,10 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     o.nnz_c = nnzc;
     o.compressed = comp ? 1 : 0;
     o.nnz_b_compressed = comp ? h->hkoff[2] : 0;
-    o.n_kinds = NK;
+    o.n_kinds = NK_PUBLIC;
     int64_t maxrs = 0;
+    for (int kk = 0; kk < NK_PUBLIC; ++kk) o.rows_symbolic[kk] = hs3.kcount_sym[kk];
     for (int kk = 0; kk < NK; ++kk) {
-        o.rows_symbolic[kk] = hs3.kcount_sym[kk];
         if (kk != K_EMPTY) maxrs = std::max<int64_t>(maxrs, hs3.kmax_num[kk][1]);
         if (kk != K_EMPTY && split) maxrs = std::max<int64_t>(maxrs, hs3.kmax_heavy[kk][1]);
     }
@@ -811,7 +814,7 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
         HIPCHK(launch_num_pl<VT>(na, acc, lc));
     }
     if (vo && h->maps_ok) {  // structure known: every mapped kind on its position maps
-        for (int K : {K_SR, K_DW, K_WH, K_HW}) {
+        for (int K : MAP_KINDS) {
             if (kcount[K] <= 0) continue;
             na.rs.kind = K;
             na.r_max = std::max(kmax[K][1], 1);
@@ -837,6 +840,11 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
         na.r_max = std::max(kmax[K_WH][1], 1);
         na.ts = pow2_at_least(2 * (int64_t)std::max(kmax[K_WH][2], 1), 16);
         HIPCHK(launch_num_wh<VT>(na, acc, lc));
+    }
+    for (int K = K_BK0; K <= K_BK4; ++K) {
+        if (kcount[K] <= 0) continue;
+        na.rs.kind = K;
+        HIPCHK(launch_num_bk<VT>(na, acc, K, lc, kcount[K]));
     }
     if (kcount[K_HW] > 0 && pol == SPG_ACC_LL) {  // LL hashmap, rows unsorted
         na.rs.kind = K_HW;
@@ -1345,7 +1353,7 @@ static spg_status build_maps(spg_handle h, const int32_t *cci) {
                      double avg_b) {
         na.rs.rows = perm;
         na.rs.koff = koff;
-        for (int K : {K_SR, K_DW, K_WH, K_HW}) {
+        for (int K : MAP_KINDS) {
             if (kcount[K] <= 0) continue;
             na.rs.kind = K;
             const int lgt = K == K_SR ? sr_lg(kmax[K_SR][1]) : 6;

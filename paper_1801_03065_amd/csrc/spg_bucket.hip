@@ -1,0 +1,428 @@
+// Scattered rows in column buckets (numeric phase).
+//
+// A row of C whose products rarely meet (random or very sparse operands: at
+// most two products per entry on average) needs its products sorted far more
+// than it needs an accumulator.  The kernel sorts them by one counting pass:
+//
+//   1. every product (column, A value * B value) is loaded once into
+//      registers, U per lane, neighbouring lanes on neighbouring products
+//      (the owner of a product: run starts of the B rows marked in LDS and a
+//      max-scan), so no lane idles past the end of a B row;
+//   2. the row's column window is cut into as many equal buckets as the
+//      lanes hold products (a monotone map of the column), and an LDS counter per bucket gives every product
+//      its place in the bucket; a scan gives each bucket its place in the row;
+//   3. a product's place in the sorted row is its bucket's start plus the
+//      products of the bucket that sort before it (about one other to look
+//      at when columns are spread evenly);
+//   4. products of one column are neighbours now: the first of them sums the
+//      run and writes the entry; without repeats the row is written as it is.
+//
+// Rows with a bucket of more than BK_DEEP products (columns clustered inside
+// the window) are sorted by a bitonic network instead of steps 2 and 3.
+//
+// Rows of up to 512 products take one wavefront, of up to 1024 and 2048 two
+// and four (LDS and registers would leave one wavefront of 16 products per
+// lane at 8 per CU: 12.5 ps a product against 9.3 with two).  LDS is 16 B per
+// product (FP64), in launches of 64 * U * NW products, so short rows do not
+// pay for the LDS of long ones.
+//
+// Measured on the batch of 48 random products (FP64, 24 B moved per product
+// in and out): 8.1 to 10.0 ps a product over rows of 65 to 2048 products,
+// 2.4 to 3.0 TB/s; bound by memory latency at 16 wavefronts per CU (registers).
+// The kernels it replaces there: column hash with its bitonic sort 94 ps, word
+// hash 58, segments 21 (29.3, 14.1 and 1.6 ms; the five launches here 5.6 ms).
+#include <type_traits>
+
+#include "spg_accum.hpp"
+#include "spg_internal.hpp"
+
+namespace spg {
+
+namespace {
+
+constexpr int BK_DEEP = 24;  // products of one bucket above which the row is sorted by the network
+
+struct RowDescB {
+    int64_t ab, cb, ce;
+    int na, wlo, nw;
+};
+
+__device__ __forceinline__ RowDescB row_desc_b(int i, const int64_t *arp, const int2 *rwin, const int64_t *coff) {
+    RowDescB d;
+    d.ab = arp[i];
+    d.na = (int)min((int64_t)WAVE, arp[i + 1] - d.ab);
+    d.cb = coff[i];
+    d.ce = coff[i + 1];
+    const int2 w = rwin[i];
+    d.wlo = w.x;
+    d.nw = w.y - w.x + 1;
+    return d;
+}
+
+// Inclusive max-scan over the 64 lanes (values >= 0) with DPP lane moves.
+__device__ __forceinline__ int bk_maxscan(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return v;
+}
+
+// A product as it is kept until its run is summed, and the sum of a run.
+// FP64: the product.  FP32 plain: the product rounded to FP32, FP32 sums.
+// FP32 compensated and FP64-accumulated: the exact product in FP64; the
+// compensated pair takes its FP32 rounding and the error from it.
+template <typename VT, int ACC>
+struct BkTerm {
+    using term_t = typename std::conditional<ACC == ACC_NATIVE, VT, double>::type;
+    static __device__ __forceinline__ term_t term(VT a, VT b) { return (term_t)a * (term_t)b; }
+    term_t s = term_t(0);
+    __device__ __forceinline__ void add(term_t x) { s += x; }
+    __device__ __forceinline__ VT fin() const { return (VT)s; }
+};
+template <>
+struct BkTerm<float, ACC_COMP> {
+    using term_t = double;
+    static __device__ __forceinline__ double term(float a, float b) { return (double)a * (double)b; }
+    float s = 0.0f, c = 0.0f;
+    __device__ __forceinline__ void add(double p) {
+        const float x = (float)p, ex = (float)(p - (double)x);  // p == x + ex exactly
+        const float s2 = s + x, bv = s2 - s;                     // TwoSum(s, x)
+        c += ((s - (s2 - bv)) + (x - bv)) + ex;
+        s = s2;
+    }
+    __device__ __forceinline__ float fin() const { return s + c; }
+};
+
+// Hand-over of LDS data between the lanes of the workgroup.  Both forms wait
+// for LDS only, so loads for the next row stay in flight.
+template <int NW>
+__device__ __forceinline__ void bk_sync() {
+    if constexpr (NW == 1) {
+        wave_lds_sync();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt = 0
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
+}
+
+// NW wavefronts per row, U products per lane.
+template <typename VT, int ACC, int NW, int U>
+__global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_num_bk(NumArgs<VT> a) {
+    using Term = BkTerm<VT, ACC>;
+    using P = typename Term::term_t;
+    constexpr int WG = WAVE * NW, CAP = WG * U;  // CAP: products of a row, and buckets
+    __shared__ __align__(16) uint32_t cnt[CAP];  // bucket: count, then start | count << 16
+    __shared__ __align__(16) int32_t key[CAP];   // columns in bucket order, then sorted
+    __shared__ __align__(16) unsigned char val_raw[CAP * sizeof(P)];
+    __shared__ int32_t st_rel[WAVE];             // per A entry: B row start - first product
+    __shared__ VT st_a[WAVE];
+    __shared__ int red[2 * NW + 2];
+    P *val = (P *)val_raw;                // products in sorted order
+    uint16_t *own = (uint16_t *)val_raw;  // before that: A entry that starts at a product
+    const int t = threadIdx.x, l = lane_id(), wv = NW == 1 ? 0 : read_first(t / WAVE);
+    const int p0 = wv * (WAVE * U) + l;   // this lane's products: p0 + u * WAVE
+#pragma unroll
+    for (int u = 0; u < U; ++u) cnt[u * WG + t] = 0;
+    int64_t lo, hi;
+    rs_bounds(a.rs, lo, hi);
+    const int64_t cbase = a.cbase_row >= 0 ? a.coff[a.cbase_row] : 0;
+    const uint32_t elast = (uint32_t)(a.nnzb - 1);
+    const Slice sl = xcd_slice(lo, hi);
+    // Software pipeline across rows, as in the other wavefront kernels: the
+    // next row's A entries (first level), then its B row extents (second
+    // level), and the descriptor of the row after it load during this row.
+    // Every wavefront of the row holds the A entries (one per lane).
+    int64_t r = sl.idx;
+    RowDescB dcur = r < sl.end ? row_desc_b(a.rs.rows[r], a.arp, a.rwin, a.coff) : RowDescB{};
+    int64_t b0 = 0, b1 = 0;
+    VT av = VT(0);
+    if (r < sl.end && l < dcur.na) {
+        const int j = a.aci[dcur.ab + l];
+        av = a.aval[dcur.ab + l];
+        b0 = a.brp[j];
+        b1 = a.brp[j + 1];
+    }
+    RowDescB dn = r + sl.step < sl.end ? row_desc_b(a.rs.rows[r + sl.step], a.arp, a.rwin, a.coff) : RowDescB{};
+    while (r < sl.end) {
+        const RowDescB d = dcur;
+        r += sl.step;
+        const bool has_next = r < sl.end;
+        // ---- products of the row: prefix of the B row lengths, owners
+        const int len = l < d.na ? (int)(b1 - b0) : 0;
+        const int inc = wave_scan_dpp(len), ex = inc - len;
+        const int f = __builtin_amdgcn_readlane(inc, WAVE - 1);
+        const int64_t n64 = d.ce - d.cb;
+        const bool fits = f > 0 && f <= CAP && n64 <= f;  // else the structure changed behind the plan
+        if (NW == 1 || wv == 0) {
+            st_rel[l] = (int32_t)b0 - ex;
+            st_a[l] = av;
+        }
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u) ((uint32_t *)own)[u * WG + t] = 0;
+        if (NW > 1 && t < 2) red[2 * NW + t] = 0;
+        bk_sync<NW>();
+        if ((NW == 1 || wv == 0) && len > 0 && (unsigned)ex < (unsigned)CAP) own[ex] = (uint16_t)l;
+        // the A entry in progress where this wavefront's products start
+        int carry = 0;
+        if (NW > 1) {
+            const unsigned long long before = __ballot(len > 0 && ex < wv * (WAVE * U));
+            carry = before ? 63 - __clzll(before) : 0;
+        }
+        // next row, first level
+        const int nna = has_next ? dn.na : 0;
+        int nj = 0;
+        if (l < nna) {
+            nj = a.aci[dn.ab + l];
+            av = a.aval[dn.ab + l];
+        }
+        bk_sync<NW>();
+        int col[U], k[U];
+        VT bv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = own[u * WAVE + p0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            k[u] = max(bk_maxscan(k[u]), carry);
+            carry = __builtin_amdgcn_readlane(k[u], WAVE - 1);
+        }
+        uint32_t e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = u * WAVE + p0;
+            e[u] = p < f ? min((uint32_t)(st_rel[k[u]] + p), elast) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) col[u] = ld32(a.bci, e[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) bv[u] = ld32(a.bval, e[u]);
+        // next row, second level; the row after it: descriptor
+        if (l < nna) {
+            b0 = a.brp[nj];
+            b1 = a.brp[nj + 1];
+        }
+        dcur = dn;
+        if (r + sl.step < sl.end) dn = row_desc_b(a.rs.rows[r + sl.step], a.arp, a.rwin, a.coff);
+        if (!fits) {  // the same in every wavefront of the row
+            if (t == 0) atomicAdd(&a.st->mismatch, 1);
+            bk_sync<NW>();
+            continue;
+        }
+        const int n = (int)n64;
+
+        // ---- buckets: monotone map of the window onto CAP buckets
+        const int c0 = d.wlo << 5;
+        const float w = 32.0f * (float)d.nw;
+        const uint32_t scale =
+            (uint32_t)fminf((float)CAP * 4294967296.0f * __builtin_amdgcn_rcpf(w), 4294967040.0f);
+        int slot[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            b[u] = (int)min(__umulhi((uint32_t)(col[u] - c0), scale), (uint32_t)(CAP - 1));
+            slot[u] = 0;
+            if (u * WAVE + p0 < f) slot[u] = (int)atomicAdd(&cnt[b[u]], 1u);
+        }
+        bk_sync<NW>();
+        // bucket starts: lane t scans buckets [t * U, (t + 1) * U)
+        int deep;
+        {
+            uint32_t cc[U];
+            int sum = 0, mx = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) cc[u] = cnt[t * U + u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                sum += (int)cc[u];
+                mx = max(mx, (int)cc[u]);
+            }
+            const int incs = wave_scan_dpp(sum);
+            int run = incs - sum;
+            deep = __builtin_amdgcn_readlane(bk_maxscan(mx), WAVE - 1);
+            if (NW > 1) {
+                if (l == WAVE - 1) {
+                    red[wv] = incs;
+                    red[NW + wv] = deep;
+                }
+                bk_sync<NW>();
+#pragma unroll
+                for (int v = 0; v < NW; ++v) {
+                    run += v < wv ? red[v] : 0;
+                    deep = max(deep, red[NW + v]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cnt[t * U + u] = (uint32_t)run | (cc[u] << 16);
+                run += (int)cc[u];
+            }
+        }
+        bk_sync<NW>();
+
+        // ---- place of each product in the sorted row
+        const bool net = deep > BK_DEEP;
+        bool repeats = true;  // some column met twice
+        if (!net) {
+            int st[U], pos[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t x = cnt[b[u]];
+                st[u] = (int)(x & 0xFFFFu);
+                b[u] = u * WAVE + p0 < f ? (int)(x >> 16) : 0;  // products of the bucket
+                pos[u] = st[u];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * WAVE + p0 < f) key[st[u] + slot[u]] = col[u];
+            bk_sync<NW>();
+            bool seen = false;
+            for (int j = 0; j < deep; ++j) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (j < b[u]) {
+                        const int kj = key[st[u] + j];
+                        const bool same = kj == col[u] && j < slot[u];
+                        seen |= same;
+                        pos[u] += (kj < col[u] || same) ? 1 : 0;
+                    }
+                }
+            }
+            repeats = __ballot(seen) != 0;
+            if (NW > 1 && repeats && l == 0) red[2 * NW] = 1;
+            bk_sync<NW>();
+            if (NW > 1) repeats = red[2 * NW] != 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) slot[u] = pos[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) slot[u] = u * WAVE + p0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u * WAVE + p0 < f) {
+                key[slot[u]] = col[u];
+                val[slot[u]] = Term::term(st_a[k[u]], bv[u]);
+            }
+        }
+        if (net) {
+            int np = WAVE;
+            while (np < f) np <<= 1;
+            for (int p = f + t; p < np; p += WG) key[p] = INT_MAX;
+            bk_sync<NW>();
+            for (int kk = 2; kk <= np; kk <<= 1)
+                for (int j = kk >> 1; j > 0; j >>= 1) {
+                    for (int p = t; p < (np >> 1); p += WG) {
+                        const int i1 = ((p & ~(j - 1)) << 1) | (p & (j - 1)), i2 = i1 + j;
+                        const bool up = (i1 & kk) == 0;
+                        const int32_t k1 = key[i1], k2 = key[i2];
+                        if ((k1 > k2) == up) {
+                            key[i1] = k2;
+                            key[i2] = k1;
+                            const P v1 = val[i1];
+                            val[i1] = val[i2];
+                            val[i2] = v1;
+                        }
+                    }
+                    bk_sync<NW>();
+                }
+        }
+        bk_sync<NW>();
+
+        // ---- write the row: each run of one column summed by its first product
+        const int64_t ob = d.cb - cbase;
+        if (!repeats && f == n) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = u * WAVE + p0;
+                if (p < f) {
+                    Term s;
+                    s.add(val[p]);
+                    a.cci[ob + p] = key[p];
+                    a.cval[ob + p] = s.fin();
+                }
+            }
+        } else {
+            unsigned long long head[U];
+            int kc[U], total = 0, base = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = u * WAVE + p0;
+                kc[u] = p < f ? key[p] : -1;
+                head[u] = __ballot(p < f && (p == 0 || key[p - 1] != kc[u]));
+                total += __popcll(head[u]);
+            }
+            if (NW > 1) {
+                if (l == 0) red[wv] = total;
+                bk_sync<NW>();
+                total = 0;
+#pragma unroll
+                for (int v = 0; v < NW; ++v) {
+                    base += v < wv ? red[v] : 0;
+                    total += red[v];
+                }
+            }
+            if (total != n) {
+                if (t == 0) atomicAdd(&a.st->mismatch, 1);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if ((head[u] >> l) & 1ull) {
+                        int p = u * WAVE + p0;
+                        Term s;
+                        do s.add(val[p]);
+                        while (++p < f && key[p] == kc[u]);
+                        const int64_t o = ob + base + mbcnt(head[u]);
+                        a.cci[o] = kc[u];
+                        a.cval[o] = s.fin();
+                    }
+                    base += __popcll(head[u]);
+                }
+            }
+        }
+        bk_sync<NW>();
+#pragma unroll
+        for (int u = 0; u < U; ++u) cnt[u * WG + t] = 0;
+    }
+}
+
+template <typename VT, int ACC, int NW, int U>
+hipError_t num_bk_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_num_bk<VT, ACC, NW, U>, WAVE * NW, 0) != hipSuccess ||
+        per_cu < 1)
+        per_cu = 1;
+    int64_t grid = std::min<int64_t>((int64_t)per_cu * c.cus, rows);
+    grid = std::max<int64_t>(XCDS, (grid + XCDS - 1) / XCDS * XCDS);
+    hipLaunchKernelGGL((k_num_bk<VT, ACC, NW, U>), dim3((unsigned)grid), dim3(WAVE * NW), 0, c.stream, a);
+    return hipGetLastError();
+}
+
+template <typename VT, int ACC>
+hipError_t num_bk_acc(const NumArgs<VT> &a, int kind, const LaunchCfg &c, int64_t rows) {
+    switch (kind) {
+    case K_BK0: return num_bk_u<VT, ACC, 1, 2>(a, c, rows);
+    case K_BK1: return num_bk_u<VT, ACC, 1, 4>(a, c, rows);
+    case K_BK2: return num_bk_u<VT, ACC, 1, 8>(a, c, rows);
+    case K_BK3: return num_bk_u<VT, ACC, 2, 8>(a, c, rows);
+    case K_BK4: return num_bk_u<VT, ACC, 4, 8>(a, c, rows);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+template <>
+hipError_t launch_num_bk<double>(const NumArgs<double> &a, int, int kind, const LaunchCfg &c, int64_t rows) {
+    return num_bk_acc<double, ACC_NATIVE>(a, kind, c, rows);
+}
+template <>
+hipError_t launch_num_bk<float>(const NumArgs<float> &a, int acc, int kind, const LaunchCfg &c, int64_t rows) {
+    if (acc == ACC_COMP) return num_bk_acc<float, ACC_COMP>(a, kind, c, rows);
+    if (acc == ACC_WIDE) return num_bk_acc<float, ACC_WIDE>(a, kind, c, rows);
+    return num_bk_acc<float, ACC_NATIVE>(a, kind, c, rows);
+}
+
+}  // namespace spg

@@ -34,7 +34,14 @@ enum Kind : int {
     K_WH = 5,     // word hash + ordered summary, one wavefront per row (numeric)
     K_SR = 6,     // short rows: a team of T <= 64 lanes per row, several rows per wavefront
     K_PL = 7,     // numeric on the symbolic phase's stored row structure, one wavefront per row
-    NK = 8
+    K_BK0 = 8,    // column buckets (numeric): one wavefront per row for rows of up to 128,
+    K_BK1 = 9,    //   256
+    K_BK2 = 10,   //   and 512 multiplications, two and four wavefronts
+    K_BK3 = 11,   //   for rows of up to 1024
+    K_BK4 = 12,   //   and 2048
+    NK = 13,
+    NK_PAD = 16,   // per-workgroup kind counts are stored 16 apart (int4 loads)
+    NK_PUBLIC = 8  // kinds reported in spg_stats: the bucket kinds count as K_WH there
 };
 
 // Global counters written by the analysis kernels (zeroed per symbolic call).
@@ -67,6 +74,7 @@ constexpr int WH_NW_MAX = 32768;  // window words of the word-hash kernel (summa
 constexpr int WH_R_MAX = 1024;    // row size of the word-hash kernel
 constexpr int WH_T_MAX = 512;     // touched words of the word-hash kernel (table 2x)
 constexpr int SR_F_MAX = 64;      // multiplications of a short row (one per lane of its team)
+constexpr int BK_F0 = 128, BK_F_MAX = 2048;  // multiplications of K_BK0 and K_BK4 (doubling in between)
 constexpr int PL_CAP = 64;        // stored (word, bits) pairs per row (one per lane)
 constexpr int PL_NW_MAX = 8192;   // window words of the stored-structure kernel (byte map in LDS)
 constexpr int PL_R_MAX = 2048;    // row size of the stored-structure kernel
@@ -387,10 +395,11 @@ struct ClassParams {
     // (each entry of C then sums more than heavy_alen products); with split
     // set only the rows on the side named by `heavy` get a kind (others: empty)
     long long heavy_flops, heavy_alen;
-    const int64_t *arp;  // A's row offsets (int64), read when heavy_alen > 0
+    const int64_t *arp;  // A's row offsets (int64), read when heavy_alen > 0 or bk is set
     int split;
     int heavy;          // numeric: counts / maxima go to the heavy-row set
     int sr_f_max;       // selector: rows with at most this many multiplications are short rows (0: off)
+    int bk;             // numeric, selector: scattered rows may take the column-bucket kinds (nnz(B) < 2^29)
     int plan_cap;       // stored row structure: pairs per row (0: off)
     int32_t *plan_len;  // symbolic: room for pairs per row (written); numeric: read
     const uint8_t *sym_kind;  // numeric: kind of each row in the symbolic phase
@@ -440,6 +449,9 @@ hipError_t launch_num_sg(const NumArgs<VT> &a, int acc, int acc2, const LaunchCf
 int sg_resident_grid(int acc, int acc2, bool dbl, int cus);
 template <typename VT>
 hipError_t launch_num_wh(const NumArgs<VT> &a, int acc, const LaunchCfg &c);
+// Scattered rows in column buckets (kind: K_BK0 .. K_BK4).
+template <typename VT>
+hipError_t launch_num_bk(const NumArgs<VT> &a, int acc, int kind, const LaunchCfg &c, int64_t rows);
 template <typename VT>
 hipError_t launch_num_pl(const NumArgs<VT> &a, int acc, const LaunchCfg &c);
 size_t lds_num_pl(int nw_max, int r_max, int acc_bytes);
@@ -491,8 +503,11 @@ template <typename VT>
 hipError_t launch_mask_g(const MaskArgs<VT> &a, const LaunchCfg &c);
 size_t lds_mask_w(int lg, int mmax);
 
-// Kinds whose rows get position maps: every row fits 1024 entries (16-bit ranks).
-__host__ __device__ inline bool map_kind(int k) { return k == K_SR || k == K_WH || k == K_HW || k == K_DW; }
+// Kinds whose rows get position maps: every row fits 2048 entries (16-bit ranks).
+constexpr int MAP_KINDS[] = {K_SR, K_DW, K_WH, K_HW, K_BK0, K_BK1, K_BK2, K_BK3, K_BK4};
+__host__ __device__ inline bool map_kind(int k) {
+    return k == K_SR || k == K_WH || k == K_HW || k == K_DW || k >= K_BK0;
+}
 // out[i] = multiplications of row i if it gets a map, else 0 (kind_heavy nullable).
 hipError_t launch_map_rows(int64_t m, const uint8_t *kind, const uint8_t *kind_heavy, const int64_t *rflops,
                            int32_t *out, hipStream_t s);
