@@ -1416,21 +1416,25 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
     HIPCHK(ensure(h->mk_arp, 8 * (m + 1)));
     HIPCHK(ensure(h->mk_brp, 8 * (n + 1)));
     HIPCHK(ensure(h->mk_mrp, 8 * (m + 1)));
-    HIPCHK(ensure(h->mk_rows, 8 * std::max<int64_t>(m, 1)));
+    HIPCHK(ensure(h->mk_rows, 12 * std::max<int64_t>(m, 1)));
     HIPCHK(ensure(h->mk_cnt, 8 * sizeof(int)));
-    int *cnt = h->mk_cnt.as<int>();  // [0..1] rows per kind, [2..3] longest mask row per kind, [4] bad input
-    int32_t *rows1 = h->mk_rows.as<int32_t>(), *rows2 = rows1 + m;
+    // [0..2] rows per kind, [3..5] longest mask row per kind, [6] bad input, [7] row queue
+    int *cnt = h->mk_cnt.as<int>(), *bad = cnt + 6;
+    int32_t *rows = h->mk_rows.as<int32_t>();
     HIPCHK(launch_fill_i32(cnt, 8, 0, st));
     HIPCHK(launch_copy_rp(m + 1, A->row_ptr, A->rp_type == SPG_I64, A->nnz, h->mk_arp.as<int64_t>(), n + 1,
-                          B->row_ptr, B->rp_type == SPG_I64, B->nnz, h->mk_brp.as<int64_t>(), cnt + 4, st));
+                          B->row_ptr, B->rp_type == SPG_I64, B->nnz, h->mk_brp.as<int64_t>(), bad, st));
     HIPCHK(launch_copy_rp(m + 1, M->row_ptr, M->rp_type == SPG_I64, M->nnz, h->mk_mrp.as<int64_t>(), 0, nullptr, 0,
-                          0, nullptr, cnt + 4, st));
+                          0, nullptr, bad, st));
     if (M->nnz > 0) HIPCHK(launch_fill_i32((int32_t *)out, M->nnz * (int64_t)(sizeof(VT) / 4), 0, st));
-    HIPCHK(launch_mask_class(m, h->mk_arp.as<int64_t>(), h->mk_mrp.as<int64_t>(), MW_MAX, rows1, rows2, cnt, st));
+    // (row pointers are clamped copies and out-of-range columns are skipped, so
+    // this stays in bounds on malformed input)
+    HIPCHK(launch_mask_class(m, n, h->mk_arp.as<int64_t>(), A->col_idx, h->mk_brp.as<int64_t>(),
+                             h->mk_mrp.as<int64_t>(), rows, cnt, st));
     int *hc = (int *)(h->hkoff + 8);
-    HIPCHK(hipMemcpyAsync(hc, cnt, 5 * sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(hc, cnt, 7 * sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (hc[4]) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: row_ptr out of range or not monotone");
+    if (hc[6]) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: row_ptr out of range or not monotone");
     MaskArgs<VT> a{};
     a.arp = h->mk_arp.as<int64_t>();
     a.aci = A->col_idx;
@@ -1443,31 +1447,34 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
     a.out = out;
     a.n = n;
     a.k = k;
-    a.lg_gs = lg_group(n ? std::max(1.0, (double)B->nnz / (double)n) : 1.0);
+    a.nnzb = B->nnz;
     a.structural = structural;
-    a.bad = cnt + 4;
+    a.bad = bad;
     LaunchCfg lc{st, 0, h->cus};
-    if (hc[0] > 0) {
-        a.rows = rows1;
-        a.nrows = hc[0];
-        int lg = 4;
-        while ((1 << lg) < 2 * hc[2]) ++lg;
-        HIPCHK(launch_mask_w<VT>(a, lg, hc[2], lc));
-    }
-    if (hc[1] > 0) {
-        a.rows = rows2;
+    if (hc[1] + hc[2] > 0) {  // workgroup rows, the heaviest first
+        a.rows = rows + m;
         a.nrows = hc[1];
-        a.arena_cap = pow2_at_least(2 * (int64_t)hc[3], 64);
-        int grid = (int)std::min<int64_t>(((hc[1] + 7) / 8) * 8, 2 * (int64_t)h->cus);
-        HIPCHK(ensure(h->mk_arena, (size_t)12 * a.arena_cap * grid));
-        a.arena = h->mk_arena.p;
-        lc.grid = grid;
-        HIPCHK(launch_mask_g<VT>(a, lc));
+        a.rows3 = rows + 2 * m;
+        a.nrows3 = hc[2];
+        if (hc[2] > 0) {
+            a.arena_cap = pow2_at_least(2 * (int64_t)hc[5], 64);
+            lc.grid = 2 * h->cus / XCDS * XCDS;
+            a.arena_slices = std::min(hc[2], lc.grid);
+            HIPCHK(ensure(h->mk_arena, (size_t)12 * a.arena_cap * a.arena_slices));
+            a.arena = h->mk_arena.p;
+        }
+        HIPCHK(launch_mask<VT>(a, hc[4], cnt + 7, lc));
     }
-    HIPCHK(hipMemcpyAsync(hc + 4, cnt + 4, sizeof(int), hipMemcpyDeviceToHost, st));
+    if (hc[0] > 0) {  // wavefront rows
+        a.rows = rows;
+        a.nrows = hc[0];
+        a.nrows3 = 0;
+        HIPCHK(launch_mask<VT>(a, hc[3], nullptr, lc));
+    }
+    HIPCHK(hipMemcpyAsync(hc + 6, bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (hc[4] & 1) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: a column index out of range");
-    if (hc[4]) return fail(h, SPG_ERR_INTERNAL, "masked product: arena too small");
+    if (hc[6] & 1) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: a column index out of range");
+    if (hc[6]) return fail(h, SPG_ERR_INTERNAL, "masked product: arena too small");
     return SPG_OK;
 }
 

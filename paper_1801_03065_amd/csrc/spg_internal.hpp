@@ -487,21 +487,27 @@ struct MaskArgs {
     VT *out;               // nnz(M), M's entry order
     const int32_t *rows;   // rows of this launch
     int64_t nrows;
+    const int32_t *rows3;  // rows of kind 3 (taken first, workgroup launch)
+    int64_t nrows3;
     int64_t n, k;          // A's columns < n, B's and M's < k
-    int lg_gs;             // lanes per B row
+    int64_t nnzb;
     int structural;
-    void *arena;           // workgroup rows: 12 B per slot per workgroup
-    int64_t arena_cap;     // slots per workgroup (power of two >= 2 x longest mask row)
+    void *arena;           // rows of kind 3: 12 B per slot, arena_slices slices
+    int64_t arena_cap;     // slots per slice (power of two >= 2 x longest mask row)
+    int arena_slices;      // min(rows of kind 3, workgroups of the launch)
     int *bad;              // bit 0: a column out of range, bit 1: arena too small
 };
-constexpr int MW_MAX = 512;  // mask row length of the wavefront kind
-hipError_t launch_mask_class(int64_t m, const int64_t *arp, const int64_t *mrp, int mw_max, int32_t *rows1,
-                             int32_t *rows2, int *cnt, hipStream_t s);
+// Mask rows of a wavefront: length (its table and accumulators leave room for
+// 20 wavefronts per CU) and multiplications (a wavefront forms about 0.4 a ns,
+// so MK_F bounds a row at 20 us); length of a workgroup's mask row in LDS.
+constexpr int MW_MAX = 256, MK_F = 8192, MG_MAX = 2048;
+// rows: 3 lists of m; cnt: rows per kind (3), longest mask row per kind (3).
+hipError_t launch_mask_class(int64_t m, int64_t n, const int64_t *arp, const int32_t *aci, const int64_t *brp,
+                             const int64_t *mrp, int32_t *rows, int *cnt, hipStream_t s);
+// Without a queue: kind 1 (wavefront rows); with one (a zeroed counter): kinds 3
+// and 2.  mmax: longest mask row of kind 1 or 2; c.grid: workgroups (with kind 3).
 template <typename VT>
-hipError_t launch_mask_w(const MaskArgs<VT> &a, int lg, int mmax, const LaunchCfg &c);
-template <typename VT>
-hipError_t launch_mask_g(const MaskArgs<VT> &a, const LaunchCfg &c);
-size_t lds_mask_w(int lg, int mmax);
+hipError_t launch_mask(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCfg &c);
 
 // Kinds whose rows get position maps: every row fits 2048 entries (16-bit ranks).
 constexpr int MAP_KINDS[] = {K_SR, K_DW, K_WH, K_HW, K_BK0, K_BK1, K_BK2, K_BK3, K_BK4};
