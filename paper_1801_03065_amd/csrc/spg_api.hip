@@ -1517,7 +1517,8 @@ static spg_status backward_impl(spg_handle h, const spg_csr *A, const spg_csr *B
     ba.gval = (const VT *)G->values;
     ba.dA = (VT *)dA;
     ba.dB = (VT *)dB;
-    ba.lg_gs = lg_group(h->avg_len);
+    ba.flops = h->stats.flops;
+    ba.max_row = h->stats.max_row_nnz;
     ba.st = h->dstats.as<DevStats>();
     LaunchCfg lc{h->stream, 0, h->cus};
     HIPCHK(launch_backward<VT>(ba, lc));

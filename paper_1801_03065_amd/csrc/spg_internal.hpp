@@ -181,7 +181,7 @@ struct BwdArgs {
     const VT *gval;        // dL/dC on pattern(C)
     VT *dA;                // nnz(A) or nullptr
     VT *dB;                // nnz(B) or nullptr
-    int lg_gs;
+    int64_t flops, max_row;  // multiplications of the product, longest row of C
     DevStats *st;
 };
 
