@@ -584,6 +584,12 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                 if (k == K_DG && sg && (eb > SG_CAP || nw > SG_NW))
                     room = (int)((eb + SG_CUT - 1) / SG_CUT + (nw + SG_NW - 1) / SG_NW + 2);
                 p.plan_len[i] = room;
+                // A heavy row's bit window is kept for the numeric phase where
+                // that costs less than rebuilding it: 8 B a word written and
+                // read (1.8 ps) against a column load and an OR per
+                // multiplication (about 3 ps on R-MAT squares), halved for
+                // margin.
+                if (p.sgb_len) p.sgb_len[i] = k == K_DG && room > 0 && f >= nw ? (int)nw : 0;
             }
             if (k == K_SR) bound = f;  // a short row's team size follows its multiplications
             a = (int)min(nw, (long long)INT_MAX);
@@ -592,6 +598,7 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
         } else if (valid && p.phase == 0) {
             row_nnz_out[i] = 0;
             if (p.plan_len) p.plan_len[i] = 0;
+            if (p.sgb_len) p.sgb_len[i] = 0;
         }
         if (valid) kind[i] = (uint8_t)k;
         if (valid && p.words_out) p.words_out[i] = 0;  // the structure kernels fill it for their rows

@@ -98,6 +98,8 @@ struct spg_handle_s {
     DevBuf kind_tmp, perm_tmp, koff_tmp, krange, kind_heavy, perm_heavy, koff_heavy, krange_heavy, sgcur;
     bool heavy_split = false;  // the plan keeps FP64-accumulated rows in their own kind lists
     bool verify = false;       // numeric / backward check the operands' structure fingerprint
+    bool sgb_kept = false;     // the symbolic phase stored heavy rows' bit windows
+    DevBuf sgb, sgb_off, sgb_len;
     DevBuf mflops, map_off, map;  // reuse: per-row mapped multiplications, map offsets, ranks
     DevBuf mk_arp, mk_brp, mk_mrp, mk_rows, mk_cnt, mk_arena;  // masked product
     bool maps_built = false;      // position maps taken for this plan (maps_ok: they exist)
@@ -349,7 +351,7 @@ spg_status spg_destroy(spg_handle h) {
     DevBuf *bufs[] = {&h->arp64, &h->brp64, &h->binfo, &h->ulist, &h->uflag, &h->bcrp, &h->bcw,
                       &h->rflops, &h->rflopsc, &h->rwin, &h->row_nnz, &h->coff, &h->kind_sym, &h->kind_num,
                       &h->perm_sym, &h->perm_num, &h->koff_sym, &h->koff_num, &h->tmp, &h->dstats, &h->red, &h->queue, &h->plan_len, &h->plan_off, &h->plan,
-                      &h->arena, &h->l2k, &h->l2v, &h->blens, &h->row_words, &h->kind_tmp, &h->perm_tmp, &h->koff_tmp, &h->krange, &h->kind_heavy, &h->perm_heavy, &h->koff_heavy, &h->krange_heavy, &h->sgcur, &h->mflops, &h->map_off, &h->map,
+                      &h->arena, &h->l2k, &h->l2v, &h->blens, &h->row_words, &h->kind_tmp, &h->perm_tmp, &h->koff_tmp, &h->krange, &h->kind_heavy, &h->perm_heavy, &h->koff_heavy, &h->krange_heavy, &h->sgcur, &h->sgb, &h->sgb_off, &h->sgb_len, &h->mflops, &h->map_off, &h->map,
                       &h->mk_arp, &h->mk_brp, &h->mk_mrp, &h->mk_rows, &h->mk_cnt, &h->mk_arena,
                       &h->row_cls, &h->kind_cls, &h->perm_cls, &h->koff_cls};
     for (DevBuf *b : bufs) release(*b);
@@ -500,6 +502,10 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         cp.plan_cap = want_pairs ? PL_CAP : 0;
         cp.plan_len = h->plan_len.as<int32_t>();
         cp.sg = want_segs_opt ? 1 : 0;
+        if (want_segs_opt) {
+            HIPCHK(ensure(h->sgb_len, 4 * (m + 1)));
+            cp.sgb_len = h->sgb_len.as<int32_t>();
+        }
     }
     cp.words_out = h->row_words.as<int32_t>();
     HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(), nullptr,
@@ -529,7 +535,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     // segment room is in the scan (no heavy rows with lists) and that bound
     // is modest, the plan is sized by it without waiting for the total;
     // otherwise the exact total is fetched (one more host sync).
-    int64_t plan_room = 0;
+    int64_t plan_room = 0, sgb_words = 0;
     if (pairs_used || segs_used) {
         HIPCHK(launch_scan_i32(m, h->plan_len.as<int32_t>(), h->plan_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
         const int64_t bound = (int64_t)PL_CAP * hs2.kcount_sym[K_DW];
@@ -537,10 +543,18 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         if (!seg_room && bound <= (int64_t(1) << 27)) {
             plan_room = bound;
         } else {
+            h->hkoff[4] = 0;
+            if (segs_used) {
+                HIPCHK(ensure(h->sgb_off, 8 * (m + 1)));
+                HIPCHK(launch_scan_i32(m, h->sgb_len.as<int32_t>(), h->sgb_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
+                HIPCHK(hipMemcpyAsync(h->hkoff + 4, h->sgb_off.as<int64_t>() + m, sizeof(int64_t),
+                                      hipMemcpyDeviceToHost, st));
+            }
             HIPCHK(hipMemcpyAsync(h->hkoff + 1, h->plan_off.as<int64_t>() + m, sizeof(int64_t),
                                   hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
             plan_room = h->hkoff[1];
+            sgb_words = h->hkoff[4];
         }
     }
     bool plan_ok = false;
@@ -553,6 +567,10 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     }
     h->planned = plan_ok && pairs_used;
     h->segmented = plan_ok && segs_used;
+    // (without room for the heavy rows' bit windows the numeric phase rebuilds them)
+    h->sgb_kept = h->segmented && sgb_words > 0 && sgb_words <= SGB_MAX &&
+                  ensure(h->sgb, 4 * (size_t)sgb_words) == hipSuccess;
+    (void)hipGetLastError();
     // segments need a list wherever a row may exceed one (rows with a bound
     // of room in plan_len): with lists missing, all heavy rows take the
     // window-wide kernel
@@ -581,6 +599,11 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         sa.plan_len = h->plan_len.as<int32_t>();
         sa.plan = h->plan.as<uint2>();
     }
+    if (h->sgb_kept) {
+        sa.sgb = h->sgb.as<uint32_t>();
+        sa.sgb_off = h->sgb_off.as<int64_t>();
+        sa.sgb_len = h->sgb_len.as<int32_t>();
+    }
     LaunchCfg lc{st, 0, h->cus};
     auto grid_cap = [&](int64_t rows) { return (int)std::min<int64_t>(2048 * 8, ((rows + 7) / 8) * 8); };
 
@@ -607,7 +630,6 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         sa.nw_max = ((hs2.kmax_sym[K_DG][0] + 31) / 32) * 32;
         HIPCHK(launch_fill_i32(sa.rs.queue, XCDS, 0, st));
         lc.grid = grid_cap(hs2.kcount_sym[K_DG]);
-        lc.grid = std::min(lc.grid, 8 * h->cus);
         HIPCHK(launch_sym_dg(sa, lc));
     }
     if (hs2.kcount_sym[K_HL] > 0) {
@@ -631,6 +653,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     HIPCHK(launch_scan_i32(m, h->row_nnz.as<int32_t>(), h->coff.as<int64_t>(), h->tmp.as<int64_t>(), st));
     cp.phase = 1;
     cp.words_out = nullptr;
+    cp.sgb_len = nullptr;
     cp.plan_cap = h->planned ? PL_CAP : 0;
     cp.sym_kind = h->kind_sym.as<uint8_t>();
     cp.sg = h->sg_mode ? 1 : 0;
@@ -1185,6 +1208,11 @@ static spg_status numeric_impl(spg_handle h, const VT *aval, const VT *bval, int
     if (h->segmented) {
         na.plan_len = h->plan_len.as<int32_t>();
         na.sym_kind = h->kind_sym.as<uint8_t>();
+    }
+    if (h->sgb_kept) {
+        na.sgb = h->sgb.as<uint32_t>();
+        na.sgb_off = h->sgb_off.as<int64_t>();
+        na.sgb_len = h->sgb_len.as<int32_t>();
     }
     na.cci = cci;
     na.cval = cval;

@@ -936,124 +936,6 @@ __device__ __forceinline__ void dg_or_pass(int i, int wlo, const int64_t *arp, c
         dg_or_batched<false>(arp[i], arp[i + 1], wlo, aci, brp, bci, bcw, bits, summ, st_off, st_bs, red);
 }
 
-// Segment list of a heavy row (the row's bit window is complete in bits /
-// summ): a segment starts at the touched word that holds entry q*SG_CUT for
-// each q, and at the first touched word of each aligned group of SG_NW words.
-// So a segment holds at most SG_CUT + 31 < SG_CAP entries and its words lie in
-// one group.  list[0] = (S, 0), list[1..S] = (first word, entries before it),
-// list[S+1] = (window words, row size).  Clears bits / summ; returns the row
-// size (low half) and touched words (high half).
-__device__ long long dg_segments(int nw, int ns, uint32_t *bits, uint32_t *summ, int *gfirst, long long *red,
-                                 uint2 *list, int cap, DevStats *st) {
-    const int t = threadIdx.x;
-    const int ng = (nw + SG_NW - 1) / SG_NW;
-    if (t < ng) gfirst[t] = INT_MAX;
-    __syncthreads();
-    for (int s = t; s < ns; s += DG_WG) {
-        const uint32_t m = summ[s];
-        if (m) atomicMin(&gfirst[(s << 5) / SG_NW], (s << 5) + __ffs(m) - 1);
-    }
-    __syncthreads();
-    long long run = 0, words = 0, cuts = 0;
-    for (int s0 = 0; s0 < ns; s0 += DG_WG) {
-        const int s = s0 + t;
-        const uint32_t m = s < ns ? summ[s] : 0u;
-        long long c = 0;
-        for (uint32_t mm = m; mm; mm &= mm - 1) c += __popc(bits[(s << 5) + __ffs(mm) - 1]);
-        long long tot;
-        const long long ex = block_excl_scan(c + ((long long)__popc(m) << 32), red, &tot);
-        const int pbeg = (int)(run + (ex & 0xffffffffll));
-        int p = pbeg, nc = 0;
-        for (uint32_t mm = m; mm; mm &= mm - 1) {
-            const int d = (s << 5) + __ffs(mm) - 1;
-            const int cd = __popc(bits[d]);
-            const int mult = ((p + SG_CUT - 1) / SG_CUT) * SG_CUT;  // first multiple of SG_CUT >= p
-            nc += (mult < p + cd || d == gfirst[d / SG_NW]) ? 1 : 0;
-            p += cd;
-        }
-        long long ctot;
-        long long idx = cuts + block_excl_scan(nc, red, &ctot);
-        p = pbeg;
-        for (uint32_t mm = m; mm; mm &= mm - 1) {
-            const int d = (s << 5) + __ffs(mm) - 1;
-            const int cd = __popc(bits[d]);
-            const int mult = ((p + SG_CUT - 1) / SG_CUT) * SG_CUT;
-            if (mult < p + cd || d == gfirst[d / SG_NW]) {
-                if (idx + 2 < cap) list[1 + idx] = make_uint2((uint32_t)d, (uint32_t)p);
-                ++idx;
-            }
-            p += cd;
-            bits[d] = 0;
-        }
-        if (s < ns) summ[s] = 0;
-        run += tot & 0xffffffffll;
-        words += tot >> 32;
-        cuts += ctot;
-    }
-    if (t == 0) {
-        if (cuts + 2 <= cap) {
-            list[0] = make_uint2((uint32_t)cuts, 0u);
-            list[1 + cuts] = make_uint2((uint32_t)nw, (uint32_t)run);
-        } else {
-            atomicAdd(&st->overflow, 1);
-        }
-    }
-    return run | (words << 32);
-}
-
-__global__ __launch_bounds__(DG_WG) void k_sym_dg(SymArgs a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const DgLayout L = dg_layout(a.nw_max);
-    uint32_t *bits = (uint32_t *)(smem + L.bits);
-    uint32_t *summ = (uint32_t *)(smem + L.summ);
-    int64_t *st_off = (int64_t *)(smem + L.st_off);
-    int64_t *st_bs = (int64_t *)(smem + L.st_bs);
-    long long *red = (long long *)(smem + L.red);
-    __shared__ int gfirst[DG_NW_MAX / SG_NW];
-    const int t = threadIdx.x;
-    const int nsm = (a.nw_max + 31) >> 5;
-    for (int w = t; w < a.nw_max; w += DG_WG) bits[w] = 0;
-    for (int w = t; w < nsm; w += DG_WG) summ[w] = 0;
-    int64_t lo, hi;
-    rs_bounds(a.rs, lo, hi);
-    int x = blockIdx.x % XCDS;
-    for (;;) {
-        const int i = dg_next_row(a.rs, lo, hi, x, red);
-        if (i < 0) break;
-        const int2 win = a.rwin[i];
-        const int ns = (win.y - win.x + 1 + 31) >> 5;
-        dg_or_pass(i, win.x, a.arp, a.aci, a.brp, a.bci, a.bcrp, a.bcw, bits, summ, st_off, st_bs, red);
-        const int cap = a.plan ? a.plan_len[i] : 0;
-        if (cap > 0) {
-            const long long r = dg_segments(win.y - win.x + 1, ns, bits, summ, gfirst, red, a.plan + a.plan_off[i],
-                                            cap, a.st);
-            if (t == 0) {
-                a.row_nnz[i] = (int32_t)(r & 0xffffffffll);
-                a.row_words[i] = (int32_t)(r >> 32);
-            }
-            continue;
-        }
-        long long cnt = 0;
-        for (int s = t; s < ns; s += DG_WG) {
-            uint32_t m = summ[s];
-            summ[s] = 0;
-            cnt += (long long)__popc(m) << 32;  // touched words in the high half
-            while (m) {
-                const int d = (s << 5) + __ffs(m) - 1;
-                m &= m - 1;
-                cnt += __popc(bits[d]);
-                bits[d] = 0;
-            }
-        }
-        long long tot;
-        block_excl_scan(cnt, red, &tot);
-        if (t == 0) {
-            a.row_nnz[i] = (int32_t)(tot & 0xffffffffll);
-            a.row_words[i] = (int32_t)(tot >> 32);
-        }
-    }
-}
-
 template <typename VT, int ACC>
 __global__ __launch_bounds__(DG_WG) void k_num_dg(NumArgs<VT> a) {
     using A = Accum<VT, ACC>;
@@ -1141,7 +1023,6 @@ inline int resident_grid(K kernel, int block, size_t lds, int cus) {
 
 size_t lds_sym_dw(int nw_max) { return sw_layout(nw_max).total; }
 size_t lds_num_dw(int nw_max, int r_max, int acc_bytes, int) { return dw_layout(nw_max, r_max, acc_bytes, true).total; }
-size_t lds_sym_dg(int nw_max) { return dg_layout(nw_max).total; }
 size_t lds_num_dg(int nw_max) { return dg_layout(nw_max).total; }
 
 // At most SW_WAVES_PER_CU resident wavefronts per CU: with small windows the
@@ -1175,13 +1056,6 @@ hipError_t sym_dw_impl(const SymArgs &a, const LaunchCfg &c) {
 
 hipError_t launch_sym_dw(const SymArgs &a, const LaunchCfg &c) {
     return a.bcrp ? sym_dw_impl<true>(a, c) : sym_dw_impl<false>(a, c);
-}
-
-hipError_t launch_sym_dg(const SymArgs &a, const LaunchCfg &c) {
-    const size_t lds = lds_sym_dg(a.nw_max);
-    const int grid = c.grid > 0 ? c.grid : resident_grid(k_sym_dg, DG_WG, lds, c.cus);
-    hipLaunchKernelGGL(k_sym_dg, dim3(grid), dim3(DG_WG), lds, c.stream, a);
-    return hipGetLastError();
 }
 
 template <typename VT, int ACC>

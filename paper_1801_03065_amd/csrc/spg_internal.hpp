@@ -80,6 +80,7 @@ constexpr int PL_NW_MAX = 8192;   // window words of the stored-structure kernel
 constexpr int PL_R_MAX = 2048;    // row size of the stored-structure kernel
 constexpr int SG_NW = 4096;       // column-set words of one heavy-row segment (aligned groups)
 constexpr int SG_CAP = 4096;      // entries of one heavy-row segment (LDS values)
+constexpr int64_t SGB_MAX = int64_t(2) << 30;  // words of heavy rows' bit windows kept at most (8 GiB)
 constexpr int SG_CUT = SG_CAP - 32;  // a segment starts at the word holding each multiple of this
 
 // ------------------------------------------------------------ argument blocks
@@ -124,6 +125,9 @@ struct SymArgs {
     uint2 *plan;              // nullptr: no pairs stored
     int b32;                  // nnz(B) < 2^30: B entries addressed with 32-bit byte offsets
     int64_t nnzb;             // nnz(B): gathers clamp their offsets to its last entry
+    uint32_t *sgb;            // K_DG: the row's bit window is stored at sgb + sgb_off (nullptr: not kept)
+    const int64_t *sgb_off;
+    const int32_t *sgb_len;   // words of room per row (0: not kept)
     DevStats *st;
 };
 
@@ -157,6 +161,9 @@ struct NumArgs {
     const int32_t *row_words; // K_PL: number of pairs of the row
     const int32_t *plan_len;  // K_DG (segmented): room in plan per row
     const uint8_t *sym_kind;  // K_DG (segmented): rows of symbolic kind K_DG with room hold a segment list
+    const uint32_t *sgb;      // K_DG (segmented): the row's bit window, as the symbolic phase stored it
+    const int64_t *sgb_off;   //   (nullptr, or sgb_len 0: rebuilt from B)
+    const int32_t *sgb_len;
     int32_t *sg_cur;          // K_DG (segmented): per workgroup, sg_cap A entries x 3 int32 (cursor, run end, B row end)
     int sg_cap;               //   (nullptr / 0: runs found by two searches per segment)
     int b32;               // nnz(B) * 8 < 2^32: B entries addressed with 32-bit offsets
@@ -402,6 +409,7 @@ struct ClassParams {
     int bk;             // numeric, selector: scattered rows may take the column-bucket kinds (nnz(B) < 2^29)
     int plan_cap;       // stored row structure: pairs per row (0: off)
     int32_t *plan_len;  // symbolic: room for pairs per row (written); numeric: read
+    int32_t *sgb_len;   // symbolic: words of a heavy row's bit window to keep (written; nullptr: none)
     const uint8_t *sym_kind;  // numeric: kind of each row in the symbolic phase
     const int *comp_flag;     // symbolic: when set, compression as decided on the device (else `compressed`)
     int32_t *words_out;       // symbolic: zeroed for every row (touched words, filled by the structure kernels)
@@ -548,7 +556,6 @@ hipError_t launch_kind_merge(int64_t m, const uint8_t *row_cls, const uint8_t *k
 // LDS bytes of the core kernels for given limits.
 size_t lds_sym_dw(int nw_max);
 size_t lds_sym_hw(int ts);
-size_t lds_sym_dg(int nw_max);
 size_t lds_sym_hl(int l1_slots);
 size_t lds_num_dw(int nw_max, int r_max, int acc_bytes, int val_bytes);
 size_t lds_num_hw(int ts, int acc_bytes);

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_mask(MaskArgs<VT> a, int lg, int m
         } else {
             if (t == 0) red[NW] = atomicAdd(queue, 1);
             __syncthreads();
-            r = red[NW];
+            r = uni64(red[NW]);
             if (r >= nrows) break;  // every workgroup leaves here once the counter has passed the rows
         }
         const bool big = BIG && r < a.nrows3;

@@ -14,11 +14,9 @@
 //      from segment to segment, in a register for rows of one chunk of A
 //      entries, in HBM scratch for longer rows, else binary search); the
 //      nonempty runs are staged back to back,
-//   2. structure: the run's columns OR-ed into an LDS bit array over the
-//      segment's words, Thread-Flat-Parallel over the segment's products
-//      (neighbouring lanes on neighbouring products, so a run's loads
-//      coalesce; each wavefront finds the run of every product of its
-//      window from run starts marked in LDS and a forward fill),
+//   2. structure: the segment's words, as the symbolic phase kept them, else
+//      the runs' columns OR-ed into an LDS bit array over the words,
+//      Thread-Flat-Parallel over the segment's products (spg_flat.hpp),
 //   3. ranks: prefix popcounts of the words give every column its place in
 //      the row,
 //   4. values: each product added at its rank in LDS (Algorithm 1's
@@ -27,19 +25,25 @@
 //      into LDS and stored in rank order (both coalesced), at the segment's
 //      offset in the row, which the symbolic phase recorded.
 //
-// Nothing lives in HBM but the inputs and C; a row with one segment (its
-// entries and window fit) runs the same steps once, with whole B rows.
+// Nothing lives in HBM but the inputs, the kept words and C; a row with one
+// segment (its entries and window fit) runs the same steps once, with whole B
+// rows.
+//
+// Bound by the vector-memory path (its data unit 65% busy before the words were
+// kept: runs inside a segment are a few entries, so a 64-lane load touches 16
+// cache lines) and by latency at 16 wavefronts per CU.  Keeping the words saves
+// the OR walk, half the loads and half the owner searches.  R-MAT scale 17
+// squared, FP64 (3.5e9 multiplications): 20.8 -> 14.9 ms, 4.3 ps a
+// multiplication; scale 20, where the words (over 40 GB) are rebuilt: 611 ->
+// 573 ms, symbolic phase 166 -> 136 ms.
 #include "spg_accum.hpp"
+#include "spg_flat.hpp"
 #include "spg_internal.hpp"
 
 namespace spg {
 namespace {
 
 constexpr int SG_U = 8;  // products per lane per round of the flat walks (loads in flight)
-// The staging scan adds (run length) + (1 << SG_SHIFT if the run is nonempty):
-// products below the shift, the nonempty run's slot above it.
-constexpr int SG_SHIFT = 48;
-constexpr long long SG_ONE = 1ll << SG_SHIFT, SG_LEN = SG_ONE - 1;
 // Lanes per workgroup (one heavy row).  LDS (~76 KB) allows two workgroups
 // per CU; 512 lanes rather than 256 double the loads in flight per CU for the
 // same LDS, with registers held to 128 (4 waves per SIMD).
@@ -70,8 +74,8 @@ __device__ __forceinline__ int sg_next_row(const RowSet &rs, int64_t lo, int64_t
         red[SG_WG / WAVE + 1] = x;
     }
     __syncthreads();
-    x = (int)red[SG_WG / WAVE + 1];
-    return (int)red[SG_WG / WAVE];
+    x = read_first((int)red[SG_WG / WAVE + 1]);
+    return read_first((int)red[SG_WG / WAVE]);  // scalar: the row's bounds then live in scalar registers
 }
 
 // First index in [lo, hi) whose column is >= key (hi when none); the row's
@@ -112,24 +116,10 @@ __device__ __forceinline__ int64_t sg_gallop(const int32_t *bci, int64_t lo, int
     return a;
 }
 
-// Index k of the run that holds flat product f: the first k >= kc with
-// st_off[k] > f (run ends, increasing: only nonempty runs are staged).  The
-// wavefront's window starts increase, so its previous run kc is a lower bound
-// and often the answer; otherwise a binary search over the rest.
-__device__ __forceinline__ int sg_find(const int64_t *st_off, int cn, long long f, int kc) {
-    if (st_off[kc] > f) return kc;
-    int lo = kc + 1, hi = cn - 1;  // st_off[cn - 1] > f for every product f of the chunk
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (st_off[mid] > f) hi = mid;
-        else lo = mid + 1;
-    }
-    return lo;
-}
-
 // ACC accumulates the rows of a.rs, ACC2 those of a.rs2 (FP32 values: the
-// heaviest rows in FP64); the value array holds either kind of entry.
-template <typename VT, int ACC, int ACC2>
+// heaviest rows in FP64); the value array holds either kind of entry.  IX:
+// 32-bit B indices where byte offsets into B's values fit 32 bits.
+template <typename VT, int ACC, int ACC2, typename IX>
 __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_num_sg(NumArgs<VT> a) {
     using A = Accum<VT, ACC>;
     using S = typename A::store_t;
@@ -141,14 +131,12 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     __shared__ __align__(16) unsigned char vals_raw[SG_CAP * VB];
     S *vals = (S *)vals_raw;
     S2 *vals2 = (S2 *)vals_raw;
-    __shared__ int64_t st_lo[SG_WG];   // run start (B entry) per A entry of the chunk
-    __shared__ int64_t st_off[SG_WG];  // inclusive prefix of the run lengths
+    __shared__ IX st_rel[SG_WG];   // per nonempty run: its first B entry, less its first product
+    __shared__ int st_off[SG_WG];  // inclusive prefix of the run lengths
     __shared__ VT st_a[SG_WG];
     __shared__ long long red[SG_WG / WAVE + 2];
-    // per wavefront: the run of each product of its window (relative to the
-    // window's first run), so that neighbouring lanes take neighbouring products
-    __shared__ __align__(16) uint16_t widx[SG_WG / WAVE][SG_U * WAVE];
-    const int t = threadIdx.x;
+    __shared__ __align__(16) uint16_t widx[SG_WG / WAVE][SG_U * WAVE];  // flat_window's scratch per wavefront
+    const int t = threadIdx.x, l = lane_id(), wv = read_first(t / WAVE);
     for (int w = t; w < SG_NW; w += SG_WG) bits[w] = 0;
     for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;  // every kind of zero
     int64_t qlo, qhi;
@@ -179,7 +167,8 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
         const int64_t ab = a.arp[i], ae = a.arp[i + 1];
         const bool has_list = a.plan_len != nullptr && a.sym_kind[i] == K_DG && a.plan_len[i] > 0;
         const uint2 *list = has_list ? a.plan + a.plan_off[i] : nullptr;
-        const int nseg = has_list ? (int)list[0].x : 1;
+        const uint32_t *kept = has_list && a.sgb != nullptr && a.sgb_len[i] > 0 ? a.sgb + a.sgb_off[i] : nullptr;
+        const int nseg = has_list ? read_first((int)list[0].x) : 1;
         const bool single = nseg == 1;
         const bool one_chunk = ae - ab <= SG_WG;
         // several chunks: per A entry, in this workgroup's scratch, the B
@@ -201,16 +190,12 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
         // one chunk: lane t keeps A entry t for the whole row, with a cursor
         // into its B row that moves from segment to segment
         int64_t cur = 0, bend = 0;
-        int cn1 = 0;
         VT av1 = VT(0);
-        if (one_chunk) {
-            cn1 = (int)(ae - ab);
-            if (t < cn1) {
-                const int j = a.aci[ab + t];
-                cur = a.brp[j];
-                bend = a.brp[j + 1];
-                av1 = a.aval[ab + t];
-            }
+        if (one_chunk && ab + t < ae) {
+            const int j = a.aci[ab + t];
+            cur = a.brp[j];
+            bend = a.brp[j + 1];
+            av1 = a.aval[ab + t];
         }
         int bad = 0;
         for (int sg = 0; sg < nseg; ++sg) {
@@ -218,203 +203,156 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             int64_t p1 = 0, p2 = nnz;
             if (has_list) {
                 const uint2 d1 = list[1 + sg], d2 = list[2 + sg];
-                w1 = (int)d1.x;
-                p1 = d1.y;
-                w2 = (int)d2.x;
-                p2 = d2.y;
+                w1 = read_first((int)d1.x);
+                p1 = (uint32_t)read_first((int)d1.y);
+                w2 = read_first((int)d2.x);
+                p2 = (uint32_t)read_first((int)d2.y);
             }
             const int cnt = (int)(p2 - p1);
             const int64_t col_lo = (int64_t)(wlo + w1) << 5, col_hi = (int64_t)(wlo + w2) << 5;
             const int span = min(w2 - w1, SG_NW);
             const int dbase = wlo + w1;  // column-set word of bits[0]
-            long long tot1 = 0;
-            int nz1 = 0;
-            if (one_chunk) {
-                long long len = 0;
-                int64_t s0 = cur;
-                if (t < cn1) {
-                    const int64_t e = single ? bend : sg_gallop(a.bci, cur, bend, col_hi);
-                    len = e - cur;
-                    cur = e;
-                }
-                long long pt;
-                const long long ex = sg_block_excl_scan(len + (len > 0 ? SG_ONE : 0), red, &pt);
-                tot1 = pt & SG_LEN;
-                nz1 = (int)(pt >> SG_SHIFT);
-                if (len > 0) {
-                    const int k = (int)(ex >> SG_SHIFT);
-                    st_lo[k] = s0;
-                    st_off[k] = (ex & SG_LEN) + len;
-                    st_a[k] = av1;
-                }
-                __syncthreads();
-            }
-            // pass 1 (structure) and pass 2 (values) walk the same runs
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int64_t cb = ab; cb < ae; cb += SG_WG) {
-                    int cn = nz1;
-                    long long tot = tot1;
-                    if (!one_chunk) {
-                        const int cnc = (int)min((int64_t)SG_WG, ae - cb);
-                        long long len = 0;
-                        int64_t lo_t = 0;
-                        VT av_t = VT(0);
-                        if (t < cnc) {
-                            const int64_t k = cb - ab + t;
-                            int64_t s0, s1;
-                            if (cur_g) {
-                                s0 = cur_g[k];
-                                if (pass == 0) {
-                                    s1 = sg_gallop(a.bci, s0, (int64_t)end_g[k], col_hi);
-                                    nxt_g[k] = (int32_t)s1;
-                                } else {
-                                    s1 = nxt_g[k];
-                                    cur_g[k] = (int32_t)s1;  // the next segment starts where this run ends
-                                }
-                            } else {
-                                const int j = a.aci[cb + t];
-                                s0 = a.brp[j];
-                                s1 = a.brp[j + 1];
-                                if (!single) {
-                                    s0 = sg_lower_bound(a.bci, s0, s1, col_lo);
-                                    s1 = sg_lower_bound(a.bci, s0, s1, col_hi);
-                                }
-                            }
-                            lo_t = s0;
-                            av_t = a.aval[cb + t];
-                            len = s1 - s0;
-                        }
-                        long long pt;
-                        const long long ex = sg_block_excl_scan(len + (len > 0 ? SG_ONE : 0), red, &pt);
-                        tot = pt & SG_LEN;
-                        cn = (int)(pt >> SG_SHIFT);
-                        if (len > 0) {
-                            const int k = (int)(ex >> SG_SHIFT);
-                            st_lo[k] = lo_t;
-                            st_off[k] = (ex & SG_LEN) + len;
-                            st_a[k] = av_t;
-                        }
-                        __syncthreads();
-                    }
-                    // Flat walk: per round, wavefront wv takes the SG_U * 64
-                    // products from F = f0 + wv * SG_U * 64 on, lane l the
-                    // products F + l + 64 u (neighbouring lanes, neighbouring
-                    // B entries).  The run of each product comes from a
-                    // per-wavefront index: run starts marked in LDS, then a
-                    // forward fill (max-scan) over the window.
-                    const int wv = t / WAVE, l = t % WAVE;
-                    uint16_t *wi = widx[wv];
-                    int kc = 0;  // the run of the wavefront's previous window start
-                    for (long long f0 = 0; f0 < tot; f0 += (long long)SG_WG * SG_U) {
-                        int64_t e[SG_U];
-                        bool ok[SG_U];
-                        const long long F = f0 + (long long)wv * (SG_U * WAVE);
-                        int klo = 0;
-                        if (F < tot) {  // the same for the whole wavefront
-                            klo = sg_find(st_off, cn, F, kc);
-                            kc = klo;
-                            *(uint4 *)&wi[l * SG_U] = make_uint4(0u, 0u, 0u, 0u);
-                            wave_lds_sync();
-                            const long long Fe = min(F + (long long)(SG_U * WAVE), tot);
-                            for (int k = klo + 1 + l; k < cn; k += WAVE) {
-                                const long long st = st_off[k - 1];  // run k's first product
-                                if (st >= Fe) break;                  // starts increase with k
-                                wi[st - F] = (uint16_t)(k - klo);
-                            }
-                            wave_lds_sync();
-                            const uint4 q4 = *(const uint4 *)&wi[l * SG_U];
-                            uint32_t w4[4] = {q4.x, q4.y, q4.z, q4.w};
-                            int m[SG_U];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                m[2 * u] = (int)(w4[u] & 0xFFFFu);
-                                m[2 * u + 1] = (int)(w4[u] >> 16);
-                            }
-#pragma unroll
-                            for (int u = 1; u < SG_U; ++u) m[u] = max(m[u], m[u - 1]);
-                            int incl = m[SG_U - 1];  // inclusive max-scan of the lanes' maxima
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, false));
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, false));
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, false));
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, false));
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xA, 0xF, false));
-                            incl = max(incl, __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xC, 0xF, false));
-                            const int before = __shfl_up(incl, 1);
-                            const int pm = l ? before : 0;
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                w4[u] = (uint32_t)max(m[2 * u], pm) | ((uint32_t)max(m[2 * u + 1], pm) << 16);
-                            *(uint4 *)&wi[l * SG_U] = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-                            wave_lds_sync();
-#pragma unroll
-                            for (int u = 0; u < SG_U; ++u) {
-                                const long long f = F + l + u * WAVE;
-                                ok[u] = f < tot;
-                                const int k = klo + (int)wi[l + u * WAVE];
-                                e[u] = st_lo[k] + (f - (k ? st_off[k - 1] : 0));
-                            }
+            // Stage the nonempty runs of one chunk of A entries, back to back:
+            // returns their number, *tot products.  A run lies in the segment's
+            // words, which bounds it (and a chunk's products below 2^31).
+            // first / last: the first and last walk over the segment's runs.
+            auto stage = [&](int64_t cb, bool first, bool last, int *tot) -> int {
+                int64_t s0 = 0, s1 = 0;
+                VT av = VT(0);
+                if (one_chunk) {
+                    s0 = cur;
+                    if (ab + t < ae) s1 = single ? bend : sg_gallop(a.bci, cur, bend, col_hi);
+                    else s1 = s0;
+                    cur = s1;
+                    av = av1;
+                } else if (cb + t < ae) {
+                    const int64_t k = cb - ab + t;
+                    if (cur_g) {
+                        s0 = cur_g[k];
+                        if (first) {
+                            s1 = sg_gallop(a.bci, s0, (int64_t)end_g[k], col_hi);
+                            if (!last) nxt_g[k] = (int32_t)s1;
                         } else {
-#pragma unroll
-                            for (int u = 0; u < SG_U; ++u) {
-                                ok[u] = false;
-                                e[u] = 0;
-                            }
+                            s1 = nxt_g[k];
                         }
+                        if (last) cur_g[k] = (int32_t)s1;  // the next segment starts where this run ends
+                    } else {
+                        const int j = a.aci[cb + t];
+                        s0 = a.brp[j];
+                        s1 = a.brp[j + 1];
+                        if (!single) {
+                            s0 = sg_lower_bound(a.bci, s0, s1, col_lo);
+                            s1 = sg_lower_bound(a.bci, s0, s1, col_hi);
+                        }
+                    }
+                    av = a.aval[cb + t];
+                }
+                const long long len = min(s1 - s0, (int64_t)SG_NW * 32);
+                long long all;
+                const long long ex = sg_block_excl_scan(len + (len > 0 ? FLAT_ONE : 0), red, &all);
+                if (len > 0) {
+                    const int k = (int)(ex >> FLAT_SHIFT), before = (int)(ex & FLAT_LEN);
+                    st_rel[k] = (IX)(s0 - before);
+                    st_off[k] = before + (int)len;
+                    st_a[k] = av;
+                }
+                *tot = read_first((int)(all & FLAT_LEN));
+                __syncthreads();
+                return read_first((int)(all >> FLAT_SHIFT));
+            };
+            // The staged products, SG_U per lane and round: body(u, product's
+            // run, B entry, in range) is called in two steps, loads then use.
+            auto walk = [&](int cn, int tot, auto &&use) {
+                int kc = 0;
+                for (int F = wv * (SG_U * WAVE); F < tot; F += SG_U * SG_WG) {
+                    int k[SG_U];
+                    IX e[SG_U];
+                    kc = flat_window<SG_U>(st_off, cn, F, tot, kc, widx[wv], k);
+#pragma unroll
+                    for (int u = 0; u < SG_U; ++u) {
+                        const int f = F + u * WAVE + l;
+                        k[u] += kc;
+                        e[u] = f < tot ? st_rel[k[u]] + f : IX(-1);
+                    }
+                    use(k, e);
+                }
+            };
+            auto ldc = [&](IX e) -> int { return sizeof(IX) == 4 ? ld32(a.bci, (uint32_t)e) : a.bci[e]; };
+            auto ldv = [&](IX e) -> VT { return sizeof(IX) == 4 ? ld32(a.bval, (uint32_t)e) : a.bval[e]; };
+            int tot1 = 0, cn1 = 0;
+            if (kept) {  // structure: as the symbolic phase stored it
+                for (int w = t; w < span; w += SG_WG) bits[w] = kept[w1 + w];
+                if (one_chunk) cn1 = stage(ab, true, true, &tot1);
+                else __syncthreads();
+            } else {
+                if (one_chunk) cn1 = stage(ab, true, true, &tot1);
+                for (int64_t cb = ab; cb < ae; cb += SG_WG) {
+                    int tot = tot1, cn = cn1;
+                    if (!one_chunk) cn = stage(cb, true, false, &tot);
+                    walk(cn, tot, [&](int (&)[SG_U], IX (&e)[SG_U]) {
                         int c[SG_U];
 #pragma unroll
-                        for (int u = 0; u < SG_U; ++u) c[u] = ok[u] ? a.bci[e[u]] : 0;
-                        if (pass == 0) {
+                        for (int u = 0; u < SG_U; ++u) c[u] = ldc(max(e[u], IX(0)));
 #pragma unroll
-                            for (int u = 0; u < SG_U; ++u) {
-                                const int d = (c[u] >> 5) - dbase;
-                                if (ok[u] && (unsigned)d < (unsigned)SG_NW) atomicOr(&bits[d], 1u << (c[u] & 31));
-                            }
-                        } else {
-                            VT v[SG_U];
-#pragma unroll
-                            for (int u = 0; u < SG_U; ++u) v[u] = ok[u] ? a.bval[e[u]] : VT(0);
-#pragma unroll
-                            for (int u = 0; u < SG_U; ++u) {
-                                const int d = (c[u] >> 5) - dbase;
-                                if (!ok[u] || (unsigned)d >= (unsigned)SG_NW) continue;
-                                const int r = (int)pre[d] + bits_below(bits[d], c[u] & 31);
-                                if (r < SG_CAP) {
-                                    if (acc2) A2::add(&vals2[r], st_a[klo + (int)wi[l + u * WAVE]], v[u]);
-                                    else A::add(&vals[r], st_a[klo + (int)wi[l + u * WAVE]], v[u]);
-                                }
-                            }
+                        for (int u = 0; u < SG_U; ++u) {
+                            const int d = (c[u] >> 5) - dbase;
+                            if (e[u] >= 0 && (unsigned)d < (unsigned)SG_NW) atomicOr(&bits[d], 1u << (c[u] & 31));
                         }
-                    }
+                    });
                     if (!one_chunk) __syncthreads();  // st_* are refilled for the next chunk
                 }
                 __syncthreads();
-                if (pass == 0) {
-                    // ranks: lane t scans words [t*SG_NW/SG_WG, ...) of the segment
-                    constexpr int WPL = SG_NW / SG_WG;
-                    const int wb = t * WPL;
-                    uint32_t wv[WPL];
-                    int sum = 0;
-#pragma unroll
-                    for (int u = 0; u < WPL; u += 4) {
-                        const uint4 q = *(const uint4 *)&bits[wb + u];
-                        wv[u] = q.x;
-                        wv[u + 1] = q.y;
-                        wv[u + 2] = q.z;
-                        wv[u + 3] = q.w;
-                    }
-#pragma unroll
-                    for (int u = 0; u < WPL; ++u) sum += __popc(wv[u]);
-                    long long tot;
-                    int run = (int)sg_block_excl_scan(sum, red, &tot);
-#pragma unroll
-                    for (int u = 0; u < WPL; ++u) {
-                        pre[wb + u] = (uint16_t)min(run, 65535);
-                        run += __popc(wv[u]);
-                    }
-                    if (tot != cnt) bad = 1;
-                    __syncthreads();
-                }
             }
+            {  // ranks: lane t scans words [t * SG_NW / SG_WG, ...) of the segment
+                constexpr int WPL = SG_NW / SG_WG;
+                const int wb = t * WPL;
+                uint32_t w[WPL];
+                int sum = 0;
+#pragma unroll
+                for (int u = 0; u < WPL; u += 4) {
+                    const uint4 q = *(const uint4 *)&bits[wb + u];
+                    w[u] = q.x;
+                    w[u + 1] = q.y;
+                    w[u + 2] = q.z;
+                    w[u + 3] = q.w;
+                }
+#pragma unroll
+                for (int u = 0; u < WPL; ++u) sum += __popc(w[u]);
+                long long tot;
+                int run = (int)sg_block_excl_scan(sum, red, &tot);
+#pragma unroll
+                for (int u = 0; u < WPL; ++u) {
+                    pre[wb + u] = (uint16_t)min(run, 65535);
+                    run += __popc(w[u]);
+                }
+                if (tot != cnt) bad = 1;
+                __syncthreads();
+            }
+            // values: each product added at its rank
+            for (int64_t cb = ab; cb < ae; cb += SG_WG) {
+                int tot = tot1, cn = cn1;
+                if (!one_chunk) cn = stage(cb, kept != nullptr, true, &tot);
+                walk(cn, tot, [&](int (&k)[SG_U], IX (&e)[SG_U]) {
+                    int c[SG_U];
+                    VT v[SG_U];
+#pragma unroll
+                    for (int u = 0; u < SG_U; ++u) c[u] = ldc(max(e[u], IX(0)));
+#pragma unroll
+                    for (int u = 0; u < SG_U; ++u) v[u] = ldv(max(e[u], IX(0)));
+#pragma unroll
+                    for (int u = 0; u < SG_U; ++u) {
+                        const int d = (c[u] >> 5) - dbase;
+                        if (e[u] < 0 || (unsigned)d >= (unsigned)SG_NW) continue;
+                        const int r = (int)pre[d] + bits_below(bits[d], c[u] & 31);
+                        if (r < SG_CAP) {
+                            if (acc2) A2::add(&vals2[r], st_a[k[u]], v[u]);
+                            else A::add(&vals[r], st_a[k[u]], v[u]);
+                        }
+                    }
+                });
+                if (!one_chunk) __syncthreads();  // st_* are refilled for the next chunk
+            }
+            __syncthreads();
             // write-out at the segment's offset, both arrays in rank order with
             // coalesced stores: first the values; then the columns, expanded
             // from the bits (one word per lane) into the freed value array;
@@ -453,7 +391,8 @@ template <typename VT, int ACC, int ACC2>
 hipError_t num_sg_impl(const NumArgs<VT> &a, const LaunchCfg &c) {
     int grid = c.grid;
     if (grid <= 0) grid = sg_resident_grid(ACC, ACC2, sizeof(VT) == 8, c.cus);
-    hipLaunchKernelGGL((k_num_sg<VT, ACC, ACC2>), dim3(grid), dim3(SG_WG), 0, c.stream, a);
+    if (a.b32) hipLaunchKernelGGL((k_num_sg<VT, ACC, ACC2, int32_t>), dim3(grid), dim3(SG_WG), 0, c.stream, a);
+    else hipLaunchKernelGGL((k_num_sg<VT, ACC, ACC2, int64_t>), dim3(grid), dim3(SG_WG), 0, c.stream, a);
     return hipGetLastError();
 }
 
@@ -470,12 +409,12 @@ int resident(K kernel, int cus) {
 }  // namespace
 
 int sg_resident_grid(int acc, int acc2, bool dbl, int cus) {
-    if (dbl) return resident(k_num_sg<double, ACC_NATIVE, ACC_NATIVE>, cus);
-    if (acc2 == ACC_WIDE && acc == ACC_NATIVE) return resident(k_num_sg<float, ACC_NATIVE, ACC_WIDE>, cus);
-    if (acc2 == ACC_WIDE && acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_WIDE>, cus);
-    if (acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_COMP>, cus);
-    if (acc == ACC_WIDE) return resident(k_num_sg<float, ACC_WIDE, ACC_WIDE>, cus);
-    return resident(k_num_sg<float, ACC_NATIVE, ACC_NATIVE>, cus);
+    if (dbl) return resident(k_num_sg<double, ACC_NATIVE, ACC_NATIVE, int64_t>, cus);
+    if (acc2 == ACC_WIDE && acc == ACC_NATIVE) return resident(k_num_sg<float, ACC_NATIVE, ACC_WIDE, int64_t>, cus);
+    if (acc2 == ACC_WIDE && acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_WIDE, int64_t>, cus);
+    if (acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_COMP, int64_t>, cus);
+    if (acc == ACC_WIDE) return resident(k_num_sg<float, ACC_WIDE, ACC_WIDE, int64_t>, cus);
+    return resident(k_num_sg<float, ACC_NATIVE, ACC_NATIVE, int64_t>, cus);
 }
 
 template <>
