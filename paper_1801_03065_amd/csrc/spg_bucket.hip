@@ -9,16 +9,19 @@
 //      (the owner of a product: run starts of the B rows marked in LDS and a
 //      max-scan), so no lane idles past the end of a B row;
 //   2. the row's column window is cut into as many equal buckets as the
-//      lanes hold products (a monotone map of the column), and an LDS counter per bucket gives every product
-//      its place in the bucket; a scan gives each bucket its place in the row;
+//      lanes hold products (a monotone map of the column); an LDS counter per
+//      bucket gives every product its place in the bucket, a scan gives each
+//      bucket its place in the row;
 //   3. a product's place in the sorted row is its bucket's start plus the
 //      products of the bucket that sort before it (about one other to look
 //      at when columns are spread evenly);
 //   4. products of one column are neighbours now: the first of them sums the
 //      run and writes the entry; without repeats the row is written as it is.
 //
-// Rows with a bucket of more than BK_DEEP products (columns clustered inside
-// the window) are sorted by a bitonic network instead of steps 2 and 3.
+// Rows with columns clustered inside the window (a bucket of more than BK_SPLIT
+// products: power-law graphs) cut every bucket again in proportion to its
+// products; the few that still have a bucket of more than BK_DEEP are sorted
+// by a bitonic network instead of steps 2 and 3.
 //
 // Rows of up to 512 products take one wavefront, of up to 1024 and 2048 two
 // and four (LDS and registers would leave one wavefront of 16 products per
@@ -40,7 +43,8 @@ namespace spg {
 
 namespace {
 
-constexpr int BK_DEEP = 24;  // products of one bucket above which the row is sorted by the network
+constexpr int BK_SPLIT = 12;  // products of one bucket above which the buckets are cut again (even columns: 5 to 7)
+constexpr int BK_DEEP = 24;   // and then above which the row is sorted by the network
 
 struct RowDescB {
     int64_t ab, cb, ce;
@@ -190,11 +194,12 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
             k[u] = max(bk_maxscan(k[u]), carry);
             carry = __builtin_amdgcn_readlane(k[u], WAVE - 1);
         }
-        uint32_t e[U];
+        uint32_t e[U], kp[(U + 3) / 4] = {};  // kp: the A entries (below 64) packed, four to a register
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = u * WAVE + p0;
             e[u] = p < f ? min((uint32_t)(st_rel[k[u]] + p), elast) : 0u;
+            kp[u / 4] |= (uint32_t)k[u] << (8 * (u % 4));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) col[u] = ld32(a.bci, e[u]);
@@ -214,23 +219,24 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
         }
         const int n = (int)n64;
 
-        // ---- buckets: monotone map of the window onto CAP buckets
+        // ---- buckets: monotone map of the window onto CAP buckets (the scale
+        // is rounded down, so the window's last column stays below CAP)
         const int c0 = d.wlo << 5;
         const float w = 32.0f * (float)d.nw;
-        const uint32_t scale =
-            (uint32_t)fminf((float)CAP * 4294967296.0f * __builtin_amdgcn_rcpf(w), 4294967040.0f);
-        int slot[U], b[U];
+        const uint32_t scale = (uint32_t)fminf((float)CAP * 4294967296.0f * 0.999998f * __builtin_amdgcn_rcpf(w),
+                                               4294967040.0f);
+        uint32_t bs[U];  // bucket | place in it << 16
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            b[u] = (int)min(__umulhi((uint32_t)(col[u] - c0), scale), (uint32_t)(CAP - 1));
-            slot[u] = 0;
-            if (u * WAVE + p0 < f) slot[u] = (int)atomicAdd(&cnt[b[u]], 1u);
-        }
-        bk_sync<NW>();
-        // bucket starts: lane t scans buckets [t * U, (t + 1) * U)
-        int deep;
-        {
-            uint32_t cc[U];
+        for (int u = 0; u < U; ++u)
+            bs[u] = min(__umulhi((uint32_t)(col[u] - c0), scale), (uint32_t)(CAP - 1));
+        // Places in the buckets, then the buckets' starts (cnt: start | count
+        // << 16); returns the largest bucket.
+        auto count = [&]() -> int {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * WAVE + p0 < f) bs[u] |= atomicAdd(&cnt[bs[u]], 1u) << 16;
+            bk_sync<NW>();
+            uint32_t cc[U];  // lane t scans buckets [t * U, (t + 1) * U)
             int sum = 0, mx = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) cc[u] = cnt[t * U + u];
@@ -240,18 +246,17 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
                 mx = max(mx, (int)cc[u]);
             }
             const int incs = wave_scan_dpp(sum);
-            int run = incs - sum;
-            deep = __builtin_amdgcn_readlane(bk_maxscan(mx), WAVE - 1);
+            int run = incs - sum, dp = __builtin_amdgcn_readlane(bk_maxscan(mx), WAVE - 1);
             if (NW > 1) {
                 if (l == WAVE - 1) {
                     red[wv] = incs;
-                    red[NW + wv] = deep;
+                    red[NW + wv] = dp;
                 }
                 bk_sync<NW>();
 #pragma unroll
                 for (int v = 0; v < NW; ++v) {
                     run += v < wv ? red[v] : 0;
-                    deep = max(deep, red[NW + v]);
+                    dp = max(dp, red[NW + v]);
                 }
             }
 #pragma unroll
@@ -259,32 +264,50 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
                 cnt[t * U + u] = (uint32_t)run | (cc[u] << 16);
                 run += (int)cc[u];
             }
+            bk_sync<NW>();
+            return read_first(dp);
+        };
+        int deep = count();
+        if (deep > BK_SPLIT) {
+            // Columns clustered in the window: each bucket is cut again into
+            // as many equal parts as it holds products.
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t xb = cnt[bs[u] & 0xFFFFu], part = (uint32_t)(col[u] - c0) * scale;  // place inside it
+                bs[u] = min((xb & 0xFFFFu) + __umulhi(part, xb >> 16), (uint32_t)(CAP - 1));
+            }
+            bk_sync<NW>();
+#pragma unroll
+            for (int u = 0; u < U; ++u) cnt[u * WG + t] = 0;
+            bk_sync<NW>();
+            deep = count();
         }
-        bk_sync<NW>();
 
-        // ---- place of each product in the sorted row
+        // ---- place of each product in the sorted row (left in bs)
         const bool net = deep > BK_DEEP;
         bool repeats = true;  // some column met twice
         if (!net) {
-            int st[U], pos[U];
+            uint32_t sc[U];  // bucket start | products << 16
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const uint32_t x = cnt[b[u]];
-                st[u] = (int)(x & 0xFFFFu);
-                b[u] = u * WAVE + p0 < f ? (int)(x >> 16) : 0;  // products of the bucket
-                pos[u] = st[u];
+                sc[u] = cnt[bs[u] & 0xFFFFu];
+                bs[u] >>= 16;
+                if (u * WAVE + p0 >= f) sc[u] = 0;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (u * WAVE + p0 < f) key[st[u] + slot[u]] = col[u];
+                if (u * WAVE + p0 < f) key[(sc[u] & 0xFFFFu) + bs[u]] = col[u];
             bk_sync<NW>();
             bool seen = false;
+            int pos[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) pos[u] = (int)(sc[u] & 0xFFFFu);
             for (int j = 0; j < deep; ++j) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (j < b[u]) {
-                        const int kj = key[st[u] + j];
-                        const bool same = kj == col[u] && j < slot[u];
+                    if (j < (int)(sc[u] >> 16)) {
+                        const int kj = key[(sc[u] & 0xFFFFu) + j];
+                        const bool same = kj == col[u] && j < (int)bs[u];
                         seen |= same;
                         pos[u] += (kj < col[u] || same) ? 1 : 0;
                     }
@@ -295,16 +318,16 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
             bk_sync<NW>();
             if (NW > 1) repeats = red[2 * NW] != 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) slot[u] = pos[u];
+            for (int u = 0; u < U; ++u) bs[u] = (uint32_t)pos[u];
         } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) slot[u] = u * WAVE + p0;
+            for (int u = 0; u < U; ++u) bs[u] = (uint32_t)(u * WAVE + p0);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (u * WAVE + p0 < f) {
-                key[slot[u]] = col[u];
-                val[slot[u]] = Term::term(st_a[k[u]], bv[u]);
+                key[bs[u]] = col[u];
+                val[bs[u]] = Term::term(st_a[(kp[u / 4] >> (8 * (u % 4))) & 0xFFu], bv[u]);
             }
         }
         if (net) {
