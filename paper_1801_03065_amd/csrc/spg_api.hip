@@ -88,7 +88,7 @@ struct spg_handle_s {
     bool segmented = false;             // the symbolic phase wrote segment lists into plan
     spg_stats stats{};
 
-    DevBuf arp64, brp64, binfo, ulist, uflag, bcrp, bcw, rflops, rflopsc, rwin, row_nnz, coff, kind_sym,
+    DevBuf arp64, brp64, binfo, uflag, bcrp, bcw, rflops, rflopsc, rwin, row_nnz, coff, kind_sym,
         kind_num, perm_sym, perm_num, koff_sym, koff_num, tmp, dstats, red, queue, plan_len, plan_off, plan, arena, l2k, l2v, blens, row_words;
     size_t arena_bytes_zeroed = 0;
     const int32_t *aci_used = nullptr, *bci_used = nullptr;  // column arrays the kernels read
@@ -348,7 +348,7 @@ spg_status spg_create(spg_handle *out, void *stream, const spg_options *opt) {
 spg_status spg_destroy(spg_handle h) {
     if (!h) return SPG_ERR_INVALID_ARG;
     (void)hipStreamSynchronize(h->stream);
-    DevBuf *bufs[] = {&h->arp64, &h->brp64, &h->binfo, &h->ulist, &h->uflag, &h->bcrp, &h->bcw,
+    DevBuf *bufs[] = {&h->arp64, &h->brp64, &h->binfo, &h->uflag, &h->bcrp, &h->bcw,
                       &h->rflops, &h->rflopsc, &h->rwin, &h->row_nnz, &h->coff, &h->kind_sym, &h->kind_num,
                       &h->perm_sym, &h->perm_num, &h->koff_sym, &h->koff_num, &h->tmp, &h->dstats, &h->red, &h->queue, &h->plan_len, &h->plan_off, &h->plan,
                       &h->arena, &h->l2k, &h->l2v, &h->blens, &h->row_words, &h->kind_tmp, &h->perm_tmp, &h->koff_tmp, &h->krange, &h->kind_heavy, &h->perm_heavy, &h->koff_heavy, &h->krange_heavy, &h->sgcur, &h->sgb, &h->sgb_off, &h->sgb_len, &h->mflops, &h->map_off, &h->map,
@@ -402,7 +402,6 @@ static spg_status plan_buffers(spg_handle h, int64_t m, int64_t n, int64_t nnzb)
     HIPCHK(ensure(h->arp64, 8 * (m + 1)));
     HIPCHK(ensure(h->brp64, 8 * (n + 1)));
     HIPCHK(ensure(h->binfo, sizeof(BRow) * std::max<int64_t>(n, 1)));
-    HIPCHK(ensure(h->ulist, 4 * std::max<int64_t>(n, 1)));
     HIPCHK(ensure(h->uflag, 4 * ((std::max<int64_t>(n, 1) + 3) / 4)));
     HIPCHK(ensure(h->bcrp, 8 * (n + 1)));
     HIPCHK(ensure(h->rflops, 8 * std::max<int64_t>(m, 1)));
@@ -455,8 +454,8 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     // Everything up to the first host sync runs on unchecked input: row
     // pointers are clamped copies, columns out of range only raise the flag
     // (k_brow, k_rowinfo) and are never used as indices before the sync.
-    HIPCHK(launch_brow(n, nnzb, k, brp, bci, bi, h->ulist.as<int32_t>(), h->uflag.as<uint8_t>(), dst, st));
-    HIPCHK(launch_brow_unsorted(h->ulist.as<int32_t>(), &dst->unsorted, brp, bci, bi, dst, st));
+    HIPCHK(launch_brow(n, nnzb, k, brp, bci, bi, h->uflag.as<uint8_t>(), dst, st));
+    HIPCHK(launch_brow_unsorted(n, h->uflag.as<uint8_t>(), brp, bci, bi, dst, st));
     const bool sel = h->opt.accumulator == SPG_ACC_AUTO;
     HIPCHK(launch_rowinfo(m, n, arp, aci, bi, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(),
                           h->rwin.as<int2>(), dst, h->red.as<long long>(), h->opt.compression, sel ? 1 : 0,
@@ -470,7 +469,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         HIPCHK(launch_scan_i32s(n, &bi->lenc, 4, h->bcrp.as<int64_t>(), h->tmp.as<int64_t>(), cflag, st));
         HIPCHK(launch_compress_sorted_flags(n, nnzb, brp, bci, bi, h->uflag.as<uint8_t>(), h->bcrp.as<int64_t>(),
                                             h->bcw.as<uint2>(), cflag, st));
-        HIPCHK(launch_compress_unsorted(h->ulist.as<int32_t>(), &dst->unsorted, brp, bci, bi,
+        HIPCHK(launch_compress_unsorted(n, h->uflag.as<uint8_t>(), &dst->unsorted, brp, bci, bi,
                                         h->bcrp.as<int64_t>(), h->bcw.as<uint2>(), cflag,
                                         st));
     }

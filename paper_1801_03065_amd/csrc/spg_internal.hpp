@@ -51,7 +51,8 @@ struct DevStats {
     unsigned long long maxnnza;    // longest row of A
     unsigned long long nnzc;
     int bad_input;    // malformed CSR (row_ptr not monotone / not ending at nnz, column out of range)
-    int unsorted;     // B rows whose columns are not sorted
+    int unsorted;     // some row of B has its columns out of order
+    int uncounted;    // ... and is too long to be counted by the row statistics kernel
     int bad_window;   // unsorted B rows too wide for the LDS window
     int mismatch;     // numeric: row size differs from the plan
     int overflow;     // level-2 arena exhausted
@@ -354,18 +355,18 @@ struct LaunchCfg {
 };
 
 // Per row of B: length, distinct column-set words, word window, sortedness
-// (uflag, and the list of unsorted rows); columns out of [0, ncols) raise the
-// malformed-input flag.
+// (uflag); columns out of [0, ncols) raise the malformed-input flag.
 hipError_t launch_brow(int64_t n, int64_t nnz, int64_t ncols, const int64_t *brp, const int32_t *bci, BRow *out,
-                       int32_t *unsorted_list, uint8_t *uflag, DevStats *st, hipStream_t s);
-hipError_t launch_brow_unsorted(const int32_t *list, const int *count, const int64_t *brp, const int32_t *bci,
-                                BRow *out, DevStats *st, hipStream_t s);
+                       uint8_t *uflag, DevStats *st, hipStream_t s);
+// Words of the unsorted rows that launch_brow left uncounted.
+hipError_t launch_brow_unsorted(int64_t n, const uint8_t *uflag, const int64_t *brp, const int32_t *bci, BRow *out,
+                                DevStats *st, hipStream_t s);
 // The compression kernels and the scan take `enable` (device flag, nullable):
 // they do nothing when it reads 0.
 hipError_t launch_compress_sorted_flags(int64_t n, int64_t nnz, const int64_t *brp, const int32_t *bci, const BRow *bi,
                                         const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw,
                                         const int *enable, hipStream_t s);
-hipError_t launch_compress_unsorted(const int32_t *list, const int *count, const int64_t *brp,
+hipError_t launch_compress_unsorted(int64_t n, const uint8_t *uflag, const int *any, const int64_t *brp,
                                     const int32_t *bci, const BRow *bi, const int64_t *bcrp, uint2 *bcw,
                                     const int *enable, hipStream_t s);
 // Per-block partials of the rowinfo reduction (folded by a one-workgroup
