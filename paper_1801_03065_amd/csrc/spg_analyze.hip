@@ -216,11 +216,9 @@ __global__ __launch_bounds__(BLK) void k_brow_short(int64_t n, int64_t ncols, co
 // in word order.  `any` (device): 0 when there is no such row.
 __global__ __launch_bounds__(WAVE) void k_brow_unsorted(int64_t n, const uint8_t *uflag, int least, const int *any,
                                                          const int64_t *brp, const int32_t *bci, BRow *bi,
-                                                         const int64_t *bcrp, uint2 *bcw, int mode, DevStats *st,
-                                                         const int *enable) {
+                                                         const int64_t *bcrp, uint2 *bcw, int mode, DevStats *st) {
     __shared__ uint32_t bits[UB_WORDS];
     const int l = lane_id();
-    if (enable && !*enable) return;
     if (!*any) return;
     for (int w = l; w < UB_WORDS; w += WAVE) bits[w] = 0;
     wave_lds_sync();
@@ -272,8 +270,7 @@ __global__ __launch_bounds__(WAVE) void k_brow_unsorted(int64_t n, const uint8_t
 // bits there.
 __global__ __launch_bounds__(BLK) void k_compress_sorted(int64_t n, const int64_t *brp, const int32_t *bci,
                                                           const BRow *bi, const uint8_t *unsorted,
-                                                          const int64_t *bcrp, uint2 *bcw, const int *enable) {
-    if (enable && !*enable) return;
+                                                          const int64_t *bcrp, uint2 *bcw) {
     const int q = threadIdx.x & (BR_GS - 1);
     const int64_t g0 = ((int64_t)blockIdx.x * BLK + threadIdx.x) / BR_GS;
     const int64_t ng = (int64_t)gridDim.x * BLK / BR_GS;
@@ -325,9 +322,7 @@ __global__ __launch_bounds__(BLK) void k_compress_sorted(int64_t n, const int64_
 // The same for B with short rows: one lane per row walks its columns and
 // writes each word run where it ends.
 __global__ __launch_bounds__(BLK) void k_compress_short(int64_t n, const int64_t *brp, const int32_t *bci,
-                                                         const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw,
-                                                         const int *enable) {
-    if (enable && !*enable) return;
+                                                         const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw) {
     for (int64_t r = (int64_t)blockIdx.x * BLK + threadIdx.x; r < n; r += (int64_t)gridDim.x * BLK) {
         if (unsorted[r]) continue;
         const int64_t b = brp[r], e = brp[r + 1];
@@ -766,7 +761,7 @@ static_assert(NK == 13 && NK_PAD == 16, "the partition reads a workgroup's kind 
 
 __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, const uint8_t *kind, const int32_t *blk,
                                                       int32_t *perm, int64_t *koff, int phase, int heavy,
-                                                      DevStats *st) {
+                                                      DevStats *st, DevStats *host) {
     constexpr int NW = CB / WAVE;
     static_assert(CL_R * NW * NK <= CB, "one thread clears each count");
     __shared__ int wcnt[CL_R * NW][NK];
@@ -872,6 +867,13 @@ __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, cons
         long long *gc = phase == 0 ? &st->kcount_sym[k] : heavy ? &st->kcount_heavy[k] : &st->kcount_num[k];
         *gc += stot[k];
     }
+    // the statistics are complete now: workgroup 0 leaves them in host memory
+    // (visible there when the kernel ends), which saves a copy command
+    if (b == 0 && host) {
+        __syncthreads();
+        static_assert(sizeof(DevStats) % 4 == 0, "copied by words");
+        for (int w = t; w < (int)(sizeof(DevStats) / 4); w += CB) ((int32_t *)host)[w] = ((const volatile int32_t *)st)[w];
+    }
     // rows of this workgroup, stable within each kind: counts per wavefront
     // and row of the lane, their prefix per kind, then each row's place
     int k[CL_R], rank[CL_R];
@@ -911,12 +913,9 @@ __global__ __launch_bounds__(CB) void k_part_scatter(int64_t m, int64_t nb, cons
 constexpr int SC_T = 256, SC_E = 8, SC_B = SC_T * SC_E;
 
 // Local scans with block sums, one workgroup scans the block sums (total to
-// out[n]), then the block offsets are added.  enable (optional, device): when
-// it reads 0 the scan is skipped.
+// out[n]), then the block offsets are added.
 template <typename T>
-__global__ __launch_bounds__(SC_T) void k_scan_local(int64_t n, const T *in, int stride, int64_t *out, int64_t *bsum,
-                                                      const int *enable) {
-    if (enable && !*enable) return;
+__global__ __launch_bounds__(SC_T) void k_scan_local(int64_t n, const T *in, int stride, int64_t *out, int64_t *bsum) {
     __shared__ long long wsum[SC_T / WAVE];
     const int t = threadIdx.x, l = lane_id(), wv = t / WAVE;
     const int64_t base = (int64_t)blockIdx.x * SC_B + (int64_t)t * SC_E;
@@ -942,8 +941,7 @@ __global__ __launch_bounds__(SC_T) void k_scan_local(int64_t n, const T *in, int
 }
 
 // Exclusive scan of the block totals in one workgroup (many blocks only).
-__global__ __launch_bounds__(SC_T) void k_scan_top(int64_t nb, int64_t *bsum, const int *enable) {
-    if (enable && !*enable) return;
+__global__ __launch_bounds__(SC_T) void k_scan_top(int64_t nb, int64_t *bsum) {
     __shared__ long long wsum[SC_T / WAVE];
     __shared__ long long carry;
     const int t = threadIdx.x, l = lane_id(), wv = t / WAVE;
@@ -972,11 +970,10 @@ __global__ __launch_bounds__(SC_T) void k_scan_top(int64_t nb, int64_t *bsum, co
 // last block stores the grand total at out[n].  With few blocks (SC_FEW) every
 // block reduces its own prefix of the raw totals, saving the one-workgroup
 // scan launch; with more, k_scan_top has replaced them by their exclusive
-// scan (and the grand total at bsum[nb]).
+// scan (and the grand total at bsum[nb]).  o: copies of the result and the
+// total (see ScanOut).
 constexpr int64_t SC_FEW = 1024;
-__global__ __launch_bounds__(SC_T) void k_scan_add(int64_t n, int64_t nb, int64_t *out, const int64_t *bsum,
-                                                    const int *enable) {
-    if (enable && !*enable) return;
+__global__ __launch_bounds__(SC_T) void k_scan_add(int64_t n, int64_t nb, int64_t *out, const int64_t *bsum, ScanOut o) {
     __shared__ long long wsum[SC_T / WAVE];
     const int t = threadIdx.x, l = lane_id(), wv = t / WAVE;
     const int64_t b = blockIdx.x;
@@ -994,18 +991,22 @@ __global__ __launch_bounds__(SC_T) void k_scan_add(int64_t n, int64_t nb, int64_
     }
     const int64_t base = b * SC_B;
     for (int e = t; e < SC_B; e += SC_T)
-        if (base + e < n) out[base + e] += add;
-    if (b == nb - 1 && t == 0) out[n] = nb <= SC_FEW ? add + bsum[b] : bsum[nb];
+        if (base + e < n) {
+            const int64_t v = out[base + e] + add;
+            out[base + e] = v;
+            if (o.rp32) o.rp32[base + e] = (int32_t)v;
+            if (o.rp64) o.rp64[base + e] = v;
+        }
+    if (b == nb - 1 && t == 0) {
+        const int64_t v = nb <= SC_FEW ? add + bsum[b] : bsum[nb];
+        out[n] = v;
+        if (o.rp32) o.rp32[n] = (int32_t)v;
+        if (o.rp64) o.rp64[n] = v;
+        if (o.total) *o.total = (unsigned long long)v;
+        if (o.host_total) *o.host_total = v;
+    }
 }
 
-__global__ __launch_bounds__(BLK) void k_store_rp32(int64_t n1, const int64_t *src, int32_t *dst) {
-    for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n1; i += (int64_t)gridDim.x * BLK)
-        dst[i] = (int32_t)src[i];
-}
-__global__ __launch_bounds__(BLK) void k_store_rp64(int64_t n1, const int64_t *src, int64_t *dst) {
-    for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n1; i += (int64_t)gridDim.x * BLK)
-        dst[i] = src[i];
-}
 __global__ __launch_bounds__(BLK) void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
     for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) p[i] = v;
 }
@@ -1067,28 +1068,27 @@ constexpr int UB_GRID = 512;  // two 64 KB-LDS workgroups per CU are resident: o
 hipError_t launch_brow_unsorted(int64_t n, const uint8_t *uflag, const int64_t *brp, const int32_t *bci, BRow *out,
                                 DevStats *st, hipStream_t s) {
     hipLaunchKernelGGL(k_brow_unsorted, dim3(UB_GRID), dim3(WAVE), 0, s, n, uflag, (int)UF_UNCOUNTED, &st->uncounted,
-                       brp, bci, out, (const int64_t *)nullptr, (uint2 *)nullptr, 0, st, (const int *)nullptr);
+                       brp, bci, out, (const int64_t *)nullptr, (uint2 *)nullptr, 0, st);
     return hipGetLastError();
 }
 
 hipError_t launch_compress_unsorted(int64_t n, const uint8_t *uflag, const int *any, const int64_t *brp,
                                     const int32_t *bci, const BRow *bi, const int64_t *bcrp, uint2 *bcw,
-                                    const int *enable, hipStream_t s) {
+                                    hipStream_t s) {
     hipLaunchKernelGGL(k_brow_unsorted, dim3(UB_GRID), dim3(WAVE), 0, s, n, uflag, (int)UF_UNSORTED, any, brp, bci,
-                       (BRow *)bi, bcrp, bcw, 1, (DevStats *)nullptr, enable);
+                       (BRow *)bi, bcrp, bcw, 1, (DevStats *)nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_compress_sorted_flags(int64_t n, int64_t nnz, const int64_t *brp, const int32_t *bci, const BRow *bi,
-                                        const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw,
-                                        const int *enable, hipStream_t s) {
+                                        const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (nnz <= BR_SHORT * n)
         hipLaunchKernelGGL(k_compress_short, dim3(grid_for(n, BLK, 4096)), dim3(BLK), 0, s, n, brp, bci, unsorted,
-                           bcrp, bcw, enable);
+                           bcrp, bcw);
     else
         hipLaunchKernelGGL(k_compress_sorted, dim3(grid_for(n * BR_GS, BLK, 8192)), dim3(BLK), 0, s, n, brp, bci, bi,
-                           unsorted, bcrp, bcw, enable);
+                           unsorted, bcrp, bcw);
     return hipGetLastError();
 }
 
@@ -1105,35 +1105,24 @@ hipError_t launch_rowinfo(int64_t m, int64_t n, const int64_t *arp, const int32_
 // tmp: block sums
 int64_t scan_tmp_elems(int64_t n) { return (n + SC_B - 1) / SC_B + 1; }
 
-template <typename T>
-static hipError_t scan_impl(int64_t n, const T *in, int stride, int64_t *out, int64_t *tmp, const int *enable,
-                            hipStream_t s) {
+hipError_t launch_scan_i32(int64_t n, const int32_t *in, int stride, int64_t *out, int64_t *tmp, const ScanOut &o,
+                           hipStream_t s) {
     const int64_t nb = (n + SC_B - 1) / SC_B;
     if (nb > 0) {
-        hipLaunchKernelGGL(k_scan_local<T>, dim3((unsigned)nb), dim3(SC_T), 0, s, n, in, stride, out, tmp, enable);
-        if (nb > SC_FEW) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SC_T), 0, s, nb, tmp, enable);
-        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(SC_T), 0, s, n, nb, out, tmp, enable);
-    } else {
+        hipLaunchKernelGGL(k_scan_local<int32_t>, dim3((unsigned)nb), dim3(SC_T), 0, s, n, in, stride, out, tmp);
+        if (nb > SC_FEW) hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SC_T), 0, s, nb, tmp);
+        hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(SC_T), 0, s, n, nb, out, tmp, o);
+    } else {  // nothing to scan: out[0] and its copies are 0
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, (int32_t *)out, (int64_t)2, 0);
+        if (o.rp32) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, o.rp32, (int64_t)1, 0);
+        if (o.rp64) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, (int32_t *)o.rp64, (int64_t)2, 0);
+        if (o.total) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, (int32_t *)o.total, (int64_t)2, 0);
+        if (o.host_total) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(BLK), 0, s, (int32_t *)o.host_total, (int64_t)2, 0);
     }
     return hipGetLastError();
 }
-
-hipError_t launch_scan_i32s(int64_t n, const int32_t *in, int stride, int64_t *out, int64_t *tmp, const int *enable,
-                            hipStream_t s) {
-    return scan_impl<int32_t>(n, in, stride, out, tmp, enable, s);
-}
 hipError_t launch_scan_i32(int64_t n, const int32_t *in, int64_t *out, int64_t *tmp, hipStream_t s) {
-    return scan_impl<int32_t>(n, in, 1, out, tmp, nullptr, s);
-}
-
-hipError_t launch_store_rp(int64_t n1, const int64_t *src, void *dst, int is64, hipStream_t s) {
-    const int g = grid_for(n1, BLK);
-    if (is64)
-        hipLaunchKernelGGL(k_store_rp64, dim3(g), dim3(BLK), 0, s, n1, src, (int64_t *)dst);
-    else
-        hipLaunchKernelGGL(k_store_rp32, dim3(g), dim3(BLK), 0, s, n1, src, (int32_t *)dst);
-    return hipGetLastError();
+    return launch_scan_i32(n, in, 1, out, tmp, ScanOut{}, s);
 }
 
 hipError_t launch_classify(int64_t m, const int64_t *rflops, const int64_t *rflopsc, const int2 *rwin,
@@ -1156,13 +1145,13 @@ hipError_t launch_classify(int64_t m, const int64_t *rflops, const int64_t *rflo
 int64_t part_tmp_elems(int64_t m) { return (((m + CR - 1) / CR) * (4 * NK + NK_PAD) + NK + 1) / 2 + 1; }
 
 hipError_t launch_partition(int64_t m, const uint8_t *kind, int32_t *perm, const int64_t *tmp, int64_t *koff,
-                            int phase, int heavy, DevStats *st, hipStream_t s) {
+                            int phase, int heavy, DevStats *st, DevStats *host, hipStream_t s) {
     const int64_t nb = (m + CR - 1) / CR;
     if (nb == 0) return hipSuccess;
     if (nb > PF_FEW)
         hipLaunchKernelGGL(k_part_fold, dim3(1), dim3(CB), 0, s, nb, (int32_t *)tmp + 4 * nb * NK);
     hipLaunchKernelGGL(k_part_scatter, dim3((unsigned)nb), dim3(CB), 0, s, m, nb, kind, (const int32_t *)tmp, perm,
-                       koff, phase, heavy, st);
+                       koff, phase, heavy, st, host);
     return hipGetLastError();
 }
 

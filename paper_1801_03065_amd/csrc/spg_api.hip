@@ -82,7 +82,8 @@ struct spg_handle_s {
     bool compressed = false;
     double avg_len = 1, avg_len_c = 1;  // B entries (raw / compressed) read per A entry
     DevStats *hst = nullptr;            // pinned host copy of the device counters
-    int64_t *hkoff = nullptr;           // pinned: [0] nnz(C), [1] stored-structure pairs
+    int64_t *hkoff = nullptr;           // pinned totals: [0] nnz(C), [1] stored-structure pairs, [2] pairs of
+                                        // compressed B, [3] mapped products, [4] kept window words, [5] error flags
     bool planned = false;               // the symbolic phase stored row structure (K_PL rows)
     bool sg_mode = false;               // heavy rows run in segments (B's rows sorted)
     bool segmented = false;             // the symbolic phase wrote segment lists into plan
@@ -324,8 +325,8 @@ spg_status spg_create(spg_handle *out, void *stream, const spg_options *opt) {
     if (e == hipSuccess) e = hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device);
     int lds = 0;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, h->device);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&h->hst, sizeof(DevStats), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&h->hkoff, sizeof(int64_t) * (2 * (NK + 1) + 2), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&h->hst, sizeof(DevStats), hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&h->hkoff, sizeof(int64_t) * (2 * (NK + 1) + 2), hipHostMallocCoherent);
     if (e == hipSuccess) e = ensure(h->dstats, sizeof(DevStats));
     if (e == hipSuccess) e = ensure(h->red, sizeof(long long) * RED_ELEMS);
     if (e == hipSuccess) e = ensure(h->queue, sizeof(int32_t) * XCDS * NK);
@@ -384,11 +385,15 @@ spg_status spg_get_stats(spg_handle h, spg_stats *out) {
 
 spg_status spg_check_errors(spg_handle h) {
     if (!h) return SPG_ERR_INVALID_ARG;
-    spg_status s = pull_stats(h);
-    if (s != SPG_OK) return s;
-    const int mism = h->hst->mismatch, ovf = h->hst->overflow;
+    // the two flags only: the statistics in host memory belong to the plan
+    static_assert(offsetof(DevStats, overflow) == offsetof(DevStats, mismatch) + sizeof(int), "copied together");
+    int *flags = (int *)(h->hkoff + 5);
+    char *dev = (char *)h->dstats.p + offsetof(DevStats, mismatch);
+    HIPCHK(hipMemcpyAsync(flags, dev, 2 * sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    const int mism = flags[0], ovf = flags[1];
     if (mism || ovf) {
-        HIPCHK(hipMemsetAsync((char *)h->dstats.p + offsetof(DevStats, mismatch), 0, 2 * sizeof(int), h->stream));
+        HIPCHK(hipMemsetAsync(dev, 0, 2 * sizeof(int), h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
     }
     if (mism) return fail(h, SPG_ERR_STRUCTURE_MISMATCH, std::to_string(mism) + " rows differ from the plan");
@@ -444,8 +449,10 @@ static void rows_numeric_stats(spg_stats &o, const DevStats &hs, bool split, con
 // The symbolic phase on validated, device-resident structure: h->arp64 (m+1),
 // h->brp64 (n+1) as int64, A's columns aci (row indices of B) and B's columns
 // bci.  Leaves the plan in the handle and C's int64 row offsets in h->coff.
+// c_rp (nullable): C's row pointers, int32 or int64, written with them.
 static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, int64_t nnza, int64_t nnzb,
-                                const int32_t *aci, const int32_t *bci, int64_t *nnzc_out) {
+                                const int32_t *aci, const int32_t *bci, int64_t *nnzc_out, void *c_rp = nullptr,
+                                bool c_rp64 = false) {
     spg_status s;
     hipStream_t st = h->stream;
     DevStats *dst = h->dstats.as<DevStats>();
@@ -460,19 +467,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     HIPCHK(launch_rowinfo(m, n, arp, aci, bi, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(),
                           h->rwin.as<int2>(), dst, h->red.as<long long>(), h->opt.compression, sel ? 1 : 0,
                           h->opt.cf_threshold, st));
-    // compressed B (Compression subsection): lengths -> offsets -> (word, bits)
-    // pairs, built when the analysis decided so (dst->comp, on the device)
-    const int *cflag = &dst->comp;
-    if (h->opt.compression != 0) {
-        HIPCHK(ensure(h->bcw, 8 * std::max<int64_t>(nnzb, 1)));
-        static_assert(sizeof(BRow) == 4 * sizeof(int32_t), "BRow is four int32");
-        HIPCHK(launch_scan_i32s(n, &bi->lenc, 4, h->bcrp.as<int64_t>(), h->tmp.as<int64_t>(), cflag, st));
-        HIPCHK(launch_compress_sorted_flags(n, nnzb, brp, bci, bi, h->uflag.as<uint8_t>(), h->bcrp.as<int64_t>(),
-                                            h->bcw.as<uint2>(), cflag, st));
-        HIPCHK(launch_compress_unsorted(n, h->uflag.as<uint8_t>(), &dst->unsorted, brp, bci, bi,
-                                        h->bcrp.as<int64_t>(), h->bcw.as<uint2>(), cflag,
-                                        st));
-    }
+    const int *cflag = &dst->comp;  // compress B: decided by the analysis, on the device
 
     ClassParams cp{};
     cp.phase = 0;
@@ -511,15 +506,35 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
                            nullptr, cp, h->kind_sym.as<uint8_t>(), h->row_nnz.as<int32_t>(), dst, h->tmp.as<int64_t>(),
                            h->koff_sym.as<int64_t>(), st));
     HIPCHK(launch_partition(m, h->kind_sym.as<uint8_t>(), h->perm_sym.as<int32_t>(), h->tmp.as<int64_t>(),
-                            h->koff_sym.as<int64_t>(), cp.phase, cp.heavy, dst, st));
+                            h->koff_sym.as<int64_t>(), cp.phase, cp.heavy, dst, h->hst, st));
     // host sync 1: input checks, flop counts, compression, per-kind sizes
-    if ((s = pull_stats(h)) != SPG_OK) return s;
+    // (left in host memory by the partition; without rows there was none)
+    if (m > 0)
+        HIPCHK(hipStreamSynchronize(st));
+    else if ((s = pull_stats(h)) != SPG_OK)
+        return s;
     const DevStats hs2 = *h->hst;
     const DevStats &hs1 = hs2;
     if (hs1.bad_input) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: row_ptr or col_idx out of range");
     // (an unsorted row of B wider than the LDS bitmap of its word count makes
     // the analysis skip compression: the structure kernels read raw B)
     const bool comp = h->opt.compression != 0 && hs1.comp != 0;
+    if (comp) {
+        // compressed B (Compression subsection): lengths -> offsets -> (word,
+        // bits) pairs.  Launched once the host knows the decision: on the
+        // device's own flag these were four empty launches (12 to 25 us) for
+        // every product that does not compress.
+        HIPCHK(ensure(h->bcw, 8 * std::max<int64_t>(nnzb, 1)));
+        static_assert(sizeof(BRow) == 4 * sizeof(int32_t), "BRow is four int32");
+        ScanOut so;
+        so.host_total = h->hkoff + 2;
+        HIPCHK(launch_scan_i32(n, &bi->lenc, 4, h->bcrp.as<int64_t>(), h->tmp.as<int64_t>(), so, st));
+        HIPCHK(launch_compress_sorted_flags(n, nnzb, brp, bci, bi, h->uflag.as<uint8_t>(), h->bcrp.as<int64_t>(),
+                                            h->bcw.as<uint2>(), st));
+        if (hs1.unsorted)
+            HIPCHK(launch_compress_unsorted(n, h->uflag.as<uint8_t>(), &dst->unsorted, brp, bci, bi,
+                                            h->bcrp.as<int64_t>(), h->bcw.as<uint2>(), st));
+    }
     const double fm = (double)hs1.fm, fmc = (double)hs1.fmc;
     h->avg_len = nnza ? std::max(1.0, fm / (double)nnza) : 1.0;
     h->avg_len_c = nnza ? std::max(1.0, (comp ? fmc : fm) / (double)nnza) : 1.0;
@@ -648,29 +663,46 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         HIPCHK(launch_sym_hl(sa, lc));
     }
 
-    // scan -> C row offsets (int64 plan copy), then the numeric classification
-    HIPCHK(launch_scan_i32(m, h->row_nnz.as<int32_t>(), h->coff.as<int64_t>(), h->tmp.as<int64_t>(), st));
+    // scan -> C row offsets (int64 plan copy, and the caller's row pointers),
+    // then the numeric classification
+    const long long thr = h->opt.fp64_heavy_row_flops;
+    const long long tmax = fp32_terms_limit(h->opt);
+    // (no separate lists unless some row of A is longer than the term limit)
+    const bool split = thr > 0 || (tmax > 0 && (long long)hs1.maxnnza > tmax);
+    // Short rows stay short rows, so where all rows with products are short
+    // the symbolic lists are the numeric ones and no classification runs
+    // (two launches: 10 us at 4096 rows, 16 us at a million).
+    const bool all_short = sel && !split && m > 0 && hs2.kcount_sym[K_SR] + hs2.kcount_sym[K_EMPTY] == m;
+    ScanOut so;
+    so.rp32 = c_rp64 ? nullptr : (int32_t *)c_rp;
+    so.rp64 = c_rp64 ? (int64_t *)c_rp : nullptr;
+    so.total = &dst->nnzc;
+    so.host_total = all_short ? h->hkoff : nullptr;
+    HIPCHK(launch_scan_i32(m, h->row_nnz.as<int32_t>(), 1, h->coff.as<int64_t>(), h->tmp.as<int64_t>(), so, st));
     cp.phase = 1;
     cp.words_out = nullptr;
     cp.sgb_len = nullptr;
     cp.plan_cap = h->planned ? PL_CAP : 0;
     cp.sym_kind = h->kind_sym.as<uint8_t>();
     cp.sg = h->sg_mode ? 1 : 0;
-    const long long thr = h->opt.fp64_heavy_row_flops;
-    const long long tmax = fp32_terms_limit(h->opt);
-    // (no separate lists unless some row of A is longer than the term limit)
-    const bool split = thr > 0 || (tmax > 0 && (long long)hs1.maxnnza > tmax);
     cp.heavy_flops = thr > 0 ? thr : 0;
     cp.heavy_alen = tmax > 0 ? tmax : 0;
     cp.arp = arp;
     cp.bk = nnzb < (int64_t(1) << 29) ? 1 : 0;  // 32-bit byte offsets into B
     cp.split = split ? 1 : 0;
     cp.heavy = 0;
-    HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
-                           h->row_nnz.as<int32_t>(), h->row_words.as<int32_t>(), cp, h->kind_num.as<uint8_t>(),
-                           nullptr, dst, h->tmp.as<int64_t>(), h->koff_num.as<int64_t>(), st));
-    HIPCHK(launch_partition(m, h->kind_num.as<uint8_t>(), h->perm_num.as<int32_t>(), h->tmp.as<int64_t>(),
-                            h->koff_num.as<int64_t>(), cp.phase, cp.heavy, dst, st));
+    if (all_short) {
+        std::swap(h->kind_sym, h->kind_num);
+        std::swap(h->perm_sym, h->perm_num);
+        std::swap(h->koff_sym, h->koff_num);
+        cp.sym_kind = h->kind_num.as<uint8_t>();  // (a row's kind is read before it is replaced)
+    } else {
+        HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
+                               h->row_nnz.as<int32_t>(), h->row_words.as<int32_t>(), cp, h->kind_num.as<uint8_t>(),
+                               nullptr, dst, h->tmp.as<int64_t>(), h->koff_num.as<int64_t>(), st));
+        HIPCHK(launch_partition(m, h->kind_num.as<uint8_t>(), h->perm_num.as<int32_t>(), h->tmp.as<int64_t>(),
+                                h->koff_num.as<int64_t>(), cp.phase, cp.heavy, dst, split ? nullptr : h->hst, st));
+    }
     h->heavy_split = false;
     if (split) {  // FP64-accumulated rows: their own kind lists (FP64 accumulation in FP32 mode)
         HIPCHK(ensure(h->kind_heavy, std::max<int64_t>(m, 1)));
@@ -683,18 +715,24 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
                                h->kind_heavy.as<uint8_t>(), nullptr, dst, h->tmp.as<int64_t>(),
                                h->koff_heavy.as<int64_t>(), st));
         HIPCHK(launch_partition(m, h->kind_heavy.as<uint8_t>(), h->perm_heavy.as<int32_t>(), h->tmp.as<int64_t>(),
-                                h->koff_heavy.as<int64_t>(), ch.phase, ch.heavy, dst, st));
+                                h->koff_heavy.as<int64_t>(), ch.phase, ch.heavy, dst, h->hst, st));
     }
-    HIPCHK(hipMemcpyAsync(h->hkoff, h->coff.as<int64_t>() + m, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    h->hkoff[2] = 0;
-    if (comp)  // pairs of compressed B: the end of its row offsets
-        HIPCHK(hipMemcpyAsync(h->hkoff + 2, h->bcrp.as<int64_t>() + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    if ((s = pull_stats(h)) != SPG_OK) return s;  // host sync 2: nnz(C), numeric kinds
+    // host sync 2: nnz(C), numeric kinds
+    if (m > 0)
+        HIPCHK(hipStreamSynchronize(st));
+    else if ((s = pull_stats(h)) != SPG_OK)
+        return s;
+    if (all_short) {
+        h->hst->nnzc = (unsigned long long)h->hkoff[0];
+        for (int kk = 0; kk < NK; ++kk) {
+            h->hst->kcount_num[kk] = hs2.kcount_sym[kk];
+            for (int f = 0; f < 3; ++f) h->hst->kmax_num[kk][f] = hs2.kmax_sym[kk][f];
+        }
+    }
     const DevStats hs3 = *h->hst;
     if (hs3.overflow) return fail(h, SPG_ERR_OUT_OF_MEMORY, "level-2 hash arena too small in the symbolic phase");
-    const int64_t nnzc = h->hkoff[0];
+    const int64_t nnzc = (int64_t)hs3.nnzc;
     h->compressed = comp;
-    *h->hst = hs3;
     spg_stats &o = h->stats;
     std::memset(&o, 0, sizeof(o));
     o.flops = (int64_t)hs1.fm;
@@ -755,10 +793,11 @@ spg_status spgemm_symbolic(spg_handle h, const spg_csr *A, const spg_csr *B, voi
     HIPCHK(launch_copy_rp(m + 1, A->row_ptr, A->rp_type == SPG_I64, A->nnz, h->arp64.as<int64_t>(), n + 1,
                           B->row_ptr, B->rp_type == SPG_I64, B->nnz, h->brp64.as<int64_t>(), bad, st));
     int64_t nnzc = 0;
-    if ((s = symbolic_core(h, m, n, k, A->nnz, B->nnz, A->col_idx, B->col_idx, &nnzc)) != SPG_OK) return s;
+    if ((s = symbolic_core(h, m, n, k, A->nnz, B->nnz, A->col_idx, B->col_idx, &nnzc, C_row_ptr,
+                           c_rpt == SPG_I64)) != SPG_OK)
+        return s;
     if (c_rpt == SPG_I32 && nnzc > INT32_MAX)
         return fail(h, SPG_ERR_INDEX_OVERFLOW, "nnz(C) exceeds an int32 row_ptr; ask for SPG_I64");
-    HIPCHK(launch_store_rp(m + 1, h->coff.as<int64_t>(), C_row_ptr, c_rpt == SPG_I64, st));
     Fingerprint &fp = h->fp;
     fp.m = m; fp.n = n; fp.k = k; fp.nnza = A->nnz; fp.nnzb = B->nnz;
     fp.arp = A->row_ptr; fp.brp = B->row_ptr; fp.aci = A->col_idx; fp.bci = B->col_idx;
@@ -1005,7 +1044,7 @@ static spg_status autotune(spg_handle h, NumArgs<VT> na, int acc) {
                                h->row_nnz.as<int32_t>(), h->row_words.as<int32_t>(), cp, h->kind_tmp.as<uint8_t>(),
                                nullptr, dst, h->tmp.as<int64_t>(), h->koff_tmp.as<int64_t>(), st));
         HIPCHK(launch_partition(m, h->kind_tmp.as<uint8_t>(), h->perm_tmp.as<int32_t>(), h->tmp.as<int64_t>(),
-                                h->koff_tmp.as<int64_t>(), cp.phase, cp.heavy, dst, st));
+                                h->koff_tmp.as<int64_t>(), cp.phase, cp.heavy, dst, nullptr, st));
         if ((s = pull_stats(h)) != SPG_OK) break;
         const DevStats hs = *h->hst;
         na.rs.rows = h->perm_tmp.as<int32_t>();
@@ -1050,7 +1089,7 @@ static spg_status autotune(spg_handle h, NumArgs<VT> na, int acc) {
                            h->row_nnz.as<int32_t>(), h->row_words.as<int32_t>(), cp, h->kind_num.as<uint8_t>(),
                            nullptr, dst, h->tmp.as<int64_t>(), h->koff_num.as<int64_t>(), st));
     HIPCHK(launch_partition(m, h->kind_num.as<uint8_t>(), h->perm_num.as<int32_t>(), h->tmp.as<int64_t>(),
-                            h->koff_num.as<int64_t>(), cp.phase, cp.heavy, dst, st));
+                            h->koff_num.as<int64_t>(), cp.phase, cp.heavy, dst, nullptr, st));
     if ((s = pull_stats(h)) != SPG_OK) return s;
     h->lg_num = best_lg;
     h->tuned = true;
@@ -1109,7 +1148,7 @@ static spg_status autotune_classes(spg_handle h, NumArgs<VT> na, int acc) {
                                    h->kind_tmp.as<uint8_t>(), nullptr, dst, h->tmp.as<int64_t>(),
                                    h->koff_tmp.as<int64_t>(), st));
             HIPCHK(launch_partition(m, h->kind_tmp.as<uint8_t>(), h->perm_tmp.as<int32_t>(), h->tmp.as<int64_t>(),
-                                    h->koff_tmp.as<int64_t>(), cp.phase, cp.heavy, dst, st));
+                                    h->koff_tmp.as<int64_t>(), cp.phase, cp.heavy, dst, nullptr, st));
             if ((s = pull_stats(h)) != SPG_OK) break;
             const DevStats hs = *h->hst;
             na.rs.rows = h->perm_tmp.as<int32_t>();
@@ -1147,7 +1186,7 @@ static spg_status autotune_classes(spg_handle h, NumArgs<VT> na, int acc) {
         HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
                                h->row_nnz.as<int32_t>(), h->row_words.as<int32_t>(), cp, kc, nullptr, dst,
                                h->tmp.as<int64_t>(), oc, st));
-        HIPCHK(launch_partition(m, kc, pc, h->tmp.as<int64_t>(), oc, cp.phase, cp.heavy, dst, st));
+        HIPCHK(launch_partition(m, kc, pc, h->tmp.as<int64_t>(), oc, cp.phase, cp.heavy, dst, nullptr, st));
         if ((s = pull_stats(h)) != SPG_OK) break;
         for (int k = 0; k < NK; ++k) {
             h->cls_kc[c][k] = h->hst->kcount_num[k];

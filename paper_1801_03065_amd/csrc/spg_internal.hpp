@@ -46,7 +46,7 @@ enum Kind : int {
 
 // Global counters written by the analysis kernels (zeroed per symbolic call).
 struct DevStats {
-    unsigned long long fm, fmc, maxrf, maxrfc, nnzbc;
+    unsigned long long fm, fmc, maxrf, maxrfc;
     unsigned long long fmb, fmcb;  // flops (raw / compressed) of rows beyond the short-row limit
     unsigned long long maxnnza;    // longest row of A
     unsigned long long nnzc;
@@ -361,14 +361,13 @@ hipError_t launch_brow(int64_t n, int64_t nnz, int64_t ncols, const int64_t *brp
 // Words of the unsorted rows that launch_brow left uncounted.
 hipError_t launch_brow_unsorted(int64_t n, const uint8_t *uflag, const int64_t *brp, const int32_t *bci, BRow *out,
                                 DevStats *st, hipStream_t s);
-// The compression kernels and the scan take `enable` (device flag, nullable):
-// they do nothing when it reads 0.
+// (word, bits) pairs of sorted rows, and of unsorted ones (any, device: 0 when
+// there are none).
 hipError_t launch_compress_sorted_flags(int64_t n, int64_t nnz, const int64_t *brp, const int32_t *bci, const BRow *bi,
-                                        const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw,
-                                        const int *enable, hipStream_t s);
+                                        const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw, hipStream_t s);
 hipError_t launch_compress_unsorted(int64_t n, const uint8_t *uflag, const int *any, const int64_t *brp,
                                     const int32_t *bci, const BRow *bi, const int64_t *bcrp, uint2 *bcw,
-                                    const int *enable, hipStream_t s);
+                                    hipStream_t s);
 // Per-block partials of the rowinfo reduction (folded by a one-workgroup
 // kernel): RED_ELEMS int64 of device scratch.
 constexpr int RED_ELEMS = 16384;
@@ -385,11 +384,18 @@ hipError_t launch_copy_rp(int64_t n1a, const void *srca, int is64a, int64_t nnza
 // Exclusive scan: out[0..n] (n+1 entries) of in[0..n), int64 result.
 // tmp must hold scan_tmp_elems(n) int64.
 int64_t scan_tmp_elems(int64_t n);
-// in[i * stride] (e.g. one field of an array of structs)
-hipError_t launch_scan_i32s(int64_t n, const int32_t *in, int stride, int64_t *out, int64_t *tmp, const int *enable,
-                            hipStream_t s);
+// in[i * stride]: e.g. one field of an array of structs.
+// ScanOut: where the last scan kernel also leaves the result as int32 or int64
+// row pointers, and the total on the device and in pinned host memory.
+struct ScanOut {
+    int32_t *rp32 = nullptr;
+    int64_t *rp64 = nullptr;
+    unsigned long long *total = nullptr;
+    int64_t *host_total = nullptr;
+};
+hipError_t launch_scan_i32(int64_t n, const int32_t *in, int stride, int64_t *out, int64_t *tmp, const ScanOut &o,
+                           hipStream_t s);
 hipError_t launch_scan_i32(int64_t n, const int32_t *in, int64_t *out, int64_t *tmp, hipStream_t s);
-hipError_t launch_store_rp(int64_t n1, const int64_t *src, void *dst, int is64, hipStream_t s);
 
 // Classification parameters shared by host and device.
 struct ClassParams {
@@ -425,12 +431,13 @@ struct ClassParams {
 // per classify workgroup (tmp, part_tmp_elems(m)); launch_partition then folds
 // them into st (counts, maxima) and koff (offsets per kind) and writes the
 // rows grouped by kind.  (koff is only filled here when there are no rows.)
+// host (pinned, nullable): the statistics as they are when the partition ends.
 hipError_t launch_classify(int64_t m, const int64_t *rflops, const int64_t *rflopsc, const int2 *rwin,
                            const int32_t *row_nnz, const int32_t *row_words, ClassParams p, uint8_t *kind,
                            int32_t *row_nnz_out, DevStats *st, int64_t *tmp, int64_t *koff, hipStream_t s);
 int64_t part_tmp_elems(int64_t m);
 hipError_t launch_partition(int64_t m, const uint8_t *kind, int32_t *perm, const int64_t *tmp, int64_t *koff,
-                            int phase, int heavy, DevStats *st, hipStream_t s);
+                            int phase, int heavy, DevStats *st, DevStats *host, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_kind_ranges(const int32_t *perm, const int64_t *koff, int64_t rb, int64_t re, int64_t *range,
                               hipStream_t s);
