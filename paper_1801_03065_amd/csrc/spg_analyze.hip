@@ -222,17 +222,20 @@ __global__ __launch_bounds__(WAVE) void k_brow_unsorted(int64_t n, const uint8_t
     if (!*any) return;
     for (int w = l; w < UB_WORDS; w += WAVE) bits[w] = 0;
     wave_lds_sync();
-    // 64 rows at a time, the flagged ones one after the other
+    // up to 64 rows at a time (fewer where all workgroups would not get as
+    // many: 1565 unsorted rows took 54 us in 25 workgroups), the flagged ones
+    // one after the other
+    const int ch = (int)min((int64_t)WAVE, (n + gridDim.x - 1) / gridDim.x);
     unsigned long long todo = 0;
-    for (int64_t r0 = (int64_t)blockIdx.x * WAVE;;) {
+    for (int64_t r0 = (int64_t)blockIdx.x * ch;;) {
         while (!todo && r0 < n) {
-            todo = __ballot(r0 + l < n && uflag[min(r0 + l, n - 1)] >= least);
-            if (!todo) r0 += (int64_t)gridDim.x * WAVE;
+            todo = __ballot(l < ch && r0 + l < n && uflag[min(r0 + l, n - 1)] >= least);
+            if (!todo) r0 += (int64_t)gridDim.x * ch;
         }
         if (!todo) break;
         const int64_t r = r0 + __ffsll((long long)todo) - 1;
         todo &= todo - 1;
-        if (!todo) r0 += (int64_t)gridDim.x * WAVE;
+        if (!todo) r0 += (int64_t)gridDim.x * ch;
         const int64_t b = brp[r], e = brp[r + 1];
         const BRow br = bi[r];
         const int64_t nw = (int64_t)br.wmax - br.wmin + 1;
@@ -559,6 +562,25 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
         smax[t][2] = 0;
         scnt[t] = 0;
     }
+    // every load of the lane's rows up front (the indices of rows past the end
+    // are clamped): one wait instead of one per condition below
+    long long f_[CL_R], fc_[CL_R], al_[CL_R];
+    int2 w_[CL_R];
+    int rn_[CL_R], rw_[CL_R], pl_[CL_R];
+    uint8_t sk_[CL_R];
+#pragma unroll
+    for (int h = 0; h < CL_R; ++h) {
+        const int64_t i = min((int64_t)blockIdx.x * CR + h * CB + t, m - 1);
+        f_[h] = rflops[i];
+        w_[h] = rwin[i];
+        fc_[h] = p.phase == 0 ? rflopsc[i] : 0;
+        rn_[h] = p.phase == 0 ? 0 : row_nnz[i];
+        rw_[h] = p.phase == 0 ? 0 : row_words[i];
+        al_[h] = p.bk || p.heavy_alen > 0 ? p.arp[i + 1] - p.arp[i] : 0;
+        const bool sym = p.phase == 1 && p.sym_kind && (p.plan_cap > 0 || p.sg);
+        sk_[h] = sym ? p.sym_kind[i] : 0;
+        pl_[h] = sym && p.plan_cap > 0 ? p.plan_len[i] : 0;
+    }
     // device-side switches: compression decided by the analysis, segments
     // only when every row of B is sorted
     const bool compressed = p.comp_flag ? (*p.comp_flag != 0) : (p.compressed != 0);
@@ -570,24 +592,23 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
         const int64_t i = (int64_t)blockIdx.x * CR + h * CB + t;
         const bool valid = i < m;
         const bool sampled = p.sample_stride <= 1 || (i % p.sample_stride) == 0;
-        long long f = (valid && sampled) ? rflops[i] : 0;
+        long long f = (valid && sampled) ? f_[h] : 0;
         if (p.phase == 1 && p.row_cls && valid && p.row_cls[i] != p.cls) f = 0;
         if (p.phase == 1 && p.split && f > 0) {
-            const bool hv = (p.heavy_flops > 0 && f >= p.heavy_flops) ||
-                            (p.heavy_alen > 0 && p.arp[i + 1] - p.arp[i] > p.heavy_alen);
+            const bool hv = (p.heavy_flops > 0 && f >= p.heavy_flops) || (p.heavy_alen > 0 && al_[h] > p.heavy_alen);
             if (hv != (p.heavy != 0)) f = 0;
         }
-        const int2 w = valid ? rwin[i] : make_int2(0, -1);
+        const int2 w = valid ? w_[h] : make_int2(0, -1);
         int k = valid ? K_EMPTY : -1, a = 0, bnd = 0, tw = 0;
         if (f > 0) {
             const long long nw = (long long)w.y - w.x + 1;
             long long bound, words;
             if (p.phase == 0) {
-                bound = compressed ? min((long long)rflopsc[i], nw) : min(f, 32 * nw);
+                bound = compressed ? min(fc_[h], nw) : min(f, 32 * nw);
                 words = min(bound, nw);
             } else {
-                bound = row_nnz[i];
-                words = row_words[i];
+                bound = rn_[h];
+                words = rw_[h];
             }
             const bool dw_fit = nw <= p.dw_nw_max && (p.phase == 0 || bound <= p.dw_r_max);
             const bool wh_fit = p.phase == 1 && nw <= p.wh_nw_max && bound <= p.wh_r_max && words <= p.wh_t_max;
@@ -607,9 +628,19 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                 default:  // selector
                     if (f <= p.sr_f_max)
                         k = K_SR;
-                    else if (p.phase == 0)
+                    // Scattered rows: as many window words as multiplications
+                    // and B rows that compression does not shorten, so few
+                    // products meet and a hash of the products is smaller
+                    // than the window (measured at k_sym_bk).  Rows of a few
+                    // more multiplications than PL_CAP may store their
+                    // structure: they keep the bit window where it fits.
+                    else if (p.phase == 0 && p.bk && f <= BK_F_MAX && nw >= f && (!dw_fit || 2 * f > 3 * PL_CAP) &&
+                             (double)fc_[h] >= 0.85 * (double)f && al_[h] <= WAVE) {
+                        k = K_BK0;
+                        for (long long top = BK_F0; top < f; top <<= 1) ++k;
+                    } else if (p.phase == 0)
                         k = dw_fit ? K_DW : (hw_fit ? K_HW : (dg_fit ? K_DG : K_HL));
-                    else if (p.plan_cap > 0 && p.sym_kind[i] == K_DW && words <= p.plan_len[i] &&
+                    else if (p.plan_cap > 0 && sk_[h] == K_DW && words <= pl_[h] &&
                              nw <= PL_NW_MAX && bound <= PL_R_MAX)
                         k = K_PL;  // the symbolic phase stored this row's structure
                     // Scattered rows (at most two products per entry, A entries
@@ -619,7 +650,7 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                     // products per entry the buckets fill with repeats and the
                     // accumulators win.  Batch of 48 (400 products a row), FP64
                     // numeric: the others 45.0 ms, buckets 5.6 ms.
-                    else if (p.bk && f <= BK_F_MAX && f <= 2 * bound && p.arp[i + 1] - p.arp[i] <= WAVE) {
+                    else if (p.bk && f <= BK_F_MAX && f <= 2 * bound && al_[h] <= WAVE) {
                         k = K_BK0;
                         for (long long top = BK_F0; top < f; top <<= 1) ++k;
                     } else
@@ -631,7 +662,7 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
             if (sg && p.phase == 0 && dg_fit &&
                 ((k == K_DW && eb > SG_CAP) || (k == K_HW && eb > p.hw_keys_max)))
                 k = K_DG;  // (a word-keyed hash row may still hold more entries than a numeric hash row)
-            if (sg && p.phase == 1 && k == K_DG && p.sym_kind[i] != K_DG && (bound > SG_CAP || nw > SG_NW))
+            if (sg && p.phase == 1 && k == K_DG && sk_[h] != K_DG && (bound > SG_CAP || nw > SG_NW))
                 k = hw_fit ? K_HW : K_HL;  // no segment list for this row
             if (p.phase == 0 && p.plan_len) {
                 int room = 0;

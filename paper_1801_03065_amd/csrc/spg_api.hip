@@ -149,6 +149,31 @@ spg_status hip_fail(spg_handle h, hipError_t e, const char *where) {
         if (_e != hipSuccess) return hip_fail(h, _e, #expr); \
     } while (0)
 
+// The launches of the scattered-row kinds (K_BK0 .. K_BK4, neighbours in the
+// kind-ordered row lists).  A kind of few rows joins the next kind's launch,
+// whose kernel holds its rows too: up to 8 rows per CU a launch of its own
+// costs its latency (6 to 12 us), more than the wider kernel's idle lanes
+// (10 us per 6000 rows).  `join`: the lists are whole (not row panels).
+template <typename F>
+hipError_t for_scattered(const long long *count, bool join, RowSet &rs, int cus, F &&launch) {
+    int64_t rows = 0;
+    rs.more = 0;
+    for (int K = K_BK0; K <= K_BK4; ++K) {
+        rows += count[K];
+        if (rows == 0) continue;
+        if (join && K < K_BK4 && count[K + 1] > 0 && rows <= 8 * (int64_t)cus) {
+            ++rs.more;
+            continue;
+        }
+        rs.kind = K - rs.more;
+        const hipError_t e = launch(K, rows);
+        if (e != hipSuccess) return e;
+        rs.more = 0;
+        rows = 0;
+    }
+    return hipSuccess;
+}
+
 hipError_t ensure(DevBuf &b, size_t bytes) {
     if (bytes == 0) bytes = 16;
     if (b.p && b.cap >= bytes) return hipSuccess;
@@ -502,6 +527,8 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         }
     }
     cp.words_out = h->row_words.as<int32_t>();
+    cp.arp = arp;
+    cp.bk = nnzb < (int64_t(1) << 29) ? 1 : 0;  // 32-bit byte offsets into B
     HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(), nullptr,
                            nullptr, cp, h->kind_sym.as<uint8_t>(), h->row_nnz.as<int32_t>(), dst, h->tmp.as<int64_t>(),
                            h->koff_sym.as<int64_t>(), st));
@@ -626,6 +653,9 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         lc.grid = 0;
         HIPCHK(launch_sym_sr(sa, sr_lg(hs2.kmax_sym[K_SR][1]), lc, hs2.kcount_sym[K_SR]));
     }
+    lc.grid = 0;
+    HIPCHK(for_scattered(hs2.kcount_sym, true, sa.rs, h->cus,
+                         [&](int K, int64_t rows) { return launch_sym_bk(sa, K, lc, rows); }));
     if (hs2.kcount_sym[K_DW] > 0) {
         sa.rs.kind = K_DW;
         sa.nw_max = ((hs2.kmax_sym[K_DW][0] + 31) / 32) * 32;
@@ -687,8 +717,6 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     cp.sg = h->sg_mode ? 1 : 0;
     cp.heavy_flops = thr > 0 ? thr : 0;
     cp.heavy_alen = tmax > 0 ? tmax : 0;
-    cp.arp = arp;
-    cp.bk = nnzb < (int64_t(1) << 29) ? 1 : 0;  // 32-bit byte offsets into B
     cp.split = split ? 1 : 0;
     cp.heavy = 0;
     if (all_short) {
@@ -744,7 +772,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     o.nnz_b_compressed = comp ? h->hkoff[2] : 0;
     o.n_kinds = NK_PUBLIC;
     int64_t maxrs = 0;
-    for (int kk = 0; kk < NK_PUBLIC; ++kk) o.rows_symbolic[kk] = hs3.kcount_sym[kk];
+    for (int kk = 0; kk < NK; ++kk) o.rows_symbolic[kk < NK_PUBLIC ? kk : K_HW] += hs3.kcount_sym[kk];
     for (int kk = 0; kk < NK; ++kk) {
         if (kk != K_EMPTY) maxrs = std::max<int64_t>(maxrs, hs3.kmax_num[kk][1]);
         if (kk != K_EMPTY && split) maxrs = std::max<int64_t>(maxrs, hs3.kmax_heavy[kk][1]);
@@ -902,11 +930,8 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
         na.ts = pow2_at_least(2 * (int64_t)std::max(kmax[K_WH][2], 1), 16);
         HIPCHK(launch_num_wh<VT>(na, acc, lc));
     }
-    for (int K = K_BK0; K <= K_BK4; ++K) {
-        if (kcount[K] <= 0) continue;
-        na.rs.kind = K;
-        HIPCHK(launch_num_bk<VT>(na, acc, K, lc, kcount[K]));
-    }
+    HIPCHK(for_scattered(kcount, na.rs.range == nullptr, na.rs, h->cus,
+                         [&](int K, int64_t rows) { return launch_num_bk<VT>(na, acc, K, lc, rows); }));
     if (kcount[K_HW] > 0 && pol == SPG_ACC_LL) {  // LL hashmap, rows unsorted
         na.rs.kind = K_HW;
         na.r_max = std::max(kmax[K_HW][1], 1);

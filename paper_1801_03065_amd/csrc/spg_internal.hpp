@@ -34,14 +34,14 @@ enum Kind : int {
     K_WH = 5,     // word hash + ordered summary, one wavefront per row (numeric)
     K_SR = 6,     // short rows: a team of T <= 64 lanes per row, several rows per wavefront
     K_PL = 7,     // numeric on the symbolic phase's stored row structure, one wavefront per row
-    K_BK0 = 8,    // column buckets (numeric): one wavefront per row for rows of up to 128,
+    K_BK0 = 8,    // scattered rows (hash in LDS, then column buckets): one wavefront per row for rows of up to 128,
     K_BK1 = 9,    //   256
     K_BK2 = 10,   //   and 512 multiplications, two and four wavefronts
     K_BK3 = 11,   //   for rows of up to 1024
     K_BK4 = 12,   //   and 2048
     NK = 13,
     NK_PAD = 16,   // per-workgroup kind counts are stored 16 apart (int4 loads)
-    NK_PUBLIC = 8  // kinds reported in spg_stats: the bucket kinds count as K_WH there
+    NK_PUBLIC = 8  // kinds reported in spg_stats: the scattered kinds count as K_HW (symbolic), K_WH (numeric)
 };
 
 // Global counters written by the analysis kernels (zeroed per symbolic call).
@@ -91,6 +91,7 @@ struct RowSet {
     const int64_t *range;  // when set: range[2*kind] .. range[2*kind+1] instead (row panels)
     int kind;
     int32_t *queue;        // XCDS dynamic-schedule counters (zeroed before launch)
+    int more;              // the kinds after it that the launch takes too (koff only)
 };
 
 __device__ __forceinline__ void rs_bounds(const RowSet &rs, int64_t &lo, int64_t &hi) {
@@ -99,7 +100,7 @@ __device__ __forceinline__ void rs_bounds(const RowSet &rs, int64_t &lo, int64_t
         hi = rs.range[2 * rs.kind + 1];
     } else {
         lo = rs.koff[rs.kind];
-        hi = rs.koff[rs.kind + 1];
+        hi = rs.koff[rs.kind + rs.more + 1];
     }
 }
 
@@ -413,7 +414,7 @@ struct ClassParams {
     int split;
     int heavy;          // numeric: counts / maxima go to the heavy-row set
     int sr_f_max;       // selector: rows with at most this many multiplications are short rows (0: off)
-    int bk;             // numeric, selector: scattered rows may take the column-bucket kinds (nnz(B) < 2^29)
+    int bk;             // selector: scattered rows may take the kinds for them (nnz(B) < 2^29)
     int plan_cap;       // stored row structure: pairs per row (0: off)
     int32_t *plan_len;  // symbolic: room for pairs per row (written); numeric: read
     int32_t *sgb_len;   // symbolic: words of a heavy row's bit window to keep (written; nullptr: none)
@@ -447,6 +448,8 @@ hipError_t launch_sym_dw(const SymArgs &a, const LaunchCfg &c);
 hipError_t launch_sym_hw(const SymArgs &a, const LaunchCfg &c);
 hipError_t launch_sym_dg(const SymArgs &a, const LaunchCfg &c);
 hipError_t launch_sym_hl(const SymArgs &a, const LaunchCfg &c);
+// Scattered rows (kind: K_BK0 .. K_BK4).
+hipError_t launch_sym_bk(const SymArgs &a, int kind, const LaunchCfg &c, int64_t rows);
 // Short rows: teams of 2^lg_t lanes; rows = number of rows in the kind (grid sizing).
 hipError_t launch_sym_sr(const SymArgs &a, int lg_t, const LaunchCfg &c, int64_t rows);
 
