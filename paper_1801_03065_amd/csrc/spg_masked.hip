@@ -11,7 +11,8 @@
 // whose column is in the table is added at its position.
 //
 // Rows fall into three kinds (k_mask_class):
-//   1. up to MW_MAX mask entries and MK_F multiplications: one wavefront;
+//   1. up to MW_MAX mask entries and MK_F multiplications (MK_F_FEW in products
+//      of up to MK_FEW rows): one wavefront;
 //   2. up to MG_MAX mask entries: one 512-lane workgroup, table in LDS;
 //   3. longer mask rows: one 512-lane workgroup, table in a slice of an HBM
 //      arena behind an LDS bit filter (a column whose bit is clear is not in
@@ -35,6 +36,7 @@ namespace spg {
 namespace {
 
 constexpr int MK_CB = 256;   // classification
+constexpr int MK_FEW = 32768, MK_F_FEW = 2048;  // (see launch_mask_class)
 constexpr int MK_WG = 512;   // lanes of a workgroup row
 constexpr int MK_U = 8;      // products per lane and round
 constexpr int MK_FLG = 17, MK_FBITS = 1 << MK_FLG;  // bits of the filter of kind 3
@@ -311,10 +313,11 @@ __global__ __launch_bounds__(NW *WAVE) void k_mask(MaskArgs<VT> a, int lg, int m
 
 // Row kinds, with the longest mask row per kind (see the file comment); rows
 // with an empty mask row or an empty A row need no kernel (their outputs are
-// zero-filled).  16 lanes sum a row's multiplications; per workgroup of MK_CB
-// rows one atomic per kind for the base of its list slice.
+// zero-filled).  16 lanes sum a row's multiplications, `its` rows one after the
+// other; per workgroup one atomic per kind for the base of its list slice.
 __global__ __launch_bounds__(MK_CB) void k_mask_class(int64_t m, int64_t n, const int64_t *arp, const int32_t *aci,
-                                                      const int64_t *brp, const int64_t *mrp, int32_t *rows, int *cnt) {
+                                                      const int64_t *brp, const int64_t *mrp, int its, int f_max, int32_t *rows,
+                                                      int *cnt) {
     __shared__ int sc[3], sb[3], smx[3];
     __shared__ uint8_t kind[MK_CB];
     const int t = threadIdx.x, q = t & 15;
@@ -322,9 +325,10 @@ __global__ __launch_bounds__(MK_CB) void k_mask_class(int64_t m, int64_t n, cons
         sc[t] = 0;
         smx[t] = 0;
     }
-    for (int it = 0; it < 16; ++it) {
+    const int64_t r0 = (int64_t)blockIdx.x * (its * (MK_CB / 16));
+    for (int it = 0; it < its; ++it) {
         const int lr = it * (MK_CB / 16) + (t >> 4);
-        const int64_t i = (int64_t)blockIdx.x * MK_CB + lr;
+        const int64_t i = r0 + lr;
         int k = 0;
         if (i < m) {
             const int64_t ml = mrp[i + 1] - mrp[i], ab = arp[i], ae = arp[i + 1];
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(MK_CB) void k_mask_class(int64_t m, int64_t n, cons
                     k = ml <= MG_MAX ? 2 : 3;
                 } else {
                     long long f = 0;
-                    for (int64_t e0 = ab; e0 < ae && f <= MK_F; e0 += 64) {  // (f <= MK_F: per lane, ends early)
+                    for (int64_t e0 = ab; e0 < ae && f <= f_max; e0 += 64) {  // (f <= f_max: per lane, ends early)
                         int j[4];
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
@@ -346,15 +350,15 @@ __global__ __launch_bounds__(MK_CB) void k_mask_class(int64_t m, int64_t n, cons
                     }
 #pragma unroll
                     for (int d = 8; d >= 1; d >>= 1) f += __shfl_xor(f, d, 16);
-                    k = f > MK_F ? 2 : 1;
+                    k = f > f_max ? 2 : 1;
                 }
             }
         }
         if (q == 0) kind[lr] = (uint8_t)k;
     }
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * MK_CB + t;
-    const int k = kind[t];
+    const int64_t i = r0 + t;
+    const int k = t < its * (MK_CB / 16) ? kind[t] : 0;
     int my = 0;
     if (k) {
         my = atomicAdd(&sc[k - 1], 1);
@@ -404,8 +408,15 @@ hipError_t mask_impl(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCf
 hipError_t launch_mask_class(int64_t m, int64_t n, const int64_t *arp, const int32_t *aci, const int64_t *brp,
                              const int64_t *mrp, int32_t *rows, int *cnt, hipStream_t s) {
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mask_class, dim3((unsigned)((m + MK_CB - 1) / MK_CB)), dim3(MK_CB), 0, s, m, n, arp, aci, brp,
-                       mrp, rows, cnt);
+    // Small products: fewer rows one after the other per 16 lanes (2048 rows in
+    // 16 turns: 26 us), and rows of MK_F_FEW multiplications already take a
+    // workgroup, since the longest row alone decides (49 us).  A call at scale
+    // 11: 82 us against 130; scale 12: 100 against 280 before the flat walk.
+    // Large products: one atomic per 256 rows, and MK_F.
+    const int its = (int)std::min<int64_t>(16, 1 + m / 16384);
+    const int per = its * (MK_CB / 16);
+    hipLaunchKernelGGL(k_mask_class, dim3((unsigned)((m + per - 1) / per)), dim3(MK_CB), 0, s, m, n, arp, aci, brp,
+                       mrp, its, m <= MK_FEW ? MK_F_FEW : MK_F, rows, cnt);
     return hipGetLastError();
 }
 
