@@ -659,15 +659,17 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
             // heavy rows in segments: the symbolic bit window of a workgroup
             // row cuts them, so rows that may exceed one segment go there
             const long long eb = min(f, 32 * nw);  // entries bound
+            const bool long_row = f > SG_F;
             if (sg && p.phase == 0 && dg_fit &&
-                ((k == K_DW && eb > SG_CAP) || (k == K_HW && eb > p.hw_keys_max)))
+                ((k == K_DW && (eb > SG_CAP || long_row)) || (k == K_HW && (eb > p.hw_keys_max || long_row))))
                 k = K_DG;  // (a word-keyed hash row may still hold more entries than a numeric hash row)
+            if (sg && p.phase == 1 && long_row && sk_[h] == K_DG && (k == K_WH || k == K_HW)) k = K_DG;
             if (sg && p.phase == 1 && k == K_DG && sk_[h] != K_DG && (bound > SG_CAP || nw > SG_NW))
                 k = hw_fit ? K_HW : K_HL;  // no segment list for this row
             if (p.phase == 0 && p.plan_len) {
                 int room = 0;
                 if (k == K_DW && p.plan_cap > 0) room = (int)min(words, (long long)p.plan_cap);
-                if (k == K_DG && sg && (eb > SG_CAP || nw > SG_NW))
+                if (k == K_DG && sg && (eb > SG_CAP || nw > SG_NW || long_row))
                     room = (int)((eb + SG_CUT - 1) / SG_CUT + (nw + SG_NW - 1) / SG_NW + 2);
                 p.plan_len[i] = room;
                 // A heavy row's bit window is kept for the numeric phase where

@@ -571,26 +571,28 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     h->segmented = false;
     const bool pairs_used = want_pairs && hs2.kcount_sym[K_DW] > 0;
     const bool segs_used = want_segs && hs2.kcount_sym[K_DG] > 0;
-    // room for stored structure: the scan of the rows' room gives each row's
-    // offset.  Bit-window rows hold at most PL_CAP pairs each, so while no
-    // segment room is in the scan (no heavy rows with lists) and that bound
-    // is modest, the plan is sized by it without waiting for the total;
-    // otherwise the exact total is fetched (one more host sync).
+    // Room for stored structure: the scans of the rows' room give each row's
+    // offset.  The kinds' largest rows bound the totals (PL_CAP pairs per
+    // bit-window row; a heavy row's segments and window words); while the
+    // bounds are modest the buffers are sized by them, else the exact totals
+    // are fetched (one more host sync: 20 us).
     int64_t plan_room = 0, sgb_words = 0;
     if (pairs_used || segs_used) {
         HIPCHK(launch_scan_i32(m, h->plan_len.as<int32_t>(), h->plan_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
-        const int64_t bound = (int64_t)PL_CAP * hs2.kcount_sym[K_DW];
-        const bool seg_room = want_segs_opt && hs2.kcount_sym[K_DG] > 0;
-        if (!seg_room && bound <= (int64_t(1) << 27)) {
-            plan_room = bound;
-        } else {
+        if (segs_used) {
+            HIPCHK(ensure(h->sgb_off, 8 * (m + 1)));
+            HIPCHK(launch_scan_i32(m, h->sgb_len.as<int32_t>(), h->sgb_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
+        }
+        const int64_t rows_dg = hs2.kcount_sym[K_DG], nw_dg = hs2.kmax_sym[K_DG][0];
+        const int64_t eb = std::min<int64_t>((int64_t)hs1.maxrf, 32 * nw_dg);
+        plan_room = (int64_t)PL_CAP * hs2.kcount_sym[K_DW] +
+                    (rows_dg > 0 ? rows_dg * ((eb + SG_CUT - 1) / SG_CUT + (nw_dg + SG_NW - 1) / SG_NW + 2) : 0);
+        sgb_words = segs_used ? rows_dg * nw_dg : 0;
+        if (plan_room > (int64_t(1) << 27) || sgb_words > SGB_BOUND) {
             h->hkoff[4] = 0;
-            if (segs_used) {
-                HIPCHK(ensure(h->sgb_off, 8 * (m + 1)));
-                HIPCHK(launch_scan_i32(m, h->sgb_len.as<int32_t>(), h->sgb_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
+            if (segs_used)
                 HIPCHK(hipMemcpyAsync(h->hkoff + 4, h->sgb_off.as<int64_t>() + m, sizeof(int64_t),
                                       hipMemcpyDeviceToHost, st));
-            }
             HIPCHK(hipMemcpyAsync(h->hkoff + 1, h->plan_off.as<int64_t>() + m, sizeof(int64_t),
                                   hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));

@@ -82,6 +82,15 @@ constexpr int PL_R_MAX = 2048;    // row size of the stored-structure kernel
 constexpr int SG_NW = 4096;       // column-set words of one heavy-row segment (aligned groups)
 constexpr int SG_CAP = 4096;      // entries of one heavy-row segment (LDS values)
 constexpr int64_t SGB_MAX = int64_t(2) << 30;  // words of heavy rows' bit windows kept at most (8 GiB)
+constexpr int64_t SGB_BOUND = int64_t(1) << 25;  // sized by a bound, without a host wait, up to this many (128 MiB)
+// Rows of more multiplications are heavy rows too, whatever their size: one
+// wavefront forms 64 products in 0.2 to 0.4 us, a workgroup row several times
+// as many.  R-MAT squares, scale 10 / 11 / 12, FP64: 593 -> 309, 1310 -> 436,
+// 846 -> 555 us; 20000 rows times 2000 columns with 70 / 100 / 140 entries a
+// row: 1697 -> 1202, 2830 -> 1317, 5308 -> 1707 us.  From 2048 on, the
+// one-wavefront kernels still win where rows are alike (50 entries: 755 against
+// 985 us) and in R-MAT squares of scale 13 and more (724 against 736 us).
+constexpr int SG_F = 4096;
 constexpr int SG_CUT = SG_CAP - 32;  // a segment starts at the word holding each multiple of this
 
 // ------------------------------------------------------------ argument blocks
