@@ -905,12 +905,26 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
         HIPCHK(launch_num_pl<VT>(na, acc, lc));
     }
     if (vo && h->maps_ok) {  // structure known: every mapped kind on its position maps
+        // Neighbouring scattered-row kinds share a launch while its rows leave
+        // room for 28 wavefronts per CU (4 KB of values each).
+        int64_t rows = 0;
+        int rmax = 0;
+        na.rs.more = 0;
         for (int K : MAP_KINDS) {
-            if (kcount[K] <= 0) continue;
-            na.rs.kind = K;
-            na.r_max = std::max(kmax[K][1], 1);
+            rows += kcount[K];
+            rmax = std::max(rmax, kmax[K][1]);
+            if (rows <= 0) continue;
+            if (K >= K_BK0 && K < K_BK4 && !na.rs.range && kcount[K + 1] > 0 && kmax[K + 1][1] * sbytes <= 4096) {
+                ++na.rs.more;
+                continue;
+            }
+            na.rs.kind = K - na.rs.more;
+            na.r_max = std::max(rmax, 1);
             const int lgt = K == K_SR ? sr_lg(kmax[K_SR][1]) : 6;
-            HIPCHK(launch_num_map<VT>(na, acc, lgt, h->lg_map_cur, lc, kcount[K]));
+            HIPCHK(launch_num_map<VT>(na, acc, lgt, h->lg_map_cur, lc, rows));
+            na.rs.more = 0;
+            rows = 0;
+            rmax = 0;
         }
         for (int kk = 0; kk < NK; ++kk) h->kc_nomap[kk] = map_kind(kk) ? 0 : kcount[kk];
         kcount = h->kc_nomap;  // the remaining kinds below
@@ -1440,6 +1454,7 @@ static spg_status build_maps(spg_handle h, const int32_t *cci) {
     na.coff = h->coff.as<int64_t>();
     na.map_off = h->map_off.as<int64_t>();
     na.map = h->map.as<uint16_t>();
+    na.nnzb = h->fp.nnzb;
     na.st = h->dstats.as<DevStats>();
     LaunchCfg lc{st, 0, h->cus};
     auto kinds = [&](const int32_t *perm, const int64_t *koff, const long long *kcount, const int (*kmax)[3],
@@ -1449,6 +1464,7 @@ static spg_status build_maps(spg_handle h, const int32_t *cci) {
         for (int K : MAP_KINDS) {
             if (kcount[K] <= 0) continue;
             na.rs.kind = K;
+            na.r_max = std::max(kmax[K][1], 1);
             const int lgt = K == K_SR ? sr_lg(kmax[K_SR][1]) : 6;
             hipError_t e = launch_posmap(na, cci, lgt, lg_map(avg_b), lc, kcount[K]);
             if (e != hipSuccess) return e;

@@ -33,7 +33,7 @@ constexpr long long FLAT_ONE = 1ll << FLAT_SHIFT, FLAT_LEN = FLAT_ONE - 1;
 // lane, relative to it (products past the chunk get its last run).
 template <int U, typename IX>
 __device__ __forceinline__ int flat_window(const IX *off, int cn, IX F, IX tot, int kc, uint16_t *wi, int (&k)[U]) {
-    static_assert(U == 2 || U % 8 == 0, "a lane clears its entries with 4- or 16-byte stores");
+    static_assert(U == 2 || U == 4 || U % 8 == 0, "a lane clears its entries with 4-, 8- or 16-byte stores");
     const int l = lane_id();
     int klo = kc;
     if (off[klo] <= F) {
@@ -47,6 +47,8 @@ __device__ __forceinline__ int flat_window(const IX *off, int cn, IX F, IX tot, 
     }
     if constexpr (U == 2) {
         ((uint32_t *)wi)[l] = 0u;
+    } else if constexpr (U == 4) {
+        ((uint2 *)wi)[l] = make_uint2(0u, 0u);
     } else {
 #pragma unroll
         for (int u = 0; u < U / 8; ++u) *(uint4 *)&wi[(u * WAVE + l) * 8] = make_uint4(0u, 0u, 0u, 0u);

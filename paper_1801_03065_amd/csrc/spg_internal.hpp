@@ -495,7 +495,6 @@ hipError_t launch_posmap(const NumArgs<double> &a, const int32_t *cci, int lgt, 
                          int64_t rows);
 template <typename VT>
 hipError_t launch_num_map(const NumArgs<VT> &a, int acc, int lgt, int lgs, const LaunchCfg &c, int64_t rows);
-size_t lds_num_map(int r_max, int lgt, int acc_bytes);
 // LL hashmap, Thread-Sequential groups of 2^lgg lanes per row, unsorted rows:
 // a.ts buckets (power of two), a.r_max slots (>= the largest row of the kind).
 template <typename VT>

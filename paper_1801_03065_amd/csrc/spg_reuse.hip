@@ -11,11 +11,13 @@
 // all (no hash, no bit window, no sort): each product is added at its rank
 // in an LDS copy of the row, and only C's values are written.
 //
-// Work split: teams of T = 2^LGT lanes per row (WAVE / T rows per
+// Work split: short rows in teams of T = 2^LGT < 64 lanes (WAVE / T rows per
 // wavefront); a team stages its row's A entries T at a time (B row start and
 // length, the prefix of the lengths, A's value), then groups of G = 2^LGS
-// lanes walk one staged B row each.
+// lanes walk one staged B row each.  Other rows take a wavefront, which walks
+// their products flat (k_map_flat).
 #include "spg_accum.hpp"
+#include "spg_flat.hpp"
 #include "spg_internal.hpp"
 
 namespace spg {
@@ -102,7 +104,7 @@ __device__ __forceinline__ int stage_chunk(const TeamRow &tr, int64_t e0, int ca
     return team_total<LGT>(inc);
 }
 
-// Position map of the rows of one kind (one-time, from C's sorted columns).
+// Position map of short rows, in teams (one-time, from C's sorted columns).
 template <int LGT, int LGS>
 __global__ __launch_bounds__(WAVE) void k_posmap(NumArgs<double> a, const int32_t *cci) {
     constexpr int T = 1 << LGT, G = 1 << LGS, NG = T / G;
@@ -147,7 +149,190 @@ __global__ __launch_bounds__(WAVE) void k_posmap(NumArgs<double> a, const int32_
     });
 }
 
-// Values of the rows of one kind on their position maps.
+// Rows with a wavefront each, their products walked flat, U per lane and round,
+// so ranks load and store as whole cache lines and B's entries in runs, all of
+// a round in flight together.  The next row's A entries and their B row
+// extents, and the bounds of the row after it, load during the row.
+struct FlatRow {
+    int64_t ab, ae, cb, mo;
+    int rn;
+};
+
+// begin(row); products(row, map of the chunk, first product, products of the
+// chunk, run and B entry per product); finish(row).  Products past the chunk
+// repeat its last one.
+template <bool VALUES, typename VT, typename IX, int U, typename Begin, typename Products, typename Finish>
+__device__ __forceinline__ void flat_rows(const NumArgs<VT> &a, IX *rel, IX *off, VT *sav, uint16_t *wi, Begin &&begin,
+                                          Products &&products, Finish &&finish) {
+    const int l = lane_id();
+    int64_t lo, hi;
+    rs_bounds(a.rs, lo, hi);
+    const Slice sl = xcd_slice(lo, hi);
+    auto bounds = [&](int64_t q) {
+        FlatRow r{};
+        if (q < sl.end) {
+            const int i = read_first(a.rs.rows[q]);
+            r.ab = a.arp[i];
+            r.ae = a.arp[i + 1];
+            r.cb = a.coff[i];
+            r.rn = (int)(a.coff[i + 1] - r.cb);
+            r.mo = a.map_off[i];
+        }
+        return r;
+    };
+    int64_t p = sl.idx, b0 = 0, b1 = 0;
+    FlatRow cur = bounds(p);
+    VT av = VT(0);
+    if (l < cur.ae - cur.ab) {
+        const int j = a.aci[cur.ab + l];
+        if constexpr (VALUES) av = a.aval[cur.ab + l];
+        b0 = a.brp[j];
+        b1 = a.brp[j + 1];
+    }
+    FlatRow nxt = bounds(p + sl.step);
+    for (; p < sl.end; p += sl.step) {
+        begin(cur);
+        int nj = 0;
+        VT nav = VT(0);
+        const bool have = l < nxt.ae - nxt.ab;
+        if (have) {
+            nj = a.aci[nxt.ab + l];
+            if constexpr (VALUES) nav = a.aval[nxt.ab + l];
+        }
+        const FlatRow after = bounds(p + 2 * sl.step);
+        uint16_t *map = a.map + cur.mo;
+        for (int64_t c0 = cur.ab; c0 < cur.ae; c0 += WAVE) {
+            const int cn0 = (int)min((int64_t)WAVE, cur.ae - c0);
+            if (c0 != cur.ab && l < cn0) {
+                const int j = a.aci[c0 + l];
+                if constexpr (VALUES) av = a.aval[c0 + l];
+                b0 = a.brp[j];
+                b1 = a.brp[j + 1];
+            }
+            const long long len = l < cn0 ? b1 - b0 : 0;
+            const long long inc = wave_incl_scan64(len + (len > 0 ? FLAT_ONE : 0));
+            const long long all = __shfl(inc, WAVE - 1);
+            const IX tot = (IX)(all & FLAT_LEN);
+            const int cn = (int)(all >> FLAT_SHIFT);
+            wave_lds_sync();
+            if (len > 0) {
+                const int run = (int)(inc >> FLAT_SHIFT) - 1;
+                const long long end = inc & FLAT_LEN;
+                off[run] = (IX)end;
+                rel[run] = (IX)(b0 - (end - len));
+                if constexpr (VALUES) sav[run] = av;
+            }
+            wave_lds_sync();
+            int kc = 0;
+            for (IX F = 0; F < tot; F += (IX)(U * WAVE)) {
+                int k[U], rk[U];
+                IX e[U];
+                if constexpr (VALUES) {  // the products' ranks, on their way during the search for their runs
+#pragma unroll
+                    for (int u = 0; u < U; ++u) rk[u] = map[min(F + (u * WAVE + l), tot - 1)];
+                }
+                kc = flat_window<U>(off, cn, F, tot, kc, wi, k);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    k[u] += kc;
+                    e[u] = rel[k[u]] + min(F + (u * WAVE + l), tot - 1);
+                }
+                products(cur, map, F, tot, k, e, rk);
+            }
+            map += tot;
+        }
+        if (have) {
+            b0 = a.brp[nj];
+            b1 = a.brp[nj + 1];
+        }
+        wave_lds_sync();
+        finish(cur);
+        av = nav;
+        cur = nxt;
+        nxt = after;
+        wave_lds_sync();
+    }
+}
+
+// Values of the launch's rows on their position maps.  Bound by latency, so by
+// wavefronts and loads in flight: r_max (the longest row of the launch) sizes
+// the LDS.  Batch of 48 random products, FP32 (6.1e8 products): 2.7 ms, its
+// data unit 76 to 91% busy; with lane groups per B row and one load in flight
+// 3.7 ms.
+template <typename VT, int ACC, typename IX, int U>
+__global__ __launch_bounds__(WAVE) void k_map_flat(NumArgs<VT> a) {
+    using Acc = Accum<VT, ACC>;
+    using S = typename Acc::store_t;
+    extern __shared__ __align__(16) unsigned char smem[];
+    S *vals = (S *)smem;
+    __shared__ IX rel[WAVE], off[WAVE];  // per staged run (see spg_flat.hpp)
+    __shared__ VT sav[WAVE];
+    __shared__ __align__(16) uint16_t wi[U * WAVE];
+    const int l = lane_id();
+    for (int u = l; u < a.r_max; u += WAVE) vals[u] = Acc::zero();
+    const int64_t cbase = a.cbase_row >= 0 ? a.coff[a.cbase_row] : 0;
+    auto rlast = [&](const FlatRow &r) { return max(min(r.rn, a.r_max) - 1, 0); };
+    flat_rows<true, VT, IX, U>(
+        a, rel, off, sav, wi, [](const FlatRow &) {},
+        [&](const FlatRow &r, const uint16_t *, IX F, IX tot, int (&k)[U], IX (&e)[U], int (&rk)[U]) {
+            VT bv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) bv[u] = a.bval[e[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (F + (u * WAVE + l) < tot) Acc::add(&vals[min(rk[u], rlast(r))], sav[k[u]], bv[u]);
+        },
+        [&](const FlatRow &r) {
+            for (int u = l; u < min(r.rn, a.r_max); u += WAVE) {
+                a.cval[r.cb - cbase + u] = Acc::fin(vals[u]);
+                vals[u] = Acc::zero();
+            }
+        });
+}
+
+// Position map of the launch's rows (one-time, from C's sorted columns cci): a
+// row's columns staged in LDS, padded to a power of two, and the searches of a
+// round advanced together.  r_max: entries the dynamic LDS holds (longer rows
+// cannot occur: the launch's longest row sizes it).  Batch of 48 random
+// products: 4.4 ms; a search per lane in HBM took 13.4 ms.
+template <typename IX, int U>
+__global__ __launch_bounds__(WAVE) void k_posmap_flat(NumArgs<double> a, const int32_t *cci) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int32_t *cols = (int32_t *)smem;
+    __shared__ IX rel[WAVE], off[WAVE];
+    __shared__ __align__(16) uint16_t wi[U * WAVE];
+    const int l = lane_id();
+    int half = 0;  // the search runs over 2 * half - 1 entries
+    flat_rows<false, double, IX, U>(
+        a, rel, off, (double *)nullptr, wi,
+        [&](const FlatRow &r) {
+            half = 1;
+            while (2 * half <= r.rn && 4 * half <= a.r_max) half *= 2;
+            for (int t = l; t < 2 * half; t += WAVE) cols[t] = t < r.rn ? cci[r.cb + t] : INT_MAX;
+        },
+        [&](const FlatRow &, uint16_t *map, IX F, IX tot, int (&)[U], IX (&e)[U], int (&)[U]) {
+            int c[U], at[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) c[u] = a.bci[e[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) at[u] = 0;
+            for (int s = half; s > 0; s >>= 1)
+#pragma unroll
+                for (int u = 0; u < U; ++u) at[u] += cols[at[u] + s - 1] < c[u] ? s : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (F + (u * WAVE + l) >= tot) continue;
+                if (cols[at[u]] != c[u]) {
+                    atomicAdd(&a.st->mismatch, 1);  // C's columns are not this product's
+                    at[u] = 0;
+                }
+                map[F + (u * WAVE + l)] = (uint16_t)at[u];
+            }
+        },
+        [](const FlatRow &) {});
+}
+
+// The same for short rows, in teams.
 template <typename VT, int ACC, int LGT, int LGS>
 __global__ __launch_bounds__(WAVE) void k_num_map(NumArgs<VT> a) {
     using Acc = Accum<VT, ACC>;
@@ -238,23 +423,57 @@ hipError_t by_lgs(int lgs, F &&f) {
     case 3: return f(std::integral_constant<int, (LGT >= 3 ? 3 : 2)>{});
     case 4: return f(std::integral_constant<int, (LGT >= 4 ? 4 : 2)>{});
     case 5: return f(std::integral_constant<int, (LGT >= 5 ? 5 : 2)>{});
-    default: return f(std::integral_constant<int, (LGT >= 6 ? 6 : 2)>{});
+    default: return f(std::integral_constant<int, 2>{});
     }
 }
 
 template <typename F>
-hipError_t by_lgt(int lgt, F &&f) {
-    switch (std::max(3, std::min(lgt, 6))) {
-    case 3: return f(std::integral_constant<int, 3>{});
+hipError_t by_team(int lgt, F &&f) {  // teams of less than a wavefront
+    switch (lgt) {
     case 4: return f(std::integral_constant<int, 4>{});
     case 5: return f(std::integral_constant<int, 5>{});
-    default: return f(std::integral_constant<int, 6>{});
+    default: return f(std::integral_constant<int, 3>{});
     }
+}
+
+template <typename IX>
+hipError_t posmap_flat(NumArgs<double> a, const int32_t *cci, const LaunchCfg &c, int64_t rows) {
+    int r = 2 * WAVE;
+    while (r <= a.r_max) r *= 2;
+    a.r_max = r;
+    int grid = resident_grid(k_posmap_flat<IX, 4>, 4 * (size_t)r, c.cus);
+    grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((rows + XCDS - 1) / XCDS) * XCDS));
+    hipLaunchKernelGGL((k_posmap_flat<IX, 4>), dim3(grid), dim3(WAVE), 4 * (size_t)r, c.stream, a, cci);
+    return hipGetLastError();
+}
+
+template <typename VT, int ACC, typename IX, int U>
+hipError_t map_flat_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
+    const size_t lds = align16(sizeof(typename Accum<VT, ACC>::store_t) * (size_t)a.r_max);
+    int grid = resident_grid(k_map_flat<VT, ACC, IX, U>, lds, c.cus);
+    grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((rows + XCDS - 1) / XCDS) * XCDS));
+    hipLaunchKernelGGL((k_map_flat<VT, ACC, IX, U>), dim3(grid), dim3(WAVE), lds, c.stream, a);
+    return hipGetLastError();
+}
+
+// Products per lane and round by the largest kind of the launch: most rows then
+// take one or two rounds (20000 rows of 100 to 150 products, FP64: 49.5 us a
+// call with 4, 52 with 2 or 8).  32-bit product numbers where 64 A entries cannot form 2^31 products.
+template <typename VT, int ACC>
+hipError_t map_flat(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
+    const int last = a.rs.kind + a.rs.more;
+    const bool i32 = a.nnzb * WAVE < (int64_t(1) << 31);
+    if (last == K_SR || last == K_BK0)
+        return i32 ? map_flat_u<VT, ACC, int32_t, 2>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 2>(a, c, rows);
+    if (last == K_BK1 || last == K_BK2)
+        return i32 ? map_flat_u<VT, ACC, int32_t, 4>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 4>(a, c, rows);
+    return i32 ? map_flat_u<VT, ACC, int32_t, 8>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 8>(a, c, rows);
 }
 
 template <typename VT, int ACC>
 hipError_t num_map_acc(const NumArgs<VT> &a, int lgt, int lgs, const LaunchCfg &c, int64_t rows) {
-    return by_lgt(lgt, [&](auto T) {
+    if (lgt >= 6) return map_flat<VT, ACC>(a, c, rows);
+    return by_team(lgt, [&](auto T) {
         constexpr int LT = decltype(T)::value;
         return by_lgs<LT>(lgs, [&](auto S) {
             constexpr int LS = decltype(S)::value;
@@ -265,11 +484,13 @@ hipError_t num_map_acc(const NumArgs<VT> &a, int lgt, int lgs, const LaunchCfg &
 
 }  // namespace
 
-size_t lds_num_map(int r_max, int lgt, int acc_bytes) { return map_layout(r_max, WAVE >> lgt, acc_bytes).total; }
 
 hipError_t launch_posmap(const NumArgs<double> &a, const int32_t *cci, int lgt, int lgs, const LaunchCfg &c,
                          int64_t rows) {
-    return by_lgt(lgt, [&](auto T) {
+    if (lgt >= 6)
+        return a.nnzb * WAVE < (int64_t(1) << 31) ? posmap_flat<int32_t>(a, cci, c, rows)
+                                                  : posmap_flat<int64_t>(a, cci, c, rows);
+    return by_team(lgt, [&](auto T) {
         constexpr int LT = decltype(T)::value;
         return by_lgs<LT>(lgs, [&](auto S) {
             constexpr int LS = decltype(S)::value;
