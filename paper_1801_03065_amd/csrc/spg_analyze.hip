@@ -78,6 +78,139 @@ __device__ __forceinline__ int row_max(int v) {
     return max(v, row_ror<1>(v));
 }
 
+// ------------------------------------------------------------------ long rows
+// Rows of more than LONG_ROW entries are left by their lane group and taken by
+// the whole wavefront after its other rows, LONG_U loads per lane in flight:
+// the longest row of a power-law graph otherwise decides the kernel (R-MAT scale 17: rows of B 293
+// -> 82 us, compression 505 -> 152, rows of A 730 -> 316; scale 13: 27 -> 13,
+// 50 -> 23, 49 -> 30).
+constexpr int LONG_ROW = 256, LONG_U = 4;
+
+// uflag: sorted row, unsorted row, unsorted row whose words are still to be counted
+enum { UF_SORTED = 0, UF_UNSORTED = 1, UF_UNCOUNTED = 2 };
+
+__device__ __forceinline__ int64_t lane_val(int64_t v, int src) {  // the lane's value, uniform
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, src);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)((uint64_t)v >> 32), src);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int wave_min(int v) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d));
+    return v;
+}
+
+// body(row, b, e) for the wavefront's long rows, one at a time: its first row
+// of a step is r0, a row per `group` lanes, rp the row pointers.
+template <typename F>
+__device__ __forceinline__ void for_long_rows(int64_t r0, int64_t n, int64_t step, int group, const int64_t *rp, F &&body) {
+    for (; r0 < n; r0 += step) {
+        const int64_t r = r0 + lane_id() / group;
+        const int64_t b = r < n ? rp[r] : 0, e = r < n ? rp[r + 1] : 0;
+        for (unsigned long long todo = __ballot(e - b > LONG_ROW && lane_id() % group == 0); todo; todo &= todo - 1) {
+            const int src = __ffsll((long long)todo) - 1;
+            body(lane_val(r, src), lane_val(b, src), lane_val(e, src));
+        }
+    }
+}
+
+// One row of B, columns [b, e): smallest and largest column, word changes, order.
+struct RowScan {
+    int cmin, cmax, heads, unsorted;
+};
+__device__ __forceinline__ RowScan brow_wave(int64_t b, int64_t e, int64_t ncols, const int32_t *bci, int &badcol) {
+    const int l = lane_id();
+    RowScan r{INT_MAX, -1, 0, 0};
+    for (int64_t c0 = b; c0 < e; c0 += LONG_U * WAVE) {
+        int col[LONG_U], prev[LONG_U];
+#pragma unroll
+        for (int u = 0; u < LONG_U; ++u) {
+            const int64_t idx = c0 + u * WAVE + l;
+            col[u] = idx < e ? bci[idx] : -1;
+            prev[u] = idx < e && idx > b ? bci[idx - 1] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < LONG_U; ++u) {
+            if (c0 + u * WAVE + l >= e) continue;
+            r.cmin = min(r.cmin, col[u]);
+            r.cmax = max(r.cmax, col[u]);
+            r.unsorted |= prev[u] >= col[u];
+            r.heads += (col[u] >> 5) != (prev[u] >> 5);
+            badcol |= (col[u] < 0) | ((int64_t)col[u] >= ncols);
+        }
+    }
+    r.cmin = wave_min(r.cmin);
+    r.cmax = wave_max(r.cmax);
+    r.heads = __builtin_amdgcn_readlane(wave_scan_dpp(r.heads), WAVE - 1);
+    r.unsorted = __ballot(r.unsorted) != 0;
+    return r;
+}
+
+// The long rows of B of a wavefront (see for_long_rows): their records.
+__device__ __forceinline__ void long_rows_of_b(int64_t r0, int64_t n, int64_t step, int group, int64_t ncols,
+                                               const int64_t *brp, const int32_t *bci, BRow *out, uint8_t *uflag,
+                                               DevStats *st, int &badcol) {
+    for_long_rows(r0, n, step, group, brp, [&](int64_t r, int64_t b, int64_t e) {
+        const RowScan w = brow_wave(b, e, ncols, bci, badcol);
+        if (lane_id() == 0) {
+            out[r] = BRow{(int32_t)(e - b), w.heads, w.cmin >> 5, w.cmax >> 5};
+            uflag[r] = w.unsorted ? UF_UNCOUNTED : UF_SORTED;
+            if (w.unsorted) st->unsorted = st->uncounted = 1;
+        }
+    });
+}
+
+// One step of an OR-scan inside runs (seg: run number, never decreasing over
+// the lanes).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void or_step(uint32_t &acc, int seg) {
+    const uint32_t v = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc, CTRL, ROWS, 0xF, false);
+    const int vs = __builtin_amdgcn_update_dpp(-1, seg, CTRL, ROWS, 0xF, false);
+    if (vs == seg) acc |= v;
+}
+
+// Compressed form of one sorted row of B, columns [b, e), at bcw[o0].
+__device__ __forceinline__ void compress_wave(int64_t b, int64_t e, int64_t o0, const int32_t *bci, uint2 *bcw) {
+    const int l = lane_id();
+    int64_t pos0 = o0;  // place of the first run that starts in the chunk
+    int prev_last = -1;
+    uint32_t carry = 0;
+    for (int64_t c0 = b; c0 < e; c0 += LONG_U * WAVE) {
+        int col[LONG_U];
+#pragma unroll
+        for (int u = 0; u < LONG_U; ++u) {
+            const int64_t idx = c0 + u * WAVE + l;
+            col[u] = idx < e ? bci[idx] : INT_MAX;
+        }
+        const int64_t nx = c0 + LONG_U * WAVE;
+        const int beyond = nx < e ? bci[nx] : INT_MAX;
+#pragma unroll
+        for (int u = 0; u < LONG_U; ++u) {
+            const bool v = c0 + u * WAVE + l < e;
+            const int before = __shfl_up(col[u], 1), after = __shfl_down(col[u], 1);
+            const int prevc = l == 0 ? prev_last : before;
+            const int next0 = u + 1 < LONG_U ? __builtin_amdgcn_readlane(col[u + 1 < LONG_U ? u + 1 : u], 0) : beyond;
+            const int nextc = l == WAVE - 1 ? next0 : after;
+            const bool head = v && (col[u] >> 5) != (prevc >> 5);
+            const unsigned long long bal = __ballot(head);
+            const int seg = mbcnt(bal) + head;  // 0: the run that came with the carry
+            uint32_t acc = v ? 1u << (col[u] & 31) : 0u;
+            if (seg == 0) acc |= carry;
+            or_step<0x111, 0xF>(acc, seg);  // row_shr:1, 2, 4, 8
+            or_step<0x112, 0xF>(acc, seg);
+            or_step<0x114, 0xF>(acc, seg);
+            or_step<0x118, 0xF>(acc, seg);
+            or_step<0x142, 0xA>(acc, seg);  // row_bcast:15 into rows 1, 3
+            or_step<0x143, 0xC>(acc, seg);  // row_bcast:31 into rows 2, 3
+            const bool tail = v && (nextc == INT_MAX || (nextc >> 5) != (col[u] >> 5));
+            if (tail) bcw[pos0 + seg - 1] = make_uint2((uint32_t)(col[u] >> 5), acc);
+            carry = (uint32_t)__builtin_amdgcn_readlane(v && !tail ? (int)acc : 0, WAVE - 1);
+            pos0 += __popcll(bal);
+            prev_last = __builtin_amdgcn_readlane(col[u], WAVE - 1);
+        }
+    }
+}
+
 // ------------------------------------------------------------------ B rows
 // One group of 16 lanes per row of B.  For rows whose columns are strictly
 // increasing, the number of distinct words col >> 5 is the number of word
@@ -90,8 +223,6 @@ __device__ __forceinline__ int row_max(int v) {
 constexpr int BR_GS = 16;
 constexpr int BR_HASH = 64, BR_SLOTS = 2 * BR_HASH;
 constexpr int UB_WORDS = 16384;  // window words of the bitmap kernel
-// uflag: sorted row, unsorted row, unsorted row whose words are still to be counted
-enum { UF_SORTED = 0, UF_UNSORTED = 1, UF_UNCOUNTED = 2 };
 
 __global__ __launch_bounds__(BLK) void k_brow(int64_t n, int64_t ncols, const int64_t *brp, const int32_t *bci,
                                                BRow *out, uint8_t *uflag, DevStats *st) {
@@ -100,8 +231,13 @@ __global__ __launch_bounds__(BLK) void k_brow(int64_t n, int64_t ncols, const in
     const int64_t g0 = ((int64_t)blockIdx.x * BLK + threadIdx.x) / BR_GS;
     const int64_t ng = (int64_t)gridDim.x * BLK / BR_GS;
     int badcol = 0;
+    bool any_long = false;
     for (int64_t r = g0; r < n; r += ng) {
         const int64_t b = brp[r], e = brp[r + 1];
+        if (e - b > LONG_ROW) {
+            any_long = true;
+            continue;
+        }
         int cmin = INT_MAX, cmax = -1, heads = 0, unsorted = 0, prev_last = -1;
         for (int64_t c0 = b; c0 < e; c0 += BR_GS) {
             const int64_t idx = c0 + q;
@@ -159,6 +295,7 @@ __global__ __launch_bounds__(BLK) void k_brow(int64_t n, int64_t ncols, const in
             uflag[r] = (uint8_t)flag;
         }
     }
+    if (__ballot(any_long)) long_rows_of_b(g0 - lane_id() / BR_GS, n, ng, BR_GS, ncols, brp, bci, out, uflag, st, badcol);
     if (__ballot(badcol) && lane_id() == 0) atomicOr(&st->bad_input, 1);
 }
 static_assert(BR_SLOTS == 128, "the word hash of k_brow has 7 bits");
@@ -171,8 +308,14 @@ constexpr int BR_SHORT = 8, BR_PAIRS = 16;
 __global__ __launch_bounds__(BLK) void k_brow_short(int64_t n, int64_t ncols, const int64_t *brp, const int32_t *bci,
                                                      BRow *out, uint8_t *uflag, DevStats *st) {
     int badcol = 0;
-    for (int64_t r = (int64_t)blockIdx.x * BLK + threadIdx.x; r < n; r += (int64_t)gridDim.x * BLK) {
+    bool any_long = false;
+    const int64_t r0 = (int64_t)blockIdx.x * BLK + threadIdx.x, step = (int64_t)gridDim.x * BLK;
+    for (int64_t r = r0; r < n; r += step) {
         const int64_t b = brp[r], e = brp[r + 1];
+        if (e - b > LONG_ROW) {
+            any_long = true;
+            continue;
+        }
         int cmin = INT_MAX, cmax = -1, heads = 0, unsorted = 0, prev = -1;
         for (int64_t k = b; k < e; ++k) {
             const int col = bci[k];
@@ -207,6 +350,7 @@ __global__ __launch_bounds__(BLK) void k_brow_short(int64_t n, int64_t ncols, co
         out[r] = o;
         uflag[r] = (uint8_t)flag;
     }
+    if (__ballot(any_long)) long_rows_of_b(r0 - lane_id(), n, step, 1, ncols, brp, bci, out, uflag, st, badcol);
     if (__ballot(badcol) && lane_id() == 0) atomicOr(&st->bad_input, 1);
 }
 
@@ -277,9 +421,14 @@ __global__ __launch_bounds__(BLK) void k_compress_sorted(int64_t n, const int64_
     const int q = threadIdx.x & (BR_GS - 1);
     const int64_t g0 = ((int64_t)blockIdx.x * BLK + threadIdx.x) / BR_GS;
     const int64_t ng = (int64_t)gridDim.x * BLK / BR_GS;
+    bool any_long = false;
     for (int64_t r = g0; r < n; r += ng) {
         if (unsorted[r]) continue;
         const int64_t b = brp[r], e = brp[r + 1];
+        if (e - b > LONG_ROW) {
+            any_long = true;
+            continue;
+        }
         const int64_t o0 = bcrp[r];
         int heads_before = 0, prev_last = -1;
         uint32_t carry = 0;
@@ -299,17 +448,10 @@ __global__ __launch_bounds__(BLK) void k_compress_sorted(int64_t n, const int64_
             uint32_t acc = v ? (1u << (col & 31)) : 0u;
             if (seg == 0) acc |= carry;
             // OR-scan inside runs: a lane takes the bits of lane q-d when it is in the same run
-#define SR_OR_STEP(CTRL)                                                                      \
-    {                                                                                         \
-        const uint32_t t = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc, CTRL, 0xF, 0xF, false); \
-        const int ts = __builtin_amdgcn_update_dpp(-1, seg, CTRL, 0xF, 0xF, false);        \
-        if (ts == seg) acc |= t;                                                              \
-    }
-            SR_OR_STEP(0x111)
-            SR_OR_STEP(0x112)
-            SR_OR_STEP(0x114)
-            SR_OR_STEP(0x118)
-#undef SR_OR_STEP
+            or_step<0x111, 0xF>(acc, seg);
+            or_step<0x112, 0xF>(acc, seg);
+            or_step<0x114, 0xF>(acc, seg);
+            or_step<0x118, 0xF>(acc, seg);
             // the run ends here when the next column is in another word (or there is none)
             const bool tail = v && (idx + 1 >= e || (nextc >> 5) != (col >> 5));
             const int64_t pos = o0 + heads_before + seg - 1;
@@ -320,15 +462,25 @@ __global__ __launch_bounds__(BLK) void k_compress_sorted(int64_t n, const int64_
             prev_last = row_last(col);
         }
     }
+    if (__ballot(any_long))
+        for_long_rows(g0 - lane_id() / BR_GS, n, ng, BR_GS, brp, [&](int64_t r, int64_t b, int64_t e) {
+            if (!unsorted[r]) compress_wave(b, e, bcrp[r], bci, bcw);
+        });
 }
 
 // The same for B with short rows: one lane per row walks its columns and
 // writes each word run where it ends.
 __global__ __launch_bounds__(BLK) void k_compress_short(int64_t n, const int64_t *brp, const int32_t *bci,
                                                          const uint8_t *unsorted, const int64_t *bcrp, uint2 *bcw) {
-    for (int64_t r = (int64_t)blockIdx.x * BLK + threadIdx.x; r < n; r += (int64_t)gridDim.x * BLK) {
+    bool any_long = false;
+    const int64_t r0 = (int64_t)blockIdx.x * BLK + threadIdx.x, step = (int64_t)gridDim.x * BLK;
+    for (int64_t r = r0; r < n; r += step) {
         if (unsorted[r]) continue;
         const int64_t b = brp[r], e = brp[r + 1];
+        if (e - b > LONG_ROW) {
+            any_long = true;
+            continue;
+        }
         int64_t pos = bcrp[r];
         int curw = INT_MIN;
         uint32_t bits = 0;
@@ -344,6 +496,10 @@ __global__ __launch_bounds__(BLK) void k_compress_short(int64_t n, const int64_t
         }
         if (curw != INT_MIN) bcw[pos] = make_uint2((uint32_t)curw, bits);
     }
+    if (__ballot(any_long))
+        for_long_rows(r0 - lane_id(), n, step, 1, brp, [&](int64_t r, int64_t b, int64_t e) {
+            if (!unsorted[r]) compress_wave(b, e, bcrp[r], bci, bcw);
+        });
 }
 
 // ------------------------------------------------------------------ A rows
@@ -391,17 +547,15 @@ __global__ __launch_bounds__(BLK) void k_rowinfo(int64_t m, int64_t n, const int
     const int64_t ng = (int64_t)gridDim.x * BLK / RI_GS;
     long long s_fm = 0, s_fmc = 0, s_mx = 0, s_mxc = 0, s_fmb = 0, s_fmcb = 0, s_mxa = 0;
     int badcol = 0;
-    for (int64_t i = g0; i < m; i += ng) {
-        const int64_t b = arp[i], e = arp[i + 1];
-        long long f = 0, fc = 0;
-        int wlo = INT_MAX, whi = -1;
-        for (int64_t base = b; base < e; base += RI_GS * RI_U) {
+    // entries [base + first, ...) below end, `step` apart, RI_U loads in flight
+    auto walk = [&](int64_t base, int64_t end, int first, int step, long long &f, long long &fc, int &wlo, int &whi) {
+        for (; base < end; base += step * RI_U) {
             int j[RI_U];
 #pragma unroll
             for (int u = 0; u < RI_U; ++u) {
-                const int64_t idx = base + q + u * RI_GS;
-                j[u] = idx < e ? aci[idx] : -1;
-                if (idx < e && (uint64_t)(int64_t)j[u] >= (uint64_t)n) badcol = 1;
+                const int64_t idx = base + first + u * step;
+                j[u] = idx < end ? aci[idx] : -1;
+                if (idx < end && (uint64_t)(int64_t)j[u] >= (uint64_t)n) badcol = 1;
                 if ((uint64_t)(int64_t)j[u] >= (uint64_t)n) j[u] = -1;  // out of range (flagged): skipped
             }
             BRow br[RI_U];
@@ -417,6 +571,17 @@ __global__ __launch_bounds__(BLK) void k_rowinfo(int64_t m, int64_t n, const int
                 }
             }
         }
+    };
+    bool any_long = false;
+    for (int64_t i = g0; i < m; i += ng) {
+        const int64_t b = arp[i], e = arp[i + 1];
+        if (e - b > LONG_ROW) {
+            any_long = true;
+            continue;
+        }
+        long long f = 0, fc = 0;
+        int wlo = INT_MAX, whi = -1;
+        walk(b, e, q, RI_GS, f, fc, wlo, whi);
         // reductions over the 8-lane group: DPP quad permutes (lane ^ 1,
         // lane ^ 2), then the half-row mirror (lane i <-> 7 - i) joins the two
         // quads
@@ -470,6 +635,24 @@ __global__ __launch_bounds__(BLK) void k_rowinfo(int64_t m, int64_t n, const int
         red[5][wv] = s_fmcb;
         red[6][wv] = s_mxa;
     }
+    if (__ballot(any_long))  // (their sums go straight to the partials, which frees registers for the loads)
+        for_long_rows(g0 - lane_id() / RI_GS, m, ng, RI_GS, arp, [&](int64_t i, int64_t b, int64_t e) {
+            long long f = 0, fc = 0;
+            int wlo = INT_MAX, whi = -1;
+            walk(b, e, lane_id(), WAVE, f, fc, wlo, whi);
+            f = wave_sum64(f);
+            fc = wave_sum64(fc);
+            wlo = wave_min(wlo);
+            whi = wave_max(whi);
+            if (lane_id() == 0) {
+                rflops[i] = f;
+                rflopsc[i] = fc;
+                rwin[i] = make_int2(wlo, whi);
+                const long long add[RI_F] = {f, fc, f, fc, f > SR_F_MAX ? f : 0, f > SR_F_MAX ? fc : 0, e - b};
+#pragma unroll
+                for (int x = 0; x < RI_F; ++x) red[x][wv] = ri_is_max(x) ? max(red[x][wv], add[x]) : red[x][wv] + add[x];
+            }
+        });
     __syncthreads();
     if (threadIdx.x < RI_F) {
         const int f = threadIdx.x;
