@@ -62,7 +62,7 @@ __global__ __launch_bounds__(WAVE) void k_bwd(BwdArgs<VT> a, int rmax) {
     __shared__ IX rel[WAVE], off[WAVE];  // per staged run (see spg_flat.hpp)
     __shared__ VT sav[WAVE];
     __shared__ double sdA[WAVE];
-    __shared__ __align__(16) uint16_t wi[U * WAVE];
+    __shared__ __align__(8) uint32_t wb[2 * U];
     const int l = lane_id();
     const Slice sl = xcd_slice(0, a.m);
     int64_t r = sl.idx;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(WAVE) void k_bwd(BwdArgs<VT> a, int rmax) {
                 int k[U], c[U], p[U];
                 IX e[U];
                 VT bv[U], gv[U];
-                kc = flat_window<U>(off, cn, F, tot, kc, wi, k);
+                kc = flat_window<U>(off, cn, F, tot, kc, wb, k);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const IX f = F + (u * WAVE + l);

@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "spg_accum.hpp"
+#include "spg_flat.hpp"
 #include "spg_internal.hpp"
 
 namespace spg {
@@ -114,6 +115,20 @@ __device__ __forceinline__ void bk_sync() {
     }
 }
 
+// Marks in wb (2 U words, this wavefront's) the bit before the first product of
+// each nonempty run (products [ex, ex + len)) that starts inside the
+// wavefront's products after the first of them; returns the runs that start
+// before, less the row's first.
+template <int NW, int U>
+__device__ __forceinline__ int bk_starts(uint32_t *wb, int len, int ex, int wv) {
+    const int l = lane_id();
+    if (l < 2 * U) wb[l] = 0u;
+    wave_lds_sync();
+    const int p = ex - 1 - wv * (WAVE * U);
+    if (len > 0 && (unsigned)p < (unsigned)(WAVE * U)) atomicOr(&wb[p >> 5], 1u << (p & 31));
+    return NW == 1 ? 0 : __popcll(__ballot(len > 0 && ex > 0 && p < 0));
+}
+
 // NW wavefronts per row, U products per lane.
 template <typename VT, int ACC, int NW, int U>
 __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_num_bk(NumArgs<VT> a) {
@@ -123,11 +138,11 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
     __shared__ __align__(16) uint32_t cnt[CAP];  // bucket: count, then start | count << 16
     __shared__ __align__(16) int32_t key[CAP];   // columns in bucket order, then sorted
     __shared__ __align__(16) unsigned char val_raw[CAP * sizeof(P)];
-    __shared__ int32_t st_rel[WAVE];             // per A entry: B row start - first product
+    __shared__ int32_t st_rel[WAVE];             // per nonempty B row: its start - its first product
     __shared__ VT st_a[WAVE];
+    __shared__ __align__(8) uint32_t starts[NW][2 * U];  // per wavefront: B row starts (see spg_flat.hpp)
     __shared__ int red[2 * NW + 2];
-    P *val = (P *)val_raw;                // products in sorted order
-    uint16_t *own = (uint16_t *)val_raw;  // before that: A entry that starts at a product
+    P *val = (P *)val_raw;  // products in sorted order
     const int t = threadIdx.x, l = lane_id(), wv = NW == 1 ? 0 : read_first(t / WAVE);
     const int p0 = wv * (WAVE * U) + l;   // this lane's products: p0 + u * WAVE
 #pragma unroll
@@ -162,21 +177,14 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
         const int f = __builtin_amdgcn_readlane(inc, WAVE - 1);
         const int64_t n64 = d.ce - d.cb;
         const bool fits = f > 0 && f <= CAP && n64 <= f;  // else the structure changed behind the plan
-        if (NW == 1 || wv == 0) {
-            st_rel[l] = (int32_t)b0 - ex;
-            st_a[l] = av;
+        if ((NW == 1 || wv == 0) && len > 0) {
+            const int run = mbcnt(__ballot(len > 0));
+            st_rel[run] = (int32_t)b0 - ex;
+            st_a[run] = av;
         }
-#pragma unroll
-        for (int u = 0; u < U / 2; ++u) ((uint32_t *)own)[u * WG + t] = 0;
+        // runs that start before this wavefront's products; the others' starts
+        const int base = bk_starts<NW, U>(starts[wv], len, ex, wv);
         if (NW > 1 && t < 2) red[2 * NW + t] = 0;
-        bk_sync<NW>();
-        if ((NW == 1 || wv == 0) && len > 0 && (unsigned)ex < (unsigned)CAP) own[ex] = (uint16_t)l;
-        // the A entry in progress where this wavefront's products start
-        int carry = 0;
-        if (NW > 1) {
-            const unsigned long long before = __ballot(len > 0 && ex < wv * (WAVE * U));
-            carry = before ? 63 - __clzll(before) : 0;
-        }
         // next row, first level
         const int nna = has_next ? dn.na : 0;
         int nj = 0;
@@ -187,14 +195,8 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
         bk_sync<NW>();
         int col[U], k[U];
         VT bv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) k[u] = own[u * WAVE + p0];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            k[u] = max(bk_maxscan(k[u]), carry);
-            carry = __builtin_amdgcn_readlane(k[u], WAVE - 1);
-        }
-        uint32_t e[U], kp[(U + 3) / 4] = {};  // kp: the A entries (below 64) packed, four to a register
+        flat_count<U>(starts[wv], base, k);
+        uint32_t e[U], kp[(U + 3) / 4] = {};  // kp: the runs (below 64) packed, four to a register
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int p = u * WAVE + p0;
@@ -424,7 +426,7 @@ __global__ __launch_bounds__(WAVE * NW) void k_sym_bk(SymArgs a) {
     constexpr int WG = WAVE * NW, CAP = WG * U, SLOTS = 2 * CAP;
     constexpr int LG = __builtin_ctz(SLOTS);
     __shared__ __align__(16) int32_t tab[SLOTS];
-    __shared__ __align__(16) uint16_t own[CAP];
+    __shared__ __align__(8) uint32_t starts[NW][2 * U];
     __shared__ int32_t st_rel[WAVE];
     __shared__ int red[NW];
     const int t = threadIdx.x, l = lane_id(), wv = NW == 1 ? 0 : read_first(t / WAVE);
@@ -461,28 +463,17 @@ __global__ __launch_bounds__(WAVE * NW) void k_sym_bk(SymArgs a) {
         const int len = l < na ? (int)(b1 - b0) : 0;
         const int inc = wave_scan_dpp(len), ex = inc - len;
         const int f = min(__builtin_amdgcn_readlane(inc, WAVE - 1), CAP);
-        if (NW == 1 || wv == 0) st_rel[l] = (int32_t)b0 - ex;
-#pragma unroll
-        for (int u = 0; u < U / 2; ++u) ((uint32_t *)own)[u * WG + t] = 0;
-        bk_sync<NW>();
-        if ((NW == 1 || wv == 0) && len > 0 && (unsigned)ex < (unsigned)CAP) own[ex] = (uint16_t)l;
-        int carry = 0;
-        if (NW > 1) {
-            const unsigned long long before = __ballot(len > 0 && ex < wv * (WAVE * U));
-            carry = before ? 63 - __clzll(before) : 0;
-        }
+        if ((NW == 1 || wv == 0) && len > 0) st_rel[mbcnt(__ballot(len > 0))] = (int32_t)b0 - ex;
+        const int base = bk_starts<NW, U>(starts[wv], len, ex, wv);
         int nj = 0;
         if (l < nna) nj = a.aci[nab + l];
         bk_sync<NW>();
         int col[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) col[u] = own[u * WAVE + p0];
+        flat_count<U>(starts[wv], base, col);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = max(bk_maxscan(col[u]), carry);
-            carry = __builtin_amdgcn_readlane(k, WAVE - 1);
             const int p = u * WAVE + p0;
-            col[u] = p < f ? (int)min((uint32_t)(st_rel[k] + p), elast) : 0;
+            col[u] = p < f ? (int)min((uint32_t)(st_rel[col[u]] + p), elast) : 0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) col[u] = ld32(a.bci, (uint32_t)col[u]);

@@ -78,7 +78,7 @@ __device__ __forceinline__ int mk_probe(const int *keys, uint32_t mask, int c, u
 
 // LDS of one workgroup of `wg` lanes; big: room for the bit filter.
 struct MkLayout {
-    size_t rel, off, av, red, wi, filt, keys, posv, acc, total;
+    size_t rel, off, av, red, wb, filt, keys, posv, acc, total;
 };
 __host__ __device__ inline MkLayout mk_layout(int wg, int lg, int mmax, bool big) {
     MkLayout L{};
@@ -91,9 +91,9 @@ __host__ __device__ inline MkLayout mk_layout(int wg, int lg, int mmax, bool big
     o += 8 * (size_t)wg;
     L.red = o;
     o += 8 * (size_t)(wg / WAVE + 2);
+    L.wb = o;  // per wavefront: starts of the runs in its window (see flat_window)
+    o += 8 * (size_t)MK_U * (wg / WAVE);
     o = align16(o);
-    L.wi = o;  // per wavefront: runs of its window's products
-    o += 2 * (size_t)MK_U * wg;
     L.filt = o;
     if (big) o += MK_FBITS / 8;
     L.keys = o;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_mask(MaskArgs<VT> a, int lg, int m
     VT *sav = (VT *)(smem + L.av);
     long long *red = (long long *)(smem + L.red);
     const int t = threadIdx.x, l = lane_id(), wv = NW == 1 ? 0 : read_first(t / WAVE);
-    uint16_t *wi = (uint16_t *)(smem + L.wi) + wv * (MK_U * WAVE);
+    uint32_t *wb = (uint32_t *)(smem + L.wb) + wv * (2 * MK_U);
     int *keys = (int *)(smem + L.keys);
     uint16_t *posv = (uint16_t *)(smem + L.posv);
     double *acc = (double *)(smem + L.acc);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_mask(MaskArgs<VT> a, int lg, int m
             for (IX F = (IX)wv * (MK_U * WAVE); F < tot; F += (IX)MK_U * WG) {
                 int k[MK_U], c[MK_U], kk[MK_U], at[MK_U];
                 IX e[MK_U];
-                kc = flat_window<MK_U>(off, cn, F, tot, kc, wi, k);
+                kc = flat_window<MK_U>(off, cn, F, tot, kc, wb, k);
 #pragma unroll
                 for (int u = 0; u < MK_U; ++u) {
                     const IX f = F + (u * WAVE + l);

@@ -162,7 +162,7 @@ struct FlatRow {
 // chunk, run and B entry per product); finish(row).  Products past the chunk
 // repeat its last one.
 template <bool VALUES, typename VT, typename IX, int U, typename Begin, typename Products, typename Finish>
-__device__ __forceinline__ void flat_rows(const NumArgs<VT> &a, IX *rel, IX *off, VT *sav, uint16_t *wi, Begin &&begin,
+__device__ __forceinline__ void flat_rows(const NumArgs<VT> &a, IX *rel, IX *off, VT *sav, uint32_t *wb, Begin &&begin,
                                           Products &&products, Finish &&finish) {
     const int l = lane_id();
     int64_t lo, hi;
@@ -231,7 +231,7 @@ __device__ __forceinline__ void flat_rows(const NumArgs<VT> &a, IX *rel, IX *off
 #pragma unroll
                     for (int u = 0; u < U; ++u) rk[u] = map[min(F + (u * WAVE + l), tot - 1)];
                 }
-                kc = flat_window<U>(off, cn, F, tot, kc, wi, k);
+                kc = flat_window<U>(off, cn, F, tot, kc, wb, k);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     k[u] += kc;
@@ -267,13 +267,13 @@ __global__ __launch_bounds__(WAVE) void k_map_flat(NumArgs<VT> a) {
     S *vals = (S *)smem;
     __shared__ IX rel[WAVE], off[WAVE];  // per staged run (see spg_flat.hpp)
     __shared__ VT sav[WAVE];
-    __shared__ __align__(16) uint16_t wi[U * WAVE];
+    __shared__ __align__(8) uint32_t wb[2 * U];
     const int l = lane_id();
     for (int u = l; u < a.r_max; u += WAVE) vals[u] = Acc::zero();
     const int64_t cbase = a.cbase_row >= 0 ? a.coff[a.cbase_row] : 0;
     auto rlast = [&](const FlatRow &r) { return max(min(r.rn, a.r_max) - 1, 0); };
     flat_rows<true, VT, IX, U>(
-        a, rel, off, sav, wi, [](const FlatRow &) {},
+        a, rel, off, sav, wb, [](const FlatRow &) {},
         [&](const FlatRow &r, const uint16_t *, IX F, IX tot, int (&k)[U], IX (&e)[U], int (&rk)[U]) {
             VT bv[U];
 #pragma unroll
@@ -300,11 +300,11 @@ __global__ __launch_bounds__(WAVE) void k_posmap_flat(NumArgs<double> a, const i
     extern __shared__ __align__(16) unsigned char smem[];
     int32_t *cols = (int32_t *)smem;
     __shared__ IX rel[WAVE], off[WAVE];
-    __shared__ __align__(16) uint16_t wi[U * WAVE];
+    __shared__ __align__(8) uint32_t wb[2 * U];
     const int l = lane_id();
     int half = 0;  // the search runs over 2 * half - 1 entries
     flat_rows<false, double, IX, U>(
-        a, rel, off, (double *)nullptr, wi,
+        a, rel, off, (double *)nullptr, wb,
         [&](const FlatRow &r) {
             half = 1;
             while (2 * half <= r.rn && 4 * half <= a.r_max) half *= 2;

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     __shared__ int st_off[SG_WG];  // inclusive prefix of the run lengths
     __shared__ VT st_a[SG_WG];
     __shared__ long long red[SG_WG / WAVE + 2];
-    __shared__ __align__(16) uint16_t widx[SG_WG / WAVE][SG_U * WAVE];  // flat_window's scratch per wavefront
+    __shared__ __align__(8) uint32_t wb[SG_WG / WAVE][2 * SG_U];  // flat_window's scratch per wavefront
     const int t = threadIdx.x, l = lane_id(), wv = read_first(t / WAVE);
     for (int w = t; w < SG_NW; w += SG_WG) bits[w] = 0;
     for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;  // every kind of zero
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
                 for (int F = wv * (SG_U * WAVE); F < tot; F += SG_U * SG_WG) {
                     int k[SG_U];
                     IX e[SG_U];
-                    kc = flat_window<SG_U>(st_off, cn, F, tot, kc, widx[wv], k);
+                    kc = flat_window<SG_U>(st_off, cn, F, tot, kc, wb[wv], k);
 #pragma unroll
                     for (int u = 0; u < SG_U; ++u) {
                         const int f = F + u * WAVE + l;

@@ -26,15 +26,15 @@ constexpr int SH_U = 8;  // words per lane and round
 __host__ __device__ constexpr size_t align_up16(size_t x) { return (x + 15) & ~size_t(15); }
 
 struct ShLayout {
-    size_t bits, rel, off, wi, red, total;
+    size_t bits, rel, off, wb, red, total;
 };
 __host__ __device__ inline ShLayout sh_layout(int nw_max, int wg, int ix_bytes) {
     ShLayout L{};
     size_t o = 0;
     L.bits = o;
     o += align_up16(4 * (size_t)nw_max);
-    L.wi = o;
-    o += 2 * (size_t)SH_U * wg;
+    L.wb = o;
+    o += 8 * (size_t)SH_U * (wg / WAVE);
     L.red = o;
     o += 8 * (size_t)(wg / WAVE + 2);
     L.rel = o;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(WG) void k_sym_dg(SymArgs a) {
     int *off = (int *)(smem + L.off);
     long long *red = (long long *)(smem + L.red);
     const int t = threadIdx.x, l = lane_id(), wv = read_first(t / WAVE);
-    uint16_t *wi = (uint16_t *)(smem + L.wi) + wv * (SH_U * WAVE);
+    uint32_t *wb = (uint32_t *)(smem + L.wb) + wv * (2 * SH_U);
     for (int w = t; w < a.nw_max; w += WG) bits[w] = 0;
     int64_t lo, hi;
     rs_bounds(a.rs, lo, hi);
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(WG) void k_sym_dg(SymArgs a) {
             int kc = 0;
             for (int F = wv * (SH_U * WAVE); F < tot; F += SH_U * WG) {
                 int k[SH_U];
-                kc = flat_window<SH_U>(off, cn, F, tot, kc, wi, k);
+                kc = flat_window<SH_U>(off, cn, F, tot, kc, wb, k);
                 uint32_t d[SH_U], cs[SH_U];
                 IX e[SH_U];
 #pragma unroll
