@@ -365,8 +365,8 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
                 if (p < f) {
                     Term s;
                     s.add(val[p]);
-                    a.cci[ob + p] = key[p];
-                    a.cval[ob + p] = s.fin();
+                    store_c(&a.cci[ob + p], key[p]);
+                    store_c(&a.cval[ob + p], s.fin());
                 }
             }
         } else {
@@ -400,8 +400,8 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
                         do s.add(val[p]);
                         while (++p < f && key[p] == kc[u]);
                         const int64_t o = ob + base + mbcnt(head[u]);
-                        a.cci[o] = kc[u];
-                        a.cval[o] = s.fin();
+                        store_c(&a.cci[o], kc[u]);
+                        store_c(&a.cval[o], s.fin());
                     }
                     base += __popcll(head[u]);
                 }

@@ -94,6 +94,17 @@ constexpr int SG_F = 4096;
 constexpr int SG_CUT = SG_CAP - 32;  // a segment starts at the word holding each multiple of this
 
 // ------------------------------------------------------------ argument blocks
+// Store of an entry of C, streamed past the L2: C is larger than it as a rule,
+// so its lines would only push B's rows out.  27-point A*A on 100^3, FP64: 4.0
+// -> 3.05 GB read beyond the L2, 1468 -> 1420 us; new values on 61^3 307 -> 279;
+// batch of 20 random products 2.11 -> 1.95 ms; R-MAT scale 16 6.64 -> 6.47.  Not
+// in k_sr: short rows are the intermediate of Galerkin products, which the next
+// product reads at once (100^3: 808 us, 824 with streamed stores).
+template <typename T>
+__device__ __forceinline__ void store_c(T *p, T v) {
+    __builtin_nontemporal_store(v, p);
+}
+
 struct RowSet {
     const int32_t *rows;   // permutation of row ids, grouped by kind
     const int64_t *koff;   // koff[kind] .. koff[kind+1] is this kind's slice

@@ -338,8 +338,8 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
         wave_lds_sync();
         if (ok) {  // row p's stores
             for (int t = l; t < rnnz; t += WAVE) {
-                if (!a.values_only) a.cci[ob + t] = colbuf[t];
-                a.cval[ob + t] = A::fin(vals[t]);
+                if (!a.values_only) store_c(&a.cci[ob + t], colbuf[t]);
+                store_c(&a.cval[ob + t], A::fin(vals[t]));
                 vals[t] = A::zero();
             }
         }

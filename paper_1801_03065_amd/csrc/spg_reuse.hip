@@ -284,7 +284,7 @@ __global__ __launch_bounds__(WAVE) void k_map_flat(NumArgs<VT> a) {
         },
         [&](const FlatRow &r) {
             for (int u = l; u < min(r.rn, a.r_max); u += WAVE) {
-                a.cval[r.cb - cbase + u] = Acc::fin(vals[u]);
+                store_c(&a.cval[r.cb - cbase + u], Acc::fin(vals[u]));
                 vals[u] = Acc::zero();
             }
         });
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(WAVE) void k_num_map(NumArgs<VT> a) {
             wave_lds_sync();
         }
         for (int u = t; u < rs; u += T) {
-            a.cval[tr.cb - cbase + u] = Acc::fin(tv[u]);
+            store_c(&a.cval[tr.cb - cbase + u], Acc::fin(tv[u]));
             tv[u] = Acc::zero();
         }
         wave_lds_sync();

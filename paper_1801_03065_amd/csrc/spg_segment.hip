@@ -359,7 +359,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             // the bits and values are cleared for the next segment
             const int64_t o = c0 + p1 - cbase;
             const int cw = min(cnt, SG_CAP);
-            for (int r = t; r < cw; r += SG_WG) a.cval[o + r] = acc2 ? A2::fin(vals2[r]) : A::fin(vals[r]);
+            for (int r = t; r < cw; r += SG_WG) store_c(&a.cval[o + r], acc2 ? A2::fin(vals2[r]) : A::fin(vals[r]));
             __syncthreads();
             int32_t *colbuf = (int32_t *)vals_raw;  // SG_CAP * VB >= 4 * SG_CAP bytes
             for (int w = t; w < span; w += SG_WG) {
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
                 bits[w] = 0;
             }
             __syncthreads();
-            for (int r = t; r < cw; r += SG_WG) a.cci[o + r] = colbuf[r];
+            for (int r = t; r < cw; r += SG_WG) store_c(&a.cci[o + r], colbuf[r]);
             __syncthreads();
             for (int r = t; r < cw; r += SG_WG) {  // all-zero bytes either way
                 if (acc2) vals2[r] = A2::zero();

@@ -344,8 +344,8 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
         if (ok) {
             const int64_t ob = d.cb - cbase;
             for (int t = l; t < rnnz; t += WAVE) {
-                a.cci[ob + t] = colbuf[t];
-                a.cval[ob + t] = A::fin(vals[t]);
+                store_c(&a.cci[ob + t], colbuf[t]);
+                store_c(&a.cval[ob + t], A::fin(vals[t]));
             }
         }
         wave_lds_sync();
