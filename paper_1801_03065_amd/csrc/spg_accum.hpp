@@ -106,4 +106,30 @@ struct Accum<float, ACC_COMP> {
 
 __host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
+// A product as it is kept until its run is summed, and the sum of a run.
+// FP64: the product.  FP32 plain: the product rounded to FP32, FP32 sums.
+// FP32 compensated and FP64-accumulated: the exact product in FP64; the
+// compensated pair takes its FP32 rounding and the error from it.
+template <typename VT, int ACC>
+struct BkTerm {
+    using term_t = typename std::conditional<ACC == ACC_NATIVE, VT, double>::type;
+    static __device__ __forceinline__ term_t term(VT a, VT b) { return (term_t)a * (term_t)b; }
+    term_t s = term_t(0);
+    __device__ __forceinline__ void add(term_t x) { s += x; }
+    __device__ __forceinline__ VT fin() const { return (VT)s; }
+};
+template <>
+struct BkTerm<float, ACC_COMP> {
+    using term_t = double;
+    static __device__ __forceinline__ double term(float a, float b) { return (double)a * (double)b; }
+    float s = 0.0f, c = 0.0f;
+    __device__ __forceinline__ void add(double p) {
+        const float x = (float)p, ex = (float)(p - (double)x);  // p == x + ex exactly
+        const float s2 = s + x, bv = s2 - s;                     // TwoSum(s, x)
+        c += ((s - (s2 - bv)) + (x - bv)) + ex;
+        s = s2;
+    }
+    __device__ __forceinline__ float fin() const { return s + c; }
+};
+
 }  // namespace spg

@@ -1279,6 +1279,7 @@ static spg_status numeric_impl(spg_handle h, const VT *aval, const VT *bval, int
     na.coff = h->coff.as<int64_t>();
     na.b32 = h->fp.nnzb < (int64_t(1) << 29);
     na.nnzb = h->fp.nnzb;
+    na.ncols = h->fp.k;
     if (h->planned || h->segmented) {
         na.plan_off = h->plan_off.as<int64_t>();
         na.plan = h->plan.as<uint2>();

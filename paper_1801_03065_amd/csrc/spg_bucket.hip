@@ -34,8 +34,6 @@
 // 2.4 to 3.0 TB/s; bound by memory latency at 16 wavefronts per CU (registers).
 // The kernels it replaces there: column hash with its bitonic sort 94 ps, word
 // hash 58, segments 21 (29.3, 14.1 and 1.6 ms; the five launches here 5.6 ms).
-#include <type_traits>
-
 #include "spg_accum.hpp"
 #include "spg_flat.hpp"
 #include "spg_internal.hpp"
@@ -74,32 +72,6 @@ __device__ __forceinline__ int bk_maxscan(int v) {
     v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
     return v;
 }
-
-// A product as it is kept until its run is summed, and the sum of a run.
-// FP64: the product.  FP32 plain: the product rounded to FP32, FP32 sums.
-// FP32 compensated and FP64-accumulated: the exact product in FP64; the
-// compensated pair takes its FP32 rounding and the error from it.
-template <typename VT, int ACC>
-struct BkTerm {
-    using term_t = typename std::conditional<ACC == ACC_NATIVE, VT, double>::type;
-    static __device__ __forceinline__ term_t term(VT a, VT b) { return (term_t)a * (term_t)b; }
-    term_t s = term_t(0);
-    __device__ __forceinline__ void add(term_t x) { s += x; }
-    __device__ __forceinline__ VT fin() const { return (VT)s; }
-};
-template <>
-struct BkTerm<float, ACC_COMP> {
-    using term_t = double;
-    static __device__ __forceinline__ double term(float a, float b) { return (double)a * (double)b; }
-    float s = 0.0f, c = 0.0f;
-    __device__ __forceinline__ void add(double p) {
-        const float x = (float)p, ex = (float)(p - (double)x);  // p == x + ex exactly
-        const float s2 = s + x, bv = s2 - s;                     // TwoSum(s, x)
-        c += ((s - (s2 - bv)) + (x - bv)) + ex;
-        s = s2;
-    }
-    __device__ __forceinline__ float fin() const { return s + c; }
-};
 
 // Hand-over of LDS data between the lanes of the workgroup.  Both forms wait
 // for LDS only, so loads for the next row stay in flight.

@@ -192,6 +192,7 @@ struct NumArgs {
     int64_t nnzb;          // nnz(B): gathers clamp their offsets to its last entry
     const int64_t *map_off;   // reuse: per row, where its products' ranks start in map
     uint16_t *map;            // reuse: rank in C's row per multiplication
+    int64_t ncols;            // columns of B
     int values_only;          // K_PL: C's columns are already in place, write values only
     DevStats *st;
 };

@@ -4,17 +4,23 @@
 // A row whose multiplication count f_m(i) is at most T = 2^lg_t lanes is
 // handled by a team of T lanes, WAVE / T rows at once.  The row's products
 // are spread one per lane (expansion: prefix sum of the B row lengths over
-// the row of A, then each lane finds the A entry that owns its product), and
-// go into a team-private linear-probing hash in LDS keyed by column (LP
-// hashmap, Accumulators subsection: 2T slots, so at most 50% occupancy).
-//   symbolic: row size = number of first insertions.
-//   numeric:  the team compacts its occupied slots, sorts the (column, slot)
-//             pairs with a bitonic network across its lanes and writes the
-//             sorted row.
+// the row of A, then each lane counts the B rows that start up to it).
+//   symbolic: the columns go into a team-private linear-probing hash in LDS
+//             (LP hashmap, Accumulators subsection: 2T slots, so at most 50%
+//             occupancy); row size = number of first insertions.
+//   numeric:  (column, lane) is sorted across the team with a bitonic network
+//             on one 32-bit key; equal columns are neighbours then, in product
+//             order, and the first of each run adds the others' products.
 // The per-row cost of a whole wavefront (stage, scans, summary) is what this
 // avoids: for rows of a few dozen multiplications it dominates.  Like the
 // wavefront kernels, the loop is software-pipelined across rows: the next
 // row's A entries and B extents load while the current row is processed.
+//
+// Bound by random lines of B past the L2 where B is large (1.5M rows of 7
+// random entries: symbolic 5.2 TB/s), else by latency.  Numeric, the same
+// product: 1032 us with a hash of the products, sorted (column, slot) pairs
+// after it; 665 us now.  Galerkin products on 100^3, both: 394 -> 343 us; 7-point
+// 100^3: 699 -> 606 us.  (Symbolic, sorting took 428 us and the hash 379.)
 #include "spg_accum.hpp"
 #include "spg_internal.hpp"
 
@@ -41,23 +47,6 @@ struct SrArgs {
     DevStats *st;
 };
 
-// Slot of column c in a table of 2^lg slots (Fibonacci hash of the low 24 bits).
-__device__ __forceinline__ uint32_t sr_hash(int c, int lg) {
-    return (__umul24((uint32_t)c & 0xFFFFFFu, 0x9E3779u) >> (24 - lg)) & ((1u << lg) - 1u);
-}
-
-// The same with max (values >= 0 after the first step; lanes without a
-// source read 0).
-template <int LG>
-__device__ __forceinline__ int team_maxscan(int v, int q) {
-    if (LG >= 1) { const int t = __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false); v = (LG >= 4 || q >= 1) ? max(v, t) : v; }
-    if (LG >= 2) { const int t = __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false); v = (LG >= 4 || q >= 2) ? max(v, t) : v; }
-    if (LG >= 3) { const int t = __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false); v = (LG >= 4 || q >= 4) ? max(v, t) : v; }
-    if (LG >= 4) v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-    if (LG >= 5) v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
-    if (LG >= 6) v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
-    return v;
-}
 // Value of lane (lane ^ J): DPP quad permutes for 1 and 2, a row rotation
 // for 8, swizzles inside 32 lanes for 4 and 16, a lane permute for 32.
 template <int J>
@@ -69,60 +58,89 @@ __device__ __forceinline__ int lane_xor(int v) {
     if (J == 16) return __builtin_amdgcn_ds_swizzle(v, 0x1F | (16 << 10));
     return __shfl_xor(v, J);
 }
+// Slot of column c in a table of 2^lg slots (Fibonacci hash of the low 24 bits).
+__device__ __forceinline__ uint32_t sr_hash(int c, int lg) {
+    return (__umul24((uint32_t)c & 0xFFFFFFu, 0x9E3779u) >> (24 - lg)) & ((1u << lg) - 1u);
+}
 // One compare-exchange step of the bitonic network (block size KK, distance J).
 template <int KK, int J>
-__device__ __forceinline__ void bitonic_step(int &key, int &slot, int q) {
-    const int ok = lane_xor<J>(key), os = lane_xor<J>(slot);
+__device__ __forceinline__ void bitonic_step(uint32_t &key, int q) {
+    const uint32_t ok = (uint32_t)lane_xor<J>((int)key);
     const bool up = (q & KK) == 0, lower = (q & J) == 0;
-    if (lower == up ? ok < key : ok > key) {
-        key = ok;
-        slot = os;
-    }
+    key = lower == up ? min(key, ok) : max(key, ok);
 }
-// Sort (key, slot) ascending inside blocks of P lanes (P <= 2^LG, a power of
-// two, wavefront-uniform): the stages for blocks above P are skipped.
-template <int LG>
-__device__ __forceinline__ void team_sort(int &key, int &slot, int q, int P) {
-#define SR_STAGE(KK, J) \
-    if (KK <= (1 << LG) && KK <= P) bitonic_step<KK, J>(key, slot, q);
+template <int KK, int J>
+__device__ __forceinline__ void bitonic_step(uint64_t &key, int q) {
+    const uint32_t ol = (uint32_t)lane_xor<J>((int)(uint32_t)key), oh = (uint32_t)lane_xor<J>((int)(uint32_t)(key >> 32));
+    const uint64_t ok = (uint64_t)oh << 32 | ol;
+    const bool up = (q & KK) == 0, lower = (q & J) == 0;
+    if (lower == up ? ok < key : ok > key) key = ok;
+}
+// Sort ascending inside blocks of P lanes (P <= 2^LG, a power of two,
+// wavefront-uniform): the stages for blocks above P are skipped.
+template <int LG, typename KEY>
+__device__ __forceinline__ void team_sort(KEY &key, int q, int P) {
+#define SR_STAGE(KK, J) bitonic_step<KK, J>(key, q);
     SR_STAGE(2, 1)
+    if (P < 4) return;
     SR_STAGE(4, 2) SR_STAGE(4, 1)
+    if (P < 8) return;
     SR_STAGE(8, 4) SR_STAGE(8, 2) SR_STAGE(8, 1)
+    if (LG < 4 || P < 16) return;
     SR_STAGE(16, 8) SR_STAGE(16, 4) SR_STAGE(16, 2) SR_STAGE(16, 1)
+    if (LG < 5 || P < 32) return;
     SR_STAGE(32, 16) SR_STAGE(32, 8) SR_STAGE(32, 4) SR_STAGE(32, 2) SR_STAGE(32, 1)
+    if (LG < 6 || P < 64) return;
     SR_STAGE(64, 32) SR_STAGE(64, 16) SR_STAGE(64, 8) SR_STAGE(64, 4) SR_STAGE(64, 2) SR_STAGE(64, 1)
 #undef SR_STAGE
 }
 
-template <bool NUM, typename VT, int ACC, int LG>
+// Largest value (>= 0) of the 64 lanes, uniform.
+__device__ __forceinline__ int sr_wave_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+    return __builtin_amdgcn_readlane(v, WAVE - 1);
+}
+// Value of the team's last lane.
+template <int LG>
+__device__ __forceinline__ int team_last(int v) {
+    if (LG == 6) return __builtin_amdgcn_readlane(v, WAVE - 1);
+    return __shfl(v, (1 << LG) - 1, 1 << LG);
+}
+
+// NUM: values (else the row's distinct columns are counted).  PACK: columns
+// below 2^26 and 32-bit byte offsets into B: (column, lane) fits 32 bits.
+template <bool NUM, typename VT, int ACC, int LG, bool PACK>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sr(SrArgs<VT> a) {
-    using A = Accum<VT, ACC>;
-    using S = typename A::store_t;
-    __shared__ int32_t keys_all[2 * WAVE];
-    __shared__ S vals_all[NUM ? 2 * WAVE : 1];
-    __shared__ int32_t own_all[WAVE];
-    __shared__ int32_t uslot_all[NUM ? WAVE : 1];
+    using Term = BkTerm<VT, ACC>;
+    using P = typename Term::term_t;
+    using IX = typename std::conditional<PACK, int32_t, int64_t>::type;
+    using KEY = typename std::conditional<PACK, uint32_t, uint64_t>::type;  // column, lane
+    __shared__ __align__(8) uint32_t starts[2];  // wavefront lanes where a B row's products start
+    __shared__ IX rel[WAVE];                     // per nonempty B row: its start less its first product's lane
+    __shared__ VT sav[NUM ? WAVE : 1];
+    __shared__ P vals[NUM ? WAVE : 1];
+    __shared__ int32_t keys[NUM ? 1 : 2 * WAVE];  // hash of 2T slots per team
     const int l = lane_id();
-    constexpr int lgT = LG, T = 1 << LG;
-    const int q = l & (T - 1), team = l >> lgT;
+    constexpr int T = 1 << LG;
+    const int q = l & (T - 1), team = l >> LG;
     constexpr int nteam = WAVE >> LG;
-    int32_t *keys = keys_all + 2 * T * team;
-    S *vals = vals_all + (NUM ? 2 * T * team : 0);
-    int32_t *own = own_all + T * team;
-    int32_t *uslot = uslot_all + (NUM ? T * team : 0);
-    keys_all[l] = -1;
-    keys_all[l + WAVE] = -1;
-    if (NUM) {
-        vals_all[l] = A::zero();
-        vals_all[l + WAVE] = A::zero();
+    const unsigned long long below = team ? (1ull << (team * T)) - 1 : 0ull;  // lanes of the teams before
+    const unsigned long long mine_m = (T == 64 ? ~0ull : ((1ull << (T & 63)) - 1) << (team * T & 63));
+    if (!NUM) {
+        keys[l] = -1;
+        keys[l + WAVE] = -1;
+        wave_lds_sync();
     }
-    wave_lds_sync();
     int64_t lo, hi;
     rs_bounds(a.rs, lo, hi);
     const int64_t ngroups = (hi - lo + nteam - 1) / nteam;
     const Slice sl = xcd_slice(0, ngroups);
     const int64_t cbase = (NUM && a.cbase_row >= 0) ? a.coff[a.cbase_row] : 0;
-    const uint32_t tmask = 2u * T - 1u;
 
     // this team's row in group gg, or -1
     auto row_of = [&](int64_t gg) -> int {
@@ -166,111 +184,125 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
             cb = a.coff[ic];
             ce = a.coff[ic + 1];
         }
-        // ---- expansion + insertion, T A entries at a time (team-uniform loop)
-        int nins = 0;
-        for (int64_t c0 = abc; c0 < aec; c0 += T) {
-            int j = jc, len = lenc;
-            int64_t b0 = b0c;
-            VT av = avc;
-            if (c0 != abc) {
-                j = 0;
-                len = 0;
-                b0 = 0;
-                av = VT(0);
-                if (c0 + q < aec) {
-                    j = a.aci[c0 + q];
-                    if (NUM) av = a.aval[c0 + q];
-                    b0 = a.brp[j];
-                    len = (int)(a.brp[j + 1] - b0);
-                }
-            }
+        // ---- one product per lane
+        IX e = 0;
+        VT avk = avc;
+        bool mine;
+        int F, span;  // the team's products; lanes they lie in
+        const bool more = __ballot(aec - abc > T) != 0;  // A rows with empty B rows, in chunks of T entries
+        if (!more && __ballot(lenc > 1) == 0) {
             // B rows of at most one entry (every A entry makes at most one
             // product, e.g. aggregation or injection operators): each lane
             // forms its own product, no expansion
-            const bool unit = __ballot(len > 1) == 0;
-            int64_t e = b0;
-            VT avk = av;
-            bool mine = len > 0;
-            if (!unit) {
-                const int inc = team_scan<LG>(len, q);
-                const int F = __shfl(inc, T - 1, T);  // products of this chunk (<= T for a short row)
-                const int off = inc - len;
-                own[q] = -1;
+            e = (IX)b0c;
+            mine = lenc > 0;
+            F = __popcll(__ballot(mine) & mine_m);
+            span = (int)(aec - abc);
+        } else {
+            F = 0;
+            mine = false;
+            int len = lenc;
+            int64_t b0 = b0c;
+            VT av = avc;
+            for (int64_t c0 = 0;;) {  // the same number of chunks in every team
+                const int inc = team_scan<LG>(len, q), off = F + inc - len;
+                const int Fc = team_last<LG>(inc);
+                const unsigned long long runs = __ballot(len > 0 && off < T);
+                if (l < 2) starts[l] = 0u;
                 wave_lds_sync();
-                if (len > 0 && off < T) own[off] = q;
-                wave_lds_sync();
-                // owner of product q: the last A entry starting at or before q
-                const int k = max(team_maxscan<LG>(own[q], q), 0);
-                const int offk = __shfl(off, k, T);
-                const int64_t b0k = __shfl(b0, k, T);
-                if (NUM) avk = __shfl(av, k, T);
-                if (q == 0 && F > T) atomicAdd(&a.st->mismatch, 1);  // not a short row: plan inconsistent
-                e = b0k + (q - offk);
-                mine = q < F;
-            }
-            if (mine) {
-                const int col = a.bci[e];
-                VT bv = VT(0);
-                if (NUM) bv = a.bval[e];
-                uint32_t h = sr_hash(col, lgT + 1);
-                for (;;) {
-                    const int32_t old = atomicCAS(&keys[h], -1, col);
-                    if (old == -1) {
-                        ++nins;
-                        break;
-                    }
-                    if (old == col) break;
-                    h = (h + 1) & tmask;
+                if (len > 0 && off < T) {
+                    const int at = team * T + off, run = mbcnt(runs);
+                    atomicOr(&starts[at >> 5], 1u << (at & 31));
+                    rel[run] = (IX)(b0 - at);
+                    if (NUM) sav[run] = av;
                 }
-                if (NUM) A::add(&vals[h], avk, bv);
+                wave_lds_sync();
+                const uint32_t s0 = read_first((int)starts[0]), s1 = read_first((int)starts[1]);
+                // a lane's run: the starts up to it, less one
+                const int k = __builtin_amdgcn_mbcnt_hi(s1 >> 1, __builtin_amdgcn_mbcnt_lo(s0 >> 1 | s1 << 31, (s0 & 1) - 1));
+                if (q >= F && q < F + Fc) {
+                    e = rel[max(k, 0)] + l;
+                    if (NUM) avk = sav[max(k, 0)];
+                    mine = true;
+                }
+                F += Fc;
+                c0 += T;
+                if (!more || __ballot(abc + c0 < aec) == 0) break;
+                len = 0;
+                if (abc + c0 + q < aec) {
+                    const int j = a.aci[abc + c0 + q];
+                    if (NUM) av = a.aval[abc + c0 + q];
+                    b0 = a.brp[j];
+                    len = (int)(a.brp[j + 1] - b0);
+                }
+                wave_lds_sync();
             }
-            wave_lds_sync();
+            if (q == 0 && F > T) atomicAdd(&a.st->mismatch, 1);  // not a short row: plan inconsistent
+            F = min(F, T);
+            span = F;
         }
-        const int cnt = __shfl(team_scan<LG>(nins, q), T - 1, T);
-
-        if (!NUM) {
+        if constexpr (!NUM) {  // distinct columns: first insertions
+            int fresh = 0;
+            if (mine) {
+                const int col = PACK ? ld32(a.bci, (uint32_t)e) : a.bci[e];
+                uint32_t h = sr_hash(col, LG + 1);
+                for (;;) {
+                    const int old = atomicCAS(&keys[2 * T * team + h], -1, col);
+                    fresh = old == -1;
+                    if (fresh || old == col) break;
+                    h = (h + 1) & (2u * T - 1u);
+                }
+            }
+            const int cnt = __popcll(__ballot(fresh) & mine_m);
             if (q == 0 && ic >= 0) {
                 a.row_nnz[ic] = cnt;
                 a.row_words[ic] = cnt;
             }
-            keys[q] = -1;
-            keys[q + T] = -1;
-        } else {
-            // ---- compact the occupied slots, sort by column, write the row
-            const int k0 = keys[q], k1 = keys[q + T];
-            const int c = (k0 >= 0) + (k1 >= 0);
-            int p = team_scan<LG>(c, q) - c;
-            if (k0 >= 0) {
-                own[p] = k0;
-                uslot[p] = q;
-                ++p;
-            }
-            if (k1 >= 0) {
-                own[p] = k1;
-                uslot[p] = q + T;
-            }
             wave_lds_sync();
-            int key = q < cnt ? own[q] : INT_MAX;
-            int slot = q < cnt ? uslot[q] : 0;
-            // bitonic sort of (key, slot) across the team, ascending, over the
-            // next power of two of the wavefront's largest row
-            int P = 2;
-            {
-                const int mc = __builtin_amdgcn_readfirstlane(wave_max(cnt));
-                while (P < mc) P <<= 1;
+            keys[l] = -1;
+            keys[l + WAVE] = -1;
+        } else {
+            KEY key = ~(KEY)0;
+            if (mine) {
+                const int col = PACK ? ld32(a.bci, (uint32_t)e) : a.bci[e];
+                const VT bv = PACK ? ld32(a.bval, (uint32_t)e) : a.bval[e];
+                vals[l] = Term::term(avk, bv);
+                key = (KEY)(uint32_t)col << 6 | l;
             }
-            team_sort<LG>(key, slot, q, P);
+            // ---- sorted by column over the next power of two of the wavefront's
+            // largest row; equal columns are neighbours then, in product order
+            {
+                const int mc = LG == 6 ? read_first(span) : sr_wave_max(span);
+                int p2 = 2;
+                while (p2 < mc) p2 <<= 1;
+                team_sort<LG>(key, q, p2);
+            }
+            const int col = (int)(uint32_t)(key >> 6);
+            const int pcol = __shfl_up(col, 1);
+            const bool head = q < F && (q == 0 || col != pcol);
+            const unsigned long long hm = __ballot(head);
+            const int cnt = __popcll(hm & mine_m);
+            wave_lds_sync();
+            const P v = vals[(uint32_t)key & 63u];
+            Term s;
+            s.add(v);
+            if (__ballot(q < F && !head)) {  // repeated columns: a head adds the products up to the next one
+                wave_lds_sync();
+                vals[l] = v;
+                wave_lds_sync();
+                const unsigned long long rest = hm >> l >> 1;
+                const int next = min(rest ? l + 1 + (__ffsll((long long)rest) - 1) : WAVE, team * T + F);
+                const int run = head ? next - l : 0, longest = sr_wave_max(run);
+                for (int x = 1; x < longest; ++x)
+                    if (x < run) s.add(vals[l + x]);
+            }
             const bool okrow = ic < 0 || ce - cb == cnt;
             if (q == 0 && !okrow) atomicAdd(&a.st->mismatch, 1);
-            if (okrow && q < cnt) {
-                a.cci[cb - cbase + q] = key;
-                a.cval[cb - cbase + q] = A::fin(vals[slot]);
+            if (okrow && head) {
+                const int64_t o = cb - cbase + (mbcnt(hm) - __popcll(hm & below));
+                a.cci[o] = col;
+                a.cval[o] = s.fin();
             }
-            wave_lds_sync();
-            keys[q] = -1;
-            keys[q + T] = -1;
-            vals[q] = A::zero();
-            vals[q + T] = A::zero();
         }
         // next row, second level: B extents of its first chunk
         int64_t b0n = 0;
@@ -313,11 +345,15 @@ int sr_grid(K kernel, int cus, int64_t groups) {
     return (int)(g < XCDS ? XCDS : g);
 }
 
-template <typename VT, int ACC, int LG>
-hipError_t num_sr_lg(const SrArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
-    const int grid = c.grid > 0 ? c.grid : sr_grid(k_sr<true, VT, ACC, LG>, c.cus, rows >> (6 - LG));
-    hipLaunchKernelGGL((k_sr<true, VT, ACC, LG>), dim3(grid), dim3(WAVE), 0, c.stream, a);
+template <bool NUM, typename VT, int ACC, int LG, bool PACK>
+hipError_t sr_pack(const SrArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
+    const int grid = c.grid > 0 ? c.grid : sr_grid(k_sr<NUM, VT, ACC, LG, PACK>, c.cus, rows >> (6 - LG));
+    hipLaunchKernelGGL((k_sr<NUM, VT, ACC, LG, PACK>), dim3(grid), dim3(WAVE), 0, c.stream, a);
     return hipGetLastError();
+}
+template <typename VT, int ACC, int LG>
+hipError_t num_sr_lg(const SrArgs<VT> &a, bool pack, const LaunchCfg &c, int64_t rows) {
+    return pack ? sr_pack<true, VT, ACC, LG, true>(a, c, rows) : sr_pack<true, VT, ACC, LG, false>(a, c, rows);
 }
 
 template <typename VT, int ACC>
@@ -336,17 +372,17 @@ hipError_t num_sr_impl(const NumArgs<VT> &n, int lg_t, const LaunchCfg &c, int64
     a.rs = n.rs;
     a.lg_t = lg_t;
     a.st = n.st;
-    if (lg_t <= 3) return num_sr_lg<VT, ACC, 3>(a, c, rows);
-    if (lg_t == 4) return num_sr_lg<VT, ACC, 4>(a, c, rows);
-    if (lg_t == 5) return num_sr_lg<VT, ACC, 5>(a, c, rows);
-    return num_sr_lg<VT, ACC, 6>(a, c, rows);
+    const bool pack = n.b32 && n.ncols <= (int64_t(1) << 26);
+    if (lg_t <= 3) return num_sr_lg<VT, ACC, 3>(a, pack, c, rows);
+    if (lg_t == 4) return num_sr_lg<VT, ACC, 4>(a, pack, c, rows);
+    if (lg_t == 5) return num_sr_lg<VT, ACC, 5>(a, pack, c, rows);
+    return num_sr_lg<VT, ACC, 6>(a, pack, c, rows);
 }
 
 template <int LG>
-hipError_t sym_sr_lg(const SrArgs<double> &a, const LaunchCfg &c, int64_t rows) {
-    const int grid = c.grid > 0 ? c.grid : sr_grid(k_sr<false, double, ACC_NATIVE, LG>, c.cus, rows >> (6 - LG));
-    hipLaunchKernelGGL((k_sr<false, double, ACC_NATIVE, LG>), dim3(grid), dim3(WAVE), 0, c.stream, a);
-    return hipGetLastError();
+hipError_t sym_sr_lg(const SrArgs<double> &a, bool b32, const LaunchCfg &c, int64_t rows) {
+    return b32 ? sr_pack<false, double, ACC_NATIVE, LG, true>(a, c, rows)
+               : sr_pack<false, double, ACC_NATIVE, LG, false>(a, c, rows);
 }
 
 }  // namespace
@@ -364,10 +400,10 @@ hipError_t launch_sym_sr(const SymArgs &s, int lg_t, const LaunchCfg &c, int64_t
     a.lg_t = lg_t;
     a.st = s.st;
     a.cbase_row = -1;
-    if (lg_t <= 3) return sym_sr_lg<3>(a, c, rows);
-    if (lg_t == 4) return sym_sr_lg<4>(a, c, rows);
-    if (lg_t == 5) return sym_sr_lg<5>(a, c, rows);
-    return sym_sr_lg<6>(a, c, rows);
+    if (lg_t <= 3) return sym_sr_lg<3>(a, s.b32, c, rows);
+    if (lg_t == 4) return sym_sr_lg<4>(a, s.b32, c, rows);
+    if (lg_t == 5) return sym_sr_lg<5>(a, s.b32, c, rows);
+    return sym_sr_lg<6>(a, s.b32, c, rows);
 }
 
 template <>
