@@ -95,25 +95,39 @@ __device__ __forceinline__ int64_t sg_lower_bound(const int32_t *bci, int64_t lo
 }
 
 // First index in [lo, hi) whose column is >= key, searched from lo (the run
-// is usually short): the row's end first, then probes at lo + 1, 3, 7, ...
-// and a binary search in the last gap.
+// is usually short): four entries in one load, which the products then find in
+// the cache; beyond them jumps of 4, 8, 16, ... and a binary search in the last
+// one.  (Testing the row's last entry first cost a line of its own per A entry
+// and segment: R-MAT scale 17 18.46 -> 18.22 ms, scale 15, FP32 numeric, 1.73 ->
+// 1.69.)
 __device__ __forceinline__ int64_t sg_gallop(const int32_t *bci, int64_t lo, int64_t hi, int64_t key) {
-    if (lo >= hi) return lo;
-    const int32_t first = bci[lo], last = bci[hi - 1];
-    if ((int64_t)first >= key) return lo;
-    if ((int64_t)last < key) return hi;
-    int64_t below = lo, step = 1;  // bci[below] < key, bci[hi - 1] >= key
-    while (below + step < hi - 1 && (int64_t)bci[below + step] < key) {
-        below += step;
-        step <<= 1;
+    if (hi - lo > 4) {
+        struct Four {
+            int32_t a, b, c, d;
+        };
+        const Four q = *(const Four *)&bci[lo];
+        const int r = (q.a < key) + (q.b < key) + (q.c < key) + (q.d < key);
+        if (r < 4) return lo + r;
+        lo += 4;
+        int64_t step = 4;
+        for (; lo + step < hi; step <<= 1) {
+            if ((int64_t)bci[lo + step - 1] >= key) {
+                hi = lo + step - 1;
+                break;
+            }
+            lo += step;
+        }
+        while (hi - lo > 4) {
+            const int64_t mid = lo + ((hi - lo) >> 1);
+            if ((int64_t)bci[mid] < key) lo = mid + 1;
+            else hi = mid;
+        }
     }
-    int64_t a = below + 1, b = min(below + step, hi - 1);  // answer in [a, b]
-    while (a < b) {
-        const int64_t mid = a + ((b - a) >> 1);
-        if ((int64_t)bci[mid] < key) a = mid + 1;
-        else b = mid;
-    }
-    return a;
+    int r = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (lo + k < hi) r += (int64_t)bci[lo + k] < key;
+    return lo + r;
 }
 
 // ACC accumulates the rows of a.rs, ACC2 those of a.rs2 (FP32 values: the
@@ -221,7 +235,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
                 VT av = VT(0);
                 if (one_chunk) {
                     s0 = cur;
-                    if (ab + t < ae) s1 = single ? bend : sg_gallop(a.bci, cur, bend, col_hi);
+                    if (ab + t < ae) s1 = sg + 1 == nseg ? bend : sg_gallop(a.bci, cur, bend, col_hi);
                     else s1 = s0;
                     cur = s1;
                     av = av1;
@@ -230,7 +244,8 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
                     if (cur_g) {
                         s0 = cur_g[k];
                         if (first) {
-                            s1 = sg_gallop(a.bci, s0, (int64_t)end_g[k], col_hi);
+                            s1 = end_g[k];
+                            if (sg + 1 < nseg) s1 = sg_gallop(a.bci, s0, s1, col_hi);
                             if (!last) nxt_g[k] = (int32_t)s1;
                         } else {
                             s1 = nxt_g[k];
