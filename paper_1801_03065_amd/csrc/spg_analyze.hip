@@ -811,13 +811,18 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                 default:  // selector
                     if (f <= p.sr_f_max)
                         k = K_SR;
-                    // Scattered rows: as many window words as multiplications
+                    // Scattered rows: half as many window words as products
                     // and B rows that compression does not shorten, so few
                     // products meet and a hash of the products is smaller
-                    // than the window (measured at k_sym_bk).  Rows of a few
-                    // more multiplications than PL_CAP may store their
-                    // structure: they keep the bit window where it fits.
-                    else if (p.phase == 0 && p.bk && f <= BK_F_MAX && nw >= f && (!dw_fit || 2 * f > 3 * PL_CAP) &&
+                    // than the window (measured at k_sym_bk).  Rows that may
+                    // store their structure keep the bit window where it fits:
+                    // f products in nw words touch about f - f^2 / (2 nw), and
+                    // above PL_CAP + 2 few rows do.  (Batch of 48, with as many
+                    // words as products and up to 96 products in windows: 8.83
+                    // ms; 8.53 now.  At three products a word the window wins
+                    // again: 10000 rows of 900 products, 240 against 248 us.)
+                    else if (p.phase == 0 && p.bk && f <= BK_F_MAX && 2 * nw >= f &&
+                             (!dw_fit || 2 * nw * (f - PL_CAP - 2) > f * f) &&
                              (double)fc_[h] >= 0.85 * (double)f && al_[h] <= WAVE) {
                         k = K_BK0;
                         for (long long top = BK_F0; top < f; top <<= 1) ++k;
