@@ -585,7 +585,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         }
         const int64_t rows_dg = hs2.kcount_sym[K_DG], nw_dg = hs2.kmax_sym[K_DG][0];
         const int64_t eb = std::min<int64_t>((int64_t)hs1.maxrf, 32 * nw_dg);
-        plan_room = (int64_t)PL_CAP * hs2.kcount_sym[K_DW] +
+        plan_room = (pairs_used ? (int64_t)PL_CAP * hs2.kcount_sym[K_DW] : 0) +
                     (rows_dg > 0 ? rows_dg * ((eb + SG_CUT - 1) / SG_CUT + (nw_dg + SG_NW - 1) / SG_NW + 2) : 0);
         sgb_words = segs_used ? rows_dg * nw_dg : 0;
         if (plan_room > (int64_t(1) << 27) || sgb_words > SGB_BOUND) {
