@@ -332,7 +332,8 @@ __global__ __launch_bounds__(WAVE) void k_posmap_flat(NumArgs<double> a, const i
         [](const FlatRow &) {});
 }
 
-// The same for short rows, in teams.
+// The same for short rows, in teams.  Their values are stored through the L2,
+// whose lines several rows share (8 entries a row: 235 us, 247 streamed).
 template <typename VT, int ACC, int LGT, int LGS>
 __global__ __launch_bounds__(WAVE) void k_num_map(NumArgs<VT> a) {
     using Acc = Accum<VT, ACC>;
@@ -374,7 +375,7 @@ __global__ __launch_bounds__(WAVE) void k_num_map(NumArgs<VT> a) {
             wave_lds_sync();
         }
         for (int u = t; u < rs; u += T) {
-            store_c(&a.cval[tr.cb - cbase + u], Acc::fin(tv[u]));
+            a.cval[tr.cb - cbase + u] = Acc::fin(tv[u]);
             tv[u] = Acc::zero();
         }
         wave_lds_sync();
@@ -458,12 +459,16 @@ hipError_t map_flat_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
 
 // Products per lane and round by the largest kind of the launch: most rows then
 // take one or two rounds (20000 rows of 100 to 150 products, FP64: 49.5 us a
-// call with 4, 52 with 2 or 8).  32-bit product numbers where 64 A entries cannot form 2^31 products.
+// call with 4, 52 with 2 or 8; 125,000 rows of 62: 52 us with 1, 59 with 2, 53 in
+// teams of 64 lanes).  32-bit product numbers where 64 A entries cannot form
+// 2^31 products.
 template <typename VT, int ACC>
 hipError_t map_flat(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
     const int last = a.rs.kind + a.rs.more;
     const bool i32 = a.nnzb * WAVE < (int64_t(1) << 31);
-    if (last == K_SR || last == K_BK0)
+    if (last == K_SR)
+        return i32 ? map_flat_u<VT, ACC, int32_t, 1>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 1>(a, c, rows);
+    if (last == K_BK0)
         return i32 ? map_flat_u<VT, ACC, int32_t, 2>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 2>(a, c, rows);
     if (last == K_BK1 || last == K_BK2)
         return i32 ? map_flat_u<VT, ACC, int32_t, 4>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 4>(a, c, rows);
