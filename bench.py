@@ -44,9 +44,9 @@ TRAFFIC = {
     "kernel": "k_num_pl",
     "sources": ["paper_1801_03065_amd/csrc/spg_plan.hip", "paper_1801_03065_amd/csrc/spg_internal.hpp",
                 "paper_1801_03065_amd/csrc/spg_accum.hpp"],
-    "sha256": "4c45b3afc98c22126d6833664bd1d6381f35cb2efb3f81e45ebc5e462adf7e84",
-    "read_bytes": 3.7433e9,
-    "write_bytes": 1.5278e9,
+    "sha256": "0fc7a483c711c2286daf4a0ea000391e239238808946d52be99b62720cfd55d4",
+    "read_bytes": 2.8686e9,
+    "write_bytes": 1.6062e9,
 }
 
 
