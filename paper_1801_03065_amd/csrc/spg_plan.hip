@@ -25,7 +25,9 @@ namespace spg {
 namespace {
 
 constexpr int PL_U = 16;  // products per lane held in registers (fast path)
-constexpr int PL_CH = 4;  // consecutive rows per chunk of a wavefront's rows
+// FP64 entries of B from which a wavefront takes its rows in chunks of four
+// (see k_num_pl): its 12-byte entries then exceed 200 MB.
+constexpr int64_t PL_CH_NNZ = int64_t(1) << 24;
 
 // Staged A entry: one 16-byte LDS record, so a product reads its A value and
 // its B row's length (which masks the lanes past the row) in one LDS read,
@@ -77,7 +79,7 @@ struct RowDescP {
 // so the staging offsets of a lane's products are immediates; NU products per
 // lane cover the fast path (NU * NG >= 64 or NU = PL_U), and every staged
 // index g + u * NG stays below 64.
-template <typename VT, int ACC, int LGS>
+template <typename VT, int ACC, int LGS, int CH>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_num_pl(NumArgs<VT> a) {
     using A = Accum<VT, ACC>;
     using S = typename A::store_t;
@@ -95,12 +97,15 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     int64_t lo, hi;
     rs_bounds(a.rs, lo, hi);
     const int64_t cbase = a.cbase_row >= 0 ? a.coff[a.cbase_row] : 0;
-    // The wavefront takes its die's rows in chunks of PL_CH consecutive rows,
-    // chunk after chunk at the stride of all the die's wavefronts: neighbouring
-    // rows of C share most of their B rows (a stencil's rows i and i+1 share
-    // two thirds), so a chunk finds them in the CU's L1 and the die's L2
-    // (27-point A*A on 100^3: 44% less traffic beyond L2 than row by row).
-    const Slice sl = xcd_slice(lo, hi, PL_CH, 0);
+    // The wavefront takes its die's rows in chunks of CH consecutive rows, chunk
+    // after chunk at the stride of all the die's wavefronts.  Neighbouring rows
+    // of C share most of their B rows (a stencil's rows i and i+1 share two
+    // thirds), so chunks of four cut the traffic beyond the L2 (27-point A*A on
+    // 100^3: by 44% before C was streamed past it) but let the wavefronts of a
+    // die drift apart and leave some idle in small launches.  Measured, chunks
+    // of 4 / single rows: FP64 100^3 1409 / 1420 us, 61^3 301 / 292, 20^3 36 / 32;
+    // FP32 100^3 1410 / 1361, 61^3 340 / 321.
+    const Slice sl = xcd_slice(lo, hi, CH, 0);
 
     // Software pipeline over the wavefront's rows p, p+s, p+2s, ... (p+s: the
     // next row of its sequence, pos(t + 1)): while row p is processed, row
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     };
     const int64_t step = sl.step;
     const int64_t p0 = sl.idx, pend = sl.end;
-    auto pos = [&](int64_t t) -> int64_t { return p0 + (t / PL_CH) * step + (t % PL_CH); };  // t-th row
+    auto pos = [&](int64_t t) -> int64_t { return p0 + (t / CH) * step + (t % CH); };  // t-th row
     auto row_at = [&](int64_t pp) -> int { return pp < pend ? read_first(a.rs.rows[pp]) : 0; };
 
     // ---- prologue: fill the pipeline (waits here are once per kernel).
@@ -379,12 +384,19 @@ inline int resident_grid(K kernel, int block, size_t lds, int cus) {
     return g < XCDS ? XCDS : g;
 }
 
+template <typename VT, int ACC, int LGS, int CH>
+hipError_t num_pl_ch(const NumArgs<VT> &a, const LaunchCfg &c) {
+    const size_t lds = lds_num_pl(a.nw_max, a.r_max, sizeof(typename Accum<VT, ACC>::store_t));
+    const int grid = c.grid > 0 ? c.grid : resident_grid(k_num_pl<VT, ACC, LGS, CH>, WAVE, lds, c.cus);
+    hipLaunchKernelGGL((k_num_pl<VT, ACC, LGS, CH>), dim3(grid), dim3(WAVE), lds, c.stream, a);
+    return hipGetLastError();
+}
+
 template <typename VT, int ACC, int LGS>
 hipError_t num_pl_lg(const NumArgs<VT> &a, const LaunchCfg &c) {
-    const size_t lds = lds_num_pl(a.nw_max, a.r_max, sizeof(typename Accum<VT, ACC>::store_t));
-    const int grid = c.grid > 0 ? c.grid : resident_grid(k_num_pl<VT, ACC, LGS>, WAVE, lds, c.cus);
-    hipLaunchKernelGGL((k_num_pl<VT, ACC, LGS>), dim3(grid), dim3(WAVE), lds, c.stream, a);
-    return hipGetLastError();
+    if constexpr (sizeof(VT) == 8)
+        if (a.nnzb >= PL_CH_NNZ) return num_pl_ch<VT, ACC, LGS, 4>(a, c);
+    return num_pl_ch<VT, ACC, LGS, 1>(a, c);
 }
 
 template <typename VT, int ACC>
