@@ -44,9 +44,9 @@ TRAFFIC = {
     "kernel": "k_num_pl",
     "sources": ["paper_1801_03065_amd/csrc/spg_plan.hip", "paper_1801_03065_amd/csrc/spg_internal.hpp",
                 "paper_1801_03065_amd/csrc/spg_accum.hpp"],
-    "sha256": "0fc7a483c711c2286daf4a0ea000391e239238808946d52be99b62720cfd55d4",
-    "read_bytes": 2.8686e9,
-    "write_bytes": 1.6062e9,
+    "sha256": "b2da5714b7c246fdd93305f944677305a793844120bf9e16e494bfa975a8c55c",
+    "read_bytes": 2.8459e9,
+    "write_bytes": 1.6061e9,
 }
 
 
