@@ -837,7 +837,7 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
                     // to entries, tables, sorts or segments.  Above two
                     // products per entry the buckets fill with repeats and the
                     // accumulators win.  Batch of 48 (400 products a row), FP64
-                    // numeric: the others 45.0 ms, buckets 5.6 ms.
+                    // numeric: the others 45.0 ms, buckets 5.0 ms.
                     else if (p.bk && f <= BK_F_MAX && f <= 2 * bound && al_[h] <= WAVE) {
                         k = K_BK0;
                         for (long long top = BK_F0; top < f; top <<= 1) ++k;

@@ -14,7 +14,7 @@
 // searches in flight: U searches per lane advance together, and LDS is sized
 // by the longest row of C, so short rows leave room for 32 wavefronts per CU.
 // Backward of 7-point 64^3 times 16 random columns a row (2.9e7
-// multiplications, FP32): 283 us; with lane groups per B row, one search at a
+// multiplications, FP32): 273 us; with lane groups per B row, one search at a
 // time and 16 KB of LDS per wavefront it took 1050 us.  (Sums over a run by LDS
 // atomics would cost 190 cycles per 64 products: the lanes of a run share
 // one address.)

@@ -33,7 +33,7 @@
 // in and out): 8.1 to 10.0 ps a product over rows of 65 to 2048 products,
 // 2.4 to 3.0 TB/s; bound by memory latency at 16 wavefronts per CU (registers).
 // The kernels it replaces there: column hash with its bitonic sort 94 ps, word
-// hash 58, segments 21 (29.3, 14.1 and 1.6 ms; the five launches here 5.6 ms).
+// hash 58, segments 21 (29.3, 14.1 and 1.6 ms; the five launches here 5.0 ms).
 #include "spg_accum.hpp"
 #include "spg_flat.hpp"
 #include "spg_internal.hpp"

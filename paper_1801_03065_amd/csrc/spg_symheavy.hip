@@ -11,7 +11,7 @@
 // heavy rows' structure the words themselves are stored.
 //
 // Bound by latency and by the LDS (counting, conflicting ORs).  R-MAT scale 17
-// squared (1.5e9 compressed multiplications in 75k rows): 3.25 ms; with a
+// squared (1.5e9 compressed multiplications in 75k rows): 3.13 ms; with a
 // binary search per word and a second OR into a summary word (which every 32nd
 // word shares) it took 9.5 ms.
 #include "spg_flat.hpp"
