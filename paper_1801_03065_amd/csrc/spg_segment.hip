@@ -16,7 +16,8 @@
 //      nonempty runs are staged back to back,
 //   2. structure: the segment's words, as the symbolic phase kept them, else
 //      the runs' columns OR-ed into an LDS bit array over the words,
-//      Thread-Flat-Parallel over the segment's products (spg_flat.hpp),
+//      Thread-Flat-Parallel over the segment's products (spg_flat.hpp); the
+//      bits must be as many as the plan's entries,
 //   3. ranks: prefix popcounts of the words give every column its place in
 //      the row,
 //   4. values: each product added at its rank in LDS (Algorithm 1's
@@ -24,6 +25,14 @@
 //   5. write-out: values in rank order, then columns expanded from the bits
 //      into LDS and stored in rank order (both coalesced), at the segment's
 //      offset in the row, which the symbolic phase recorded.
+//
+// Kept words may not be the products' (B changed behind the plan).  They are if
+// every product finds its bit and every entry has a product; an entry without
+// one is still zero.  So a row whose products all found their bits and that has
+// no zero entry is done (one more instruction per product, one per entry: R-MAT
+// scale 17 and 15 unchanged within 1%); a zero entry (a cancelled sum, stored
+// zeros) has the row's bits OR-ed and counted after all, a product without its
+// bit has the row done again on the words of its products.
 //
 // Nothing lives in HBM but the inputs, the kept words and C; a row with one
 // segment (its entries and window fit) runs the same steps once, with whole B
@@ -150,6 +159,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     __shared__ VT st_a[SG_WG];
     __shared__ long long red[SG_WG / WAVE + 2];
     __shared__ __align__(8) uint32_t wb[SG_WG / WAVE][2 * SG_U];  // flat_window's scratch per wavefront
+    __shared__ int redo_zero, redo_miss;  // kept words: an entry is zero, a product's column is not in them
     const int t = threadIdx.x, l = lane_id(), wv = read_first(t / WAVE);
     for (int w = t; w < SG_NW; w += SG_WG) bits[w] = 0;
     for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;  // every kind of zero
@@ -162,9 +172,13 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     int64_t qlo2 = 0, qhi2 = 0;
     if (second) rs_bounds(a.rs2, qlo2, qhi2);
     int x2 = x;
+    enum { NO, PRODUCTS, CHECK };  // the row again, on the words of its products (CHECK: to count them)
+    int again = NO, i = 0;
     for (;;) {
-        int i;
-        if (second) {
+        if (again != NO) {  // values may have been added past the segment's
+            for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;
+            __syncthreads();
+        } else if (second) {
             i = sg_next_row(a.rs2, qlo2, qhi2, x2, red);
             if (i < 0) {
                 second = false;
@@ -174,6 +188,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             i = sg_next_row(a.rs, qlo, qhi, x, red);
             if (i < 0) break;
         }
+        if (t == 0) redo_zero = redo_miss = 0;
         const bool acc2 = ACC2 != ACC && second;  // this row accumulates with ACC2
         const int2 win = a.rwin[i];
         const int wlo = win.x, nw = win.y - win.x + 1;
@@ -181,7 +196,7 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
         const int64_t ab = a.arp[i], ae = a.arp[i + 1];
         const bool has_list = a.plan_len != nullptr && a.sym_kind[i] == K_DG && a.plan_len[i] > 0;
         const uint2 *list = has_list ? a.plan + a.plan_off[i] : nullptr;
-        const uint32_t *kept = has_list && a.sgb != nullptr && a.sgb_len[i] > 0 ? a.sgb + a.sgb_off[i] : nullptr;
+        const uint32_t *kept = again == NO && has_list && a.sgb != nullptr && a.sgb_len[i] > 0 ? a.sgb + a.sgb_off[i] : nullptr;
         const int nseg = has_list ? read_first((int)list[0].x) : 1;
         const bool single = nseg == 1;
         const bool one_chunk = ae - ab <= SG_WG;
@@ -343,12 +358,22 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
                 if (tot != cnt) bad = 1;
                 __syncthreads();
             }
+            if (again == CHECK) {  // the values stand
+                if (!one_chunk) {  // past the segment (below: the walk over the values does it)
+                    int tot;
+                    for (int64_t cb = ab; cb < ae; cb += SG_WG) stage(cb, false, true, &tot);
+                }
+                for (int w = t; w < SG_NW; w += SG_WG) bits[w] = 0;
+                __syncthreads();
+                continue;
+            }
             // values: each product added at its rank
+            uint32_t hit = 1;  // bit 0: every product's column is in the words
             for (int64_t cb = ab; cb < ae; cb += SG_WG) {
                 int tot = tot1, cn = cn1;
                 if (!one_chunk) cn = stage(cb, kept != nullptr, true, &tot);
                 walk(cn, tot, [&](int (&k)[SG_U], IX (&e)[SG_U]) {
-                    int c[SG_U];
+                    int c[SG_U], r[SG_U];  // columns, ranks
                     VT v[SG_U];
 #pragma unroll
                     for (int u = 0; u < SG_U; ++u) c[u] = ldc(max(e[u], IX(0)));
@@ -357,12 +382,20 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
 #pragma unroll
                     for (int u = 0; u < SG_U; ++u) {
                         const int d = (c[u] >> 5) - dbase;
-                        if (e[u] < 0 || (unsigned)d >= (unsigned)SG_NW) continue;
-                        const int r = (int)pre[d] + bits_below(bits[d], c[u] & 31);
-                        if (r < SG_CAP) {
-                            if (acc2) A2::add(&vals2[r], st_a[k[u]], v[u]);
-                            else A::add(&vals[r], st_a[k[u]], v[u]);
-                        }
+                        const bool in = e[u] >= 0 && (unsigned)d < (unsigned)SG_NW;
+                        const uint32_t w = in ? bits[d] : ~0u;
+                        const int b = c[u] & 31;
+                        r[u] = in ? (int)pre[d] + bits_below(w, b) : SG_CAP;
+                        hit &= w >> b;
+                    }
+                    if (acc2) {
+#pragma unroll
+                        for (int u = 0; u < SG_U; ++u)
+                            if (r[u] < SG_CAP) A2::add(&vals2[r[u]], st_a[k[u]], v[u]);
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < SG_U; ++u)
+                            if (r[u] < SG_CAP) A::add(&vals[r[u]], st_a[k[u]], v[u]);
                     }
                 });
                 if (!one_chunk) __syncthreads();  // st_* are refilled for the next chunk
@@ -374,10 +407,19 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             // the bits and values are cleared for the next segment
             const int64_t o = c0 + p1 - cbase;
             const int cw = min(cnt, SG_CAP);
-            for (int r = t; r < cw; r += SG_WG) store_c(&a.cval[o + r], acc2 ? A2::fin(vals2[r]) : A::fin(vals[r]));
+            bool hole = false;  // an entry is zero: without a product, or a sum of zero
+            for (int r = t; r < cw; r += SG_WG) {
+                const VT v = acc2 ? A2::fin(vals2[r]) : A::fin(vals[r]);
+                hole |= v == VT(0);
+                store_c(&a.cval[o + r], v);
+            }
+            if (hole) redo_zero = 1;
+            if (!(hit & 1u)) redo_miss = 1;
             __syncthreads();
             int32_t *colbuf = (int32_t *)vals_raw;  // SG_CAP * VB >= 4 * SG_CAP bytes
-            for (int w = t; w < span; w += SG_WG) {
+            // (other products than the plan's reach past the segment's words and entries)
+            const int wend = bad ? SG_NW : span, rend = bad ? SG_CAP : cw;
+            for (int w = t; w < wend; w += SG_WG) {
                 uint32_t m = bits[w];
                 int r = pre[w];
                 const int colb = (dbase + w) << 5;
@@ -392,11 +434,17 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             __syncthreads();
             for (int r = t; r < cw; r += SG_WG) store_c(&a.cci[o + r], colbuf[r]);
             __syncthreads();
-            for (int r = t; r < cw; r += SG_WG) {  // all-zero bytes either way
+            for (int r = t; r < rend; r += SG_WG) {  // all-zero bytes either way
                 if (acc2) vals2[r] = A2::zero();
                 else vals[r] = A::zero();
             }
             __syncthreads();
+        }
+        if (kept) {
+            const int miss = read_first(redo_miss);
+            if (miss | read_first(redo_zero)) again = miss ? PRODUCTS : CHECK;
+        } else {
+            again = NO;
         }
         if (t == 0 && bad) atomicAdd(&a.st->mismatch, 1);
     }
