@@ -28,11 +28,12 @@
 //
 // Kept words may not be the products' (B changed behind the plan).  They are if
 // every product finds its bit and every entry has a product; an entry without
-// one is still zero.  So a row whose products all found their bits and that has
-// no zero entry is done (one more instruction per product, one per entry: R-MAT
-// scale 17 and 15 unchanged within 1%); a zero entry (a cancelled sum, stored
-// zeros) has the row's bits OR-ed and counted after all, a product without its
-// bit has the row done again on the words of its products.
+// one still holds the -0.0 it starts from, which sums that cancel do not give.
+// So a row whose products all found their bits and that has no entry of -0.0 is
+// done (one more instruction per product, two per entry: R-MAT scale 17 and 15
+// unchanged within 1%); an entry of -0.0 (products of -0.0 only: stored zeros)
+// has the row's bits OR-ed and counted after all, a product without its bit has
+// the row done again on the words of its products.
 //
 // Nothing lives in HBM but the inputs, the kept words and C; a row with one
 // segment (its entries and window fit) runs the same steps once, with whole B
@@ -139,6 +140,15 @@ __device__ __forceinline__ int64_t sg_gallop(const int32_t *bci, int64_t lo, int
     return lo + r;
 }
 
+// An accumulator without a product: -0.0, which adding any product replaces
+// (with that product; +0.0 by a sum of zero).
+__device__ __forceinline__ double sg_none(double) { return -0.0; }
+__device__ __forceinline__ float sg_none(float) { return -0.0f; }
+__device__ __forceinline__ unsigned long long sg_none(unsigned long long) { return 0x80000000ull; }  // (s, c)
+__device__ __forceinline__ bool sg_is_none(double v) { return __double_as_longlong(v) == LLONG_MIN; }
+__device__ __forceinline__ bool sg_is_none(float v) { return __float_as_int(v) == INT_MIN; }
+__device__ __forceinline__ bool sg_is_none(unsigned long long v) { return (int)(uint32_t)v == INT_MIN; }
+
 // ACC accumulates the rows of a.rs, ACC2 those of a.rs2 (FP32 values: the
 // heaviest rows in FP64); the value array holds either kind of entry.  IX:
 // 32-bit B indices where byte offsets into B's values fit 32 bits.
@@ -159,10 +169,9 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     __shared__ VT st_a[SG_WG];
     __shared__ long long red[SG_WG / WAVE + 2];
     __shared__ __align__(8) uint32_t wb[SG_WG / WAVE][2 * SG_U];  // flat_window's scratch per wavefront
-    __shared__ int redo_zero, redo_miss;  // kept words: an entry is zero, a product's column is not in them
+    __shared__ int redo_none, redo_miss;  // kept words: an entry may have no product, a product's column is not in them
     const int t = threadIdx.x, l = lane_id(), wv = read_first(t / WAVE);
     for (int w = t; w < SG_NW; w += SG_WG) bits[w] = 0;
-    for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;  // every kind of zero
     int64_t qlo, qhi;
     rs_bounds(a.rs, qlo, qhi);
     const int64_t cbase = a.cbase_row >= 0 ? a.coff[a.cbase_row] : 0;
@@ -174,21 +183,30 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
     int x2 = x;
     enum { NO, PRODUCTS, CHECK };  // the row again, on the words of its products (CHECK: to count them)
     int again = NO, i = 0;
+    // the first n accumulators of the current row set
+    auto clear = [&](int n) {
+        if (ACC2 != ACC && second)
+            for (int r = t; r < n; r += SG_WG) vals2[r] = sg_none(S2());
+        else
+            for (int r = t; r < n; r += SG_WG) vals[r] = sg_none(S());
+    };
+    clear(SG_CAP);
     for (;;) {
         if (again != NO) {  // values may have been added past the segment's
-            for (int r = t; r < SG_CAP * VB / 4; r += SG_WG) ((uint32_t *)vals_raw)[r] = 0u;
+            clear(SG_CAP);
             __syncthreads();
         } else if (second) {
             i = sg_next_row(a.rs2, qlo2, qhi2, x2, red);
             if (i < 0) {
                 second = false;
+                clear(SG_CAP);
                 continue;
             }
         } else {
             i = sg_next_row(a.rs, qlo, qhi, x, red);
             if (i < 0) break;
         }
-        if (t == 0) redo_zero = redo_miss = 0;
+        if (t == 0) redo_none = redo_miss = 0;
         const bool acc2 = ACC2 != ACC && second;  // this row accumulates with ACC2
         const int2 win = a.rwin[i];
         const int wlo = win.x, nw = win.y - win.x + 1;
@@ -407,13 +425,16 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             // the bits and values are cleared for the next segment
             const int64_t o = c0 + p1 - cbase;
             const int cw = min(cnt, SG_CAP);
-            bool hole = false;  // an entry is zero: without a product, or a sum of zero
-            for (int r = t; r < cw; r += SG_WG) {
-                const VT v = acc2 ? A2::fin(vals2[r]) : A::fin(vals[r]);
-                hole |= v == VT(0);
-                store_c(&a.cval[o + r], v);
-            }
-            if (hole) redo_zero = 1;
+            bool none = false;
+            auto put = [&](const auto *from, auto fin) {
+                for (int r = t; r < cw; r += SG_WG) {
+                    none |= sg_is_none(from[r]);
+                    store_c(&a.cval[o + r], fin(from[r]) + VT(0));  // (-0.0 becomes 0.0)
+                }
+            };
+            if (acc2) put(vals2, A2::fin);
+            else put(vals, A::fin);
+            if (none) redo_none = 1;
             if (!(hit & 1u)) redo_miss = 1;
             __syncthreads();
             int32_t *colbuf = (int32_t *)vals_raw;  // SG_CAP * VB >= 4 * SG_CAP bytes
@@ -434,15 +455,12 @@ __global__ __launch_bounds__(SG_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) v
             __syncthreads();
             for (int r = t; r < cw; r += SG_WG) store_c(&a.cci[o + r], colbuf[r]);
             __syncthreads();
-            for (int r = t; r < rend; r += SG_WG) {  // all-zero bytes either way
-                if (acc2) vals2[r] = A2::zero();
-                else vals[r] = A::zero();
-            }
+            clear(rend);
             __syncthreads();
         }
         if (kept) {
             const int miss = read_first(redo_miss);
-            if (miss | read_first(redo_zero)) again = miss ? PRODUCTS : CHECK;
+            if (miss | read_first(redo_none)) again = miss ? PRODUCTS : CHECK;
         } else {
             again = NO;
         }

@@ -122,6 +122,14 @@ def test_stored_zeros_of_heavy_rows(case, dtype):
     ref, S = oracle_ref(f32_inputs(A), f32_inputs(B)) if dtype == "f32" else oracle_ref(A, B)
     got = (rp.cpu().numpy().astype(np.int64), C.col_idx.cpu().numpy(), C.values.cpu().numpy())
     (check_f64 if dtype == "f64" else check_f32)(ref, S, got)
+    zero = got[2] == 0
+    assert zero.any() and not np.signbit(got[2][zero]).any()  # sums start from 0.0
+    # sums that cancel: exact in any order
+    A1, B1 = A.with_values(np.sign(A.values) + (A.values == 0)), B.with_values(np.sign(B.values))
+    d1, e1 = dA.with_values(torch.as_tensor(A1.values).to(dA.values)), dB.with_values(torch.as_tensor(B1.values).to(dB.values))
+    C1 = spg.spgemm_numeric(h, d1, e1, rp, nnz)
+    h.check_errors()
+    assert np.array_equal(C1.values.cpu().numpy(), oracle_ref(A1, B1)[0].values.astype(got[2].dtype))
     B2 = _changed(B, na, 1, "loses")
     dB.col_idx.copy_(torch.as_tensor(B2.col_idx, device="cuda"))
     spg.spgemm_numeric(h, dA, dB, rp, nnz, out=C)
