@@ -1232,6 +1232,12 @@ __global__ __launch_bounds__(BLK) void k_fill_i32(int32_t *p, int64_t n, int32_t
     for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) p[i] = v;
 }
 
+// Row pointers of C from the plan's offsets.
+template <typename T>
+__global__ __launch_bounds__(BLK) void k_store_rp(int64_t n1, const int64_t *src, T *dst) {
+    for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n1; i += (int64_t)gridDim.x * BLK) dst[i] = (T)src[i];
+}
+
 // Per kind, the slice of the (row-sorted) kind list holding rows in [rb, re).
 __global__ void k_kind_ranges(const int32_t *perm, const int64_t *koff, int64_t rb, int64_t re, int64_t *range) {
     const int k = threadIdx.x;
@@ -1373,6 +1379,13 @@ hipError_t launch_partition(int64_t m, const uint8_t *kind, int32_t *perm, const
         hipLaunchKernelGGL(k_part_fold, dim3(1), dim3(CB), 0, s, nb, (int32_t *)tmp + 4 * nb * NK);
     hipLaunchKernelGGL(k_part_scatter, dim3((unsigned)nb), dim3(CB), 0, s, m, nb, kind, (const int32_t *)tmp, perm,
                        koff, phase, heavy, st, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_store_rp(int64_t n1, const int64_t *src, void *dst, bool is64, hipStream_t s) {
+    const dim3 g(grid_for(n1, BLK));
+    if (is64) hipLaunchKernelGGL(k_store_rp<int64_t>, g, dim3(BLK), 0, s, n1, src, (int64_t *)dst);
+    else hipLaunchKernelGGL(k_store_rp<int32_t>, g, dim3(BLK), 0, s, n1, src, (int32_t *)dst);
     return hipGetLastError();
 }
 

@@ -474,7 +474,8 @@ static void rows_numeric_stats(spg_stats &o, const DevStats &hs, bool split, con
 // The symbolic phase on validated, device-resident structure: h->arp64 (m+1),
 // h->brp64 (n+1) as int64, A's columns aci (row indices of B) and B's columns
 // bci.  Leaves the plan in the handle and C's int64 row offsets in h->coff.
-// c_rp (nullable): C's row pointers, int32 or int64, written with them.
+// c_rp (nullable): C's row pointers, int32 or int64; not touched where the
+// product is refused.
 static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, int64_t nnza, int64_t nnzb,
                                 const int32_t *aci, const int32_t *bci, int64_t *nnzc_out, void *c_rp = nullptr,
                                 bool c_rp64 = false) {
@@ -705,9 +706,14 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     // the symbolic lists are the numeric ones and no classification runs
     // (two launches: 10 us at 4096 rows, 16 us at a million).
     const bool all_short = sel && !split && m > 0 && hs2.kcount_sym[K_SR] + hs2.kcount_sym[K_EMPTY] == m;
+    // The scan writes the caller's row pointers too where nothing can refuse the
+    // product any more: entries that may pass an int32, and kinds whose scratch
+    // may run out, have them copied at the end (5 us).
+    const bool rp_now = !split && (c_rp64 || hs1.fm <= (unsigned long long)INT32_MAX) &&
+                        hs2.kcount_sym[K_HL] + hs2.kcount_sym[K_DG] == 0;
     ScanOut so;
-    so.rp32 = c_rp64 ? nullptr : (int32_t *)c_rp;
-    so.rp64 = c_rp64 ? (int64_t *)c_rp : nullptr;
+    so.rp32 = rp_now && !c_rp64 ? (int32_t *)c_rp : nullptr;
+    so.rp64 = rp_now && c_rp64 ? (int64_t *)c_rp : nullptr;
     so.total = &dst->nnzc;
     so.host_total = all_short ? h->hkoff : nullptr;
     HIPCHK(launch_scan_i32(m, h->row_nnz.as<int32_t>(), 1, h->coff.as<int64_t>(), h->tmp.as<int64_t>(), so, st));
@@ -762,6 +768,9 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     const DevStats hs3 = *h->hst;
     if (hs3.overflow) return fail(h, SPG_ERR_OUT_OF_MEMORY, "level-2 hash arena too small in the symbolic phase");
     const int64_t nnzc = (int64_t)hs3.nnzc;
+    if (c_rp && !c_rp64 && nnzc > INT32_MAX)
+        return fail(h, SPG_ERR_INDEX_OVERFLOW, "nnz(C) exceeds an int32 row_ptr; ask for SPG_I64");
+    if (c_rp && !rp_now) HIPCHK(launch_store_rp(m + 1, h->coff.as<int64_t>(), c_rp, c_rp64, st));
     h->compressed = comp;
     spg_stats &o = h->stats;
     std::memset(&o, 0, sizeof(o));
@@ -826,8 +835,6 @@ spg_status spgemm_symbolic(spg_handle h, const spg_csr *A, const spg_csr *B, voi
     if ((s = symbolic_core(h, m, n, k, A->nnz, B->nnz, A->col_idx, B->col_idx, &nnzc, C_row_ptr,
                            c_rpt == SPG_I64)) != SPG_OK)
         return s;
-    if (c_rpt == SPG_I32 && nnzc > INT32_MAX)
-        return fail(h, SPG_ERR_INDEX_OVERFLOW, "nnz(C) exceeds an int32 row_ptr; ask for SPG_I64");
     Fingerprint &fp = h->fp;
     fp.m = m; fp.n = n; fp.k = k; fp.nnza = A->nnz; fp.nnzb = B->nnz;
     fp.arp = A->row_ptr; fp.brp = B->row_ptr; fp.aci = A->col_idx; fp.bci = B->col_idx;

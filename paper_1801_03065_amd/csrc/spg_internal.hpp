@@ -461,6 +461,8 @@ int64_t part_tmp_elems(int64_t m);
 hipError_t launch_partition(int64_t m, const uint8_t *kind, int32_t *perm, const int64_t *tmp, int64_t *koff,
                             int phase, int heavy, DevStats *st, DevStats *host, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
+// C's row pointers (int32 or int64) from the plan's offsets.
+hipError_t launch_store_rp(int64_t n1, const int64_t *src, void *dst, bool is64, hipStream_t s);
 hipError_t launch_kind_ranges(const int32_t *perm, const int64_t *koff, int64_t rb, int64_t re, int64_t *range,
                               hipStream_t s);
 
