@@ -198,6 +198,28 @@ void release(DevBuf &b) {
     b.cap = 0;
 }
 
+// The heavy rows' kept bit windows yield to everything else: the numeric phase
+// rebuilds them.  (hipFree waits for the kernels that use them.)
+void drop_windows(spg_handle h) {
+    h->sgb_kept = false;
+    release(h->sgb);
+}
+// ensure for what the call cannot do without.
+hipError_t need(spg_handle h, DevBuf &b, size_t bytes) {
+    const hipError_t e = ensure(b, bytes);
+    if (e == hipSuccess || !h->sgb.p) return e;
+    (void)hipGetLastError();
+    drop_windows(h);
+    return ensure(b, bytes);
+}
+// Bit windows of `bytes` may be kept: up to 128 MiB as they come; more where that
+// takes a sixteenth of the free memory at most.
+bool windows_allowed(spg_handle h, size_t bytes) {
+    if (bytes <= 4 * (size_t)SGB_BOUND || bytes <= h->sgb.cap) return true;
+    size_t free_b = 0, total = 0;
+    return hipMemGetInfo(&free_b, &total) == hipSuccess && bytes <= free_b / 16;
+}
+
 // Team size of the short-row kernel: the smallest power of two >= the largest
 // multiplication count among its rows, at least 8 lanes.
 static int sr_lg(int max_flops) {
@@ -429,25 +451,25 @@ spg_status spg_check_errors(spg_handle h) {
 // ------------------------------------------------------------------ symbolic
 // Plan buffers for an m x n times n x k product (grow-only).
 static spg_status plan_buffers(spg_handle h, int64_t m, int64_t n, int64_t nnzb) {
-    HIPCHK(ensure(h->arp64, 8 * (m + 1)));
-    HIPCHK(ensure(h->brp64, 8 * (n + 1)));
-    HIPCHK(ensure(h->binfo, sizeof(BRow) * std::max<int64_t>(n, 1)));
-    HIPCHK(ensure(h->uflag, 4 * ((std::max<int64_t>(n, 1) + 3) / 4)));
-    HIPCHK(ensure(h->bcrp, 8 * (n + 1)));
-    HIPCHK(ensure(h->rflops, 8 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->rflopsc, 8 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->rwin, 8 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->row_nnz, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->row_words, 4 * (m + 2)));  // one padding element (8-byte reads of the last row)
-    HIPCHK(ensure(h->coff, 8 * (m + 1)));
-    HIPCHK(ensure(h->kind_sym, std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->kind_num, std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->perm_sym, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->perm_num, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->koff_sym, 8 * (NK + 1)));
-    HIPCHK(ensure(h->koff_num, 8 * (NK + 1)));
+    HIPCHK(need(h, h->arp64, 8 * (m + 1)));
+    HIPCHK(need(h, h->brp64, 8 * (n + 1)));
+    HIPCHK(need(h, h->binfo, sizeof(BRow) * std::max<int64_t>(n, 1)));
+    HIPCHK(need(h, h->uflag, 4 * ((std::max<int64_t>(n, 1) + 3) / 4)));
+    HIPCHK(need(h, h->bcrp, 8 * (n + 1)));
+    HIPCHK(need(h, h->rflops, 8 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->rflopsc, 8 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->rwin, 8 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->row_nnz, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->row_words, 4 * (m + 2)));  // one padding element (8-byte reads of the last row)
+    HIPCHK(need(h, h->coff, 8 * (m + 1)));
+    HIPCHK(need(h, h->kind_sym, std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->kind_num, std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->perm_sym, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->perm_num, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->koff_sym, 8 * (NK + 1)));
+    HIPCHK(need(h, h->koff_num, 8 * (NK + 1)));
     const int64_t tmp_elems = std::max({scan_tmp_elems(m), scan_tmp_elems(n), part_tmp_elems(m)});
-    HIPCHK(ensure(h->tmp, 8 * tmp_elems));
+    HIPCHK(need(h, h->tmp, 8 * tmp_elems));
 
     return SPG_OK;
 }
@@ -517,13 +539,13 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     const bool want_segs_opt = sel || h->opt.accumulator == SPG_ACC_DENSE;
     const bool want_plan = want_pairs || want_segs_opt;
     if (want_plan) {
-        HIPCHK(ensure(h->plan_len, 4 * (m + 2)));  // one padding element (8-byte reads of the last row)
-        HIPCHK(ensure(h->plan_off, 8 * (m + 1)));
+        HIPCHK(need(h, h->plan_len, 4 * (m + 2)));  // one padding element (8-byte reads of the last row)
+        HIPCHK(need(h, h->plan_off, 8 * (m + 1)));
         cp.plan_cap = want_pairs ? PL_CAP : 0;
         cp.plan_len = h->plan_len.as<int32_t>();
         cp.sg = want_segs_opt ? 1 : 0;
         if (want_segs_opt) {
-            HIPCHK(ensure(h->sgb_len, 4 * (m + 1)));
+            HIPCHK(need(h, h->sgb_len, 4 * (m + 1)));
             cp.sgb_len = h->sgb_len.as<int32_t>();
         }
     }
@@ -552,7 +574,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         // bits) pairs.  Launched once the host knows the decision: on the
         // device's own flag these were four empty launches (12 to 25 us) for
         // every product that does not compress.
-        HIPCHK(ensure(h->bcw, 8 * std::max<int64_t>(nnzb, 1)));
+        HIPCHK(need(h, h->bcw, 8 * std::max<int64_t>(nnzb, 1)));
         static_assert(sizeof(BRow) == 4 * sizeof(int32_t), "BRow is four int32");
         ScanOut so;
         so.host_total = h->hkoff + 2;
@@ -570,6 +592,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
 
     h->planned = false;
     h->segmented = false;
+    h->sgb_kept = false;
     const bool pairs_used = want_pairs && hs2.kcount_sym[K_DW] > 0;
     const bool segs_used = want_segs && hs2.kcount_sym[K_DG] > 0;
     // Room for stored structure: the scans of the rows' room give each row's
@@ -581,7 +604,7 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     if (pairs_used || segs_used) {
         HIPCHK(launch_scan_i32(m, h->plan_len.as<int32_t>(), h->plan_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
         if (segs_used) {
-            HIPCHK(ensure(h->sgb_off, 8 * (m + 1)));
+            HIPCHK(need(h, h->sgb_off, 8 * (m + 1)));
             HIPCHK(launch_scan_i32(m, h->sgb_len.as<int32_t>(), h->sgb_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
         }
         const int64_t rows_dg = hs2.kcount_sym[K_DG], nw_dg = hs2.kmax_sym[K_DG][0];
@@ -606,13 +629,13 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         // without room for the pairs the numeric phase rebuilds the structure
         // itself; without room for the segment lists heavy rows use the
         // window-wide kernel
-        plan_ok = ensure(h->plan, 8 * (size_t)plan_room) == hipSuccess;
+        plan_ok = need(h, h->plan, 8 * (size_t)plan_room) == hipSuccess;
         (void)hipGetLastError();
     }
     h->planned = plan_ok && pairs_used;
     h->segmented = plan_ok && segs_used;
     // (without room for the heavy rows' bit windows the numeric phase rebuilds them)
-    h->sgb_kept = h->segmented && sgb_words > 0 && sgb_words <= SGB_MAX &&
+    h->sgb_kept = h->segmented && sgb_words > 0 && sgb_words <= SGB_MAX && windows_allowed(h, 4 * (size_t)sgb_words) &&
                   ensure(h->sgb, 4 * (size_t)sgb_words) == hipSuccess;
     (void)hipGetLastError();
     // segments need a list wherever a row may exceed one (rows with a bound
@@ -687,8 +710,8 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
         const int64_t cap2 = pow2_at_least(2 * (int64_t)std::max(1, hs2.kmax_sym[K_HL][1]), 64);
         int grid = (int)std::min<int64_t>(grid_cap(hs2.kcount_sym[K_HL]), 2 * h->cus);
         sa.l2_cap = cap2;
-        HIPCHK(ensure(h->l2k, (size_t)4 * cap2 * grid));
-        HIPCHK(ensure(h->l2v, (size_t)4 * cap2 * grid));
+        HIPCHK(need(h, h->l2k, (size_t)4 * cap2 * grid));
+        HIPCHK(need(h, h->l2v, (size_t)4 * cap2 * grid));
         sa.l2_keys = h->l2k.as<uint32_t>();
         sa.l2_vals = h->l2v.as<uint32_t>();
         HIPCHK(launch_fill_i32(sa.rs.queue, XCDS, 0, st));
@@ -741,9 +764,9 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     }
     h->heavy_split = false;
     if (split) {  // FP64-accumulated rows: their own kind lists (FP64 accumulation in FP32 mode)
-        HIPCHK(ensure(h->kind_heavy, std::max<int64_t>(m, 1)));
-        HIPCHK(ensure(h->perm_heavy, 4 * std::max<int64_t>(m, 1)));
-        HIPCHK(ensure(h->koff_heavy, 8 * (NK + 1)));
+        HIPCHK(need(h, h->kind_heavy, std::max<int64_t>(m, 1)));
+        HIPCHK(need(h, h->perm_heavy, 4 * std::max<int64_t>(m, 1)));
+        HIPCHK(need(h, h->koff_heavy, 8 * (NK + 1)));
         ClassParams ch = cp;
         ch.heavy = 1;
         HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
@@ -771,6 +794,12 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     if (c_rp && !c_rp64 && nnzc > INT32_MAX)
         return fail(h, SPG_ERR_INDEX_OVERFLOW, "nnz(C) exceeds an int32 row_ptr; ask for SPG_I64");
     if (c_rp && !rp_now) HIPCHK(launch_store_rp(m + 1, h->coff.as<int64_t>(), c_rp, c_rp64, st));
+    // Large windows are held only while the free memory holds C, which the caller
+    // allocates next, and only by a plan that uses them.
+    if (h->sgb.cap > 4 * (size_t)SGB_BOUND) {
+        size_t free_b = 0, total = 0;
+        if (!h->sgb_kept || hipMemGetInfo(&free_b, &total) != hipSuccess || free_b / 12 < (size_t)nnzc) drop_windows(h);
+    }
     h->compressed = comp;
     spg_stats &o = h->stats;
     std::memset(&o, 0, sizeof(o));
@@ -1000,6 +1029,7 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
             }
             (void)hipGetLastError();
         }
+        if (!h->sgb_kept) na.sgb = nullptr;  // dropped since the call began
         HIPCHK(launch_num_sg<VT>(na, acc, acc_b, lc));
         lc.grid = 0;
     } else if (kcount[K_DG] > 0 && dg != DG_SKIP) {
@@ -1017,7 +1047,7 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
             na.arena = h->scr;
         } else {
             if (h->arena.cap < bytes || h->arena_bytes_zeroed < bytes) {
-                HIPCHK(ensure(h->arena, bytes));
+                HIPCHK(need(h, h->arena, bytes));
                 HIPCHK(hipMemsetAsync(h->arena.p, 0, h->arena.cap, st));
                 h->arena_bytes_zeroed = h->arena.cap;
             }
@@ -1041,7 +1071,7 @@ static spg_status launch_kinds(spg_handle h, NumArgs<VT> na, const long long *kc
         if (h->noalloc) {
             na.arena = h->scr;
         } else {
-            if (h->l2k.cap < bytes) HIPCHK(ensure(h->l2k, bytes));
+            if (h->l2k.cap < bytes) HIPCHK(need(h, h->l2k, bytes));
             na.arena = h->l2k.p;
         }
         HIPCHK(launch_fill_i32(na.rs.queue, XCDS, 0, st));
@@ -1063,9 +1093,9 @@ static spg_status autotune(spg_handle h, NumArgs<VT> na, int acc) {
     hipStream_t st = h->stream;
     const int64_t m = h->fp.m;
     DevStats *dst = h->dstats.as<DevStats>();
-    HIPCHK(ensure(h->kind_tmp, std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->perm_tmp, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->koff_tmp, 8 * (NK + 1)));
+    HIPCHK(need(h, h->kind_tmp, std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->perm_tmp, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->koff_tmp, 8 * (NK + 1)));
     const int stride = (int)std::max<int64_t>(1, std::min<int64_t>(16, m / 16384));
     ClassParams cp = h->cparams;
     cp.phase = 1;
@@ -1158,12 +1188,12 @@ static spg_status autotune_classes(spg_handle h, NumArgs<VT> na, int acc) {
     hipStream_t st = h->stream;
     const int64_t m = h->fp.m;
     DevStats *dst = h->dstats.as<DevStats>();
-    HIPCHK(ensure(h->kind_tmp, std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->perm_tmp, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->koff_tmp, 8 * (NK + 1)));
-    HIPCHK(ensure(h->kind_cls, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->perm_cls, 16 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->koff_cls, 8 * 4 * (NK + 1)));
+    HIPCHK(need(h, h->kind_tmp, std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->perm_tmp, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->koff_tmp, 8 * (NK + 1)));
+    HIPCHK(need(h, h->kind_cls, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->perm_cls, 16 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->koff_cls, 8 * 4 * (NK + 1)));
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
@@ -1310,7 +1340,7 @@ static spg_status numeric_impl(spg_handle h, const VT *aval, const VT *bval, int
     na.lg_gs = h->lg_num;
     na.cbase_row = -1;
     if (row_begin >= 0) {  // one panel of rows: per-kind slices, output relative to the panel
-        HIPCHK(ensure(h->krange, 16 * NK));
+        HIPCHK(need(h, h->krange, 16 * NK));
         HIPCHK(launch_kind_ranges(h->perm_num.as<int32_t>(), h->koff_num.as<int64_t>(), row_begin, row_end,
                                   h->krange.as<int64_t>(), h->stream));
         na.rs.rows = h->perm_num.as<int32_t>();
@@ -1319,7 +1349,7 @@ static spg_status numeric_impl(spg_handle h, const VT *aval, const VT *bval, int
         na.cbase_row = row_begin;
         spg_status s = launch_kinds<VT>(h, na, hs.kcount_num, hs.kmax_num, acc);
         if (s != SPG_OK || !h->heavy_split) return s;
-        HIPCHK(ensure(h->krange_heavy, 16 * NK));
+        HIPCHK(need(h, h->krange_heavy, 16 * NK));
         HIPCHK(launch_kind_ranges(h->perm_heavy.as<int32_t>(), h->koff_heavy.as<int64_t>(), row_begin, row_end,
                                   h->krange_heavy.as<int64_t>(), h->stream));
         na.rs.rows = h->perm_heavy.as<int32_t>();
@@ -1440,8 +1470,8 @@ static spg_status build_maps(spg_handle h, const int32_t *cci) {
     if (h->ncls && h->cls_tuned)
         for (int c = 0; c < 4; ++c)
             if (h->cls_rows[c] && h->cls_pol[c] == SPG_ACC_LL) return SPG_OK;
-    HIPCHK(ensure(h->mflops, 4 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->map_off, 8 * (m + 1)));
+    HIPCHK(need(h, h->mflops, 4 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->map_off, 8 * (m + 1)));
     HIPCHK(launch_map_rows(m, h->kind_num.as<uint8_t>(), h->heavy_split ? h->kind_heavy.as<uint8_t>() : nullptr,
                            h->rflops.as<int64_t>(), h->mflops.as<int32_t>(), st));
     HIPCHK(launch_scan_i32(m, h->mflops.as<int32_t>(), h->map_off.as<int64_t>(), h->tmp.as<int64_t>(), st));
@@ -1449,7 +1479,7 @@ static spg_status build_maps(spg_handle h, const int32_t *cci) {
     HIPCHK(hipStreamSynchronize(st));
     const int64_t total = h->hkoff[3];
     if (total == 0) return SPG_OK;
-    if (ensure(h->map, 2 * (size_t)total) != hipSuccess) {
+    if (need(h, h->map, 2 * (size_t)total) != hipSuccess) {
         (void)hipGetLastError();
         return SPG_OK;
     }
@@ -1530,11 +1560,11 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
                               int structural) {
     hipStream_t st = h->stream;
     const int64_t m = A->nrows, n = B->nrows, k = B->ncols;
-    HIPCHK(ensure(h->mk_arp, 8 * (m + 1)));
-    HIPCHK(ensure(h->mk_brp, 8 * (n + 1)));
-    HIPCHK(ensure(h->mk_mrp, 8 * (m + 1)));
-    HIPCHK(ensure(h->mk_rows, 12 * std::max<int64_t>(m, 1)));
-    HIPCHK(ensure(h->mk_cnt, 8 * sizeof(int)));
+    HIPCHK(need(h, h->mk_arp, 8 * (m + 1)));
+    HIPCHK(need(h, h->mk_brp, 8 * (n + 1)));
+    HIPCHK(need(h, h->mk_mrp, 8 * (m + 1)));
+    HIPCHK(need(h, h->mk_rows, 12 * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->mk_cnt, 8 * sizeof(int)));
     // [0..2] rows per kind, [3..5] longest mask row per kind, [6] bad input, [7] row queue
     int *cnt = h->mk_cnt.as<int>(), *bad = cnt + 6;
     int32_t *rows = h->mk_rows.as<int32_t>();
@@ -1577,7 +1607,7 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
             a.arena_cap = pow2_at_least(2 * (int64_t)hc[5], 64);
             lc.grid = 2 * h->cus / XCDS * XCDS;
             a.arena_slices = std::min(hc[2], lc.grid);
-            HIPCHK(ensure(h->mk_arena, (size_t)12 * a.arena_cap * a.arena_slices));
+            HIPCHK(need(h, h->mk_arena, (size_t)12 * a.arena_cap * a.arena_slices));
             a.arena = h->mk_arena.p;
         }
         HIPCHK(launch_mask<VT>(a, hc[4], cnt + 7, lc));
@@ -1671,7 +1701,7 @@ extern "C" spg_status spgemm_backward(spg_handle h, const spg_csr *A, const spg_
 
 // ------------------------------------------------------------------ batch
 static spg_status upload_desc(spg_handle h, const std::vector<BatchDesc> &d, BatchDesc **out) {
-    HIPCHK(ensure(h->batch.desc, sizeof(BatchDesc) * d.size() * 4 + 16));
+    HIPCHK(need(h, h->batch.desc, sizeof(BatchDesc) * d.size() * 4 + 16));
     // four regions: A, B, C row pointers, scratch for gather/scatter descriptors
     *out = h->batch.desc.as<BatchDesc>();
     HIPCHK(hipMemcpyAsync(*out, d.data(), sizeof(BatchDesc) * d.size(), hipMemcpyHostToDevice, h->stream));
@@ -1721,8 +1751,8 @@ extern "C" spg_status spgemm_batch_symbolic(spg_handle h, int32_t count, const s
     bt.nnzb = NB;
     hipStream_t st = h->stream;
     if ((s = plan_buffers(h, R, N, NB)) != SPG_OK) return s;
-    HIPCHK(ensure(bt.aci, 4 * std::max<int64_t>(NA, 1)));
-    HIPCHK(ensure(bt.bci, 4 * std::max<int64_t>(NB, 1)));
+    HIPCHK(need(h, bt.aci, 4 * std::max<int64_t>(NA, 1)));
+    HIPCHK(need(h, bt.bci, 4 * std::max<int64_t>(NB, 1)));
     DevStats *dst = h->dstats.as<DevStats>();
     HIPCHK(hipMemsetAsync(dst, 0, sizeof(DevStats), st));
     BatchDesc *dev = nullptr;
@@ -1741,7 +1771,7 @@ extern "C" spg_status spgemm_batch_symbolic(spg_handle h, int32_t count, const s
         return s;
     // per-product entries of C, then each C_i.row_ptr
     if ((s = upload_desc(h, bt.c, &dev)) != SPG_OK) return s;
-    HIPCHK(ensure(h->blens, 16 * (size_t)count));
+    HIPCHK(need(h, h->blens, 16 * (size_t)count));
     HIPCHK(launch_batch_bounds(dev, count, h->coff.as<int64_t>(), h->blens.as<int64_t>(), st));
     std::vector<int64_t> bnd(2 * (size_t)count);
     HIPCHK(hipMemcpyAsync(bnd.data(), h->blens.p, 16 * (size_t)count, hipMemcpyDeviceToHost, st));
@@ -1780,7 +1810,7 @@ extern "C" spg_status spgemm_batch_symbolic(spg_handle h, int32_t count, const s
             used += rows_c[c] > 0;
         }
         if (used > 1) {
-            HIPCHK(ensure(h->row_cls, std::max<int64_t>(R, 1)));
+            HIPCHK(need(h, h->row_cls, std::max<int64_t>(R, 1)));
             if ((s = upload_desc(h, bt.a, &dev)) != SPG_OK) return s;
             HIPCHK(launch_batch_row_class(dev, count, bt.max_rows, h->row_cls.as<uint8_t>(), st));
             h->ncls = 4;
@@ -1818,7 +1848,7 @@ static spg_status batch_numeric_impl(spg_handle h, int32_t count, const spg_csr 
     if (!a_contig) {
         std::vector<BatchDesc> d = bt.a;
         for (int i = 0; i < count; ++i) d[i].vals = A[i].values;
-        HIPCHK(ensure(bt.astage, vb * std::max<int64_t>(bt.nnza, 1)));
+        HIPCHK(need(h, bt.astage, vb * std::max<int64_t>(bt.nnza, 1)));
         if ((s = upload_desc(h, d, &dev)) != SPG_OK) return s;
         HIPCHK(launch_batch_gather(dev, count, bt.max_nnza, bt.astage.p, (int)vb, st));
         aval = bt.astage.as<VT>();
@@ -1826,14 +1856,14 @@ static spg_status batch_numeric_impl(spg_handle h, int32_t count, const spg_csr 
     if (!b_contig) {
         std::vector<BatchDesc> d = bt.b;
         for (int i = 0; i < count; ++i) d[i].vals = B[i].values;
-        HIPCHK(ensure(bt.bstage, vb * std::max<int64_t>(bt.nnzb, 1)));
+        HIPCHK(need(h, bt.bstage, vb * std::max<int64_t>(bt.nnzb, 1)));
         if ((s = upload_desc(h, d, &dev)) != SPG_OK) return s;
         HIPCHK(launch_batch_gather(dev, count, bt.max_nnzb, bt.bstage.p, (int)vb, st));
         bval = bt.bstage.as<VT>();
     }
     if (!c_contig) {
-        HIPCHK(ensure(bt.cci, 4 * std::max<int64_t>(h->nnzc, 1)));
-        HIPCHK(ensure(bt.cval, vb * std::max<int64_t>(h->nnzc, 1)));
+        HIPCHK(need(h, bt.cci, 4 * std::max<int64_t>(h->nnzc, 1)));
+        HIPCHK(need(h, bt.cval, vb * std::max<int64_t>(h->nnzc, 1)));
         cci = bt.cci.as<int32_t>();
         cval = bt.cval.as<VT>();
     }

@@ -81,7 +81,8 @@ constexpr int PL_NW_MAX = 8192;   // window words of the stored-structure kernel
 constexpr int PL_R_MAX = 2048;    // row size of the stored-structure kernel
 constexpr int SG_NW = 4096;       // column-set words of one heavy-row segment (aligned groups)
 constexpr int SG_CAP = 4096;      // entries of one heavy-row segment (LDS values)
-constexpr int64_t SGB_MAX = int64_t(2) << 30;  // words of heavy rows' bit windows kept at most (8 GiB)
+constexpr int64_t SGB_MAX = int64_t(2) << 30;  // words of heavy rows' bit windows kept at most (8 GiB; beyond
+                                               // SGB_BOUND a sixteenth of the free memory, and while C fits beside them)
 constexpr int64_t SGB_BOUND = int64_t(1) << 25;  // sized by a bound, without a host wait, up to this many (128 MiB)
 // Rows of more multiplications are heavy rows too, whatever their size: one
 // wavefront forms 64 products in 0.2 to 0.4 us, a workgroup row several times
