@@ -224,7 +224,7 @@ hipError_t bwd_impl(const BwdArgs<VT> &a, const LaunchCfg &c) {
         hipLaunchKernelGGL(k_zero<VT>, dim3((unsigned)blocks), dim3(256), 0, c.stream, a.dB, a.nnzb);
     }
     if (a.m == 0) return hipGetLastError();
-    const bool i32 = a.nnzb * WAVE < (int64_t(1) << 31);
+    const bool i32 = flat_32bit(a.nnzb, WAVE, 8 * WAVE);
     if (a.flops <= 2 * WAVE * a.m)
         return i32 ? bwd_launch<VT, int32_t, 2>(a, c) : bwd_launch<VT, int64_t, 2>(a, c);
     return i32 ? bwd_launch<VT, int32_t, 8>(a, c) : bwd_launch<VT, int64_t, 8>(a, c);

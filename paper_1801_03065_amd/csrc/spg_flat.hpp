@@ -14,6 +14,15 @@ namespace spg {
 constexpr int FLAT_SHIFT = 48;
 constexpr long long FLAT_ONE = 1ll << FLAT_SHIFT, FLAT_LEN = FLAT_ONE - 1;
 
+// Products numbered in 32 bits: a chunk of `lanes` A entries forms at most
+// nnz(B) products per entry (fewer in all unless A repeats a column), and a walk
+// in rounds of `round` products steps past the last of them.
+constexpr bool flat_32bit(int64_t nnzb, int lanes, int round) {
+    return nnzb <= (INT32_MAX - round) / lanes;
+}
+static_assert(flat_32bit(33554423, 64, 512) && !flat_32bit(33554424, 64, 512), "last product number plus a round");
+static_assert(flat_32bit(4194295, 512, 4096) && !flat_32bit(4194303, 512, 4096), "fits itself, its last round does not");
+
 // k[u] = base + the bits of the window's mask (wb: 2 U words) below product
 // u * 64 + lane: two counting instructions on masks that every lane shares.
 template <int U>

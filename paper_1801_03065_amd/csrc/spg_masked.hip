@@ -399,7 +399,7 @@ hipError_t mask_ix(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCfg 
 // per product than 64-bit ones (triangles at scale 18: 2.16 against 2.27 ms in the two launches).
 template <typename VT, int NW, bool BIG>
 hipError_t mask_impl(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCfg &c) {
-    if (a.nnzb * (NW * WAVE) < (int64_t(1) << 31)) return mask_ix<VT, int32_t, NW, BIG>(a, mmax, queue, c);
+    if (flat_32bit(a.nnzb, NW * WAVE, MK_U * NW * WAVE)) return mask_ix<VT, int32_t, NW, BIG>(a, mmax, queue, c);
     return mask_ix<VT, int64_t, NW, BIG>(a, mmax, queue, c);
 }
 

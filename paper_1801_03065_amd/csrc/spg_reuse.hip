@@ -465,7 +465,7 @@ hipError_t map_flat_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
 template <typename VT, int ACC>
 hipError_t map_flat(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
     const int last = a.rs.kind + a.rs.more;
-    const bool i32 = a.nnzb * WAVE < (int64_t(1) << 31);
+    const bool i32 = flat_32bit(a.nnzb, WAVE, 8 * WAVE);
     if (last == K_SR)
         return i32 ? map_flat_u<VT, ACC, int32_t, 1>(a, c, rows) : map_flat_u<VT, ACC, int64_t, 1>(a, c, rows);
     if (last == K_BK0)
@@ -493,7 +493,7 @@ hipError_t num_map_acc(const NumArgs<VT> &a, int lgt, int lgs, const LaunchCfg &
 hipError_t launch_posmap(const NumArgs<double> &a, const int32_t *cci, int lgt, int lgs, const LaunchCfg &c,
                          int64_t rows) {
     if (lgt >= 6)
-        return a.nnzb * WAVE < (int64_t(1) << 31) ? posmap_flat<int32_t>(a, cci, c, rows)
+        return flat_32bit(a.nnzb, WAVE, 4 * WAVE) ? posmap_flat<int32_t>(a, cci, c, rows)
                                                   : posmap_flat<int64_t>(a, cci, c, rows);
     return by_team(lgt, [&](auto T) {
         constexpr int LT = decltype(T)::value;
