@@ -92,9 +92,9 @@ __global__ __launch_bounds__(WG) void k_sym_dg(SymArgs a) {
         if (i < 0) break;
         const int2 win = a.rwin[i];
         const int wlo = win.x, nw = win.y - win.x + 1;
-        // a B row holds at most this many words (columns) of the window, which
-        // bounds a chunk's products below 2^31
-        const int64_t lim = COMP ? nw : 32 * (int64_t)nw;
+        // a chunk's products stay below 2^31, the walk's last round included (a B
+        // row holds up to 2^20 columns of a window, more only if it repeats them)
+        const int64_t lim = (INT32_MAX - SH_U * WG) / WG;
         const int64_t ab = a.arp[i], ae = a.arp[i + 1];
         for (int64_t cb = ab; cb < ae; cb += WG) {
             int64_t b0 = 0, len = 0;
