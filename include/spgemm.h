@@ -162,7 +162,8 @@ typedef struct {
     int32_t tuned_lanes;            /* autotune: lanes per B row in the numeric phase (0 = not tuned) */
     int32_t fp64_rows;              /* rows kept in the FP64-accumulated kind lists
                                        (fp64_heavy_row_flops, fp32_terms_max) */
-    int32_t reserved[4];
+    int64_t rows_scattered_symbolic; /* of rows_symbolic[2], the rows counted by the product hash */
+    int64_t rows_scattered_numeric;  /* of rows_numeric[5], the rows sorted in column buckets */
 } spg_stats;
 
 typedef struct spg_handle_s *spg_handle;

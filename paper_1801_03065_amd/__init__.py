@@ -78,7 +78,8 @@ class spg_stats(ctypes.Structure):
                 ("n_kinds", ctypes.c_int32), ("rows_symbolic", ctypes.c_int64 * 8),
                 ("rows_numeric", ctypes.c_int64 * 8), ("l2_spill_rows", ctypes.c_int32),
                 ("tuned_policy", ctypes.c_int32), ("tuned_lanes", ctypes.c_int32),
-                ("fp64_rows", ctypes.c_int32), ("reserved", ctypes.c_int32 * 4)]
+                ("fp64_rows", ctypes.c_int32), ("rows_scattered_symbolic", ctypes.c_int64),
+                ("rows_scattered_numeric", ctypes.c_int64)]
 
 
 _P = ctypes.c_void_p
@@ -233,7 +234,7 @@ class Handle:
         rc = lib().spg_get_stats(self._h, ctypes.byref(st))
         if rc != SPG_OK:
             self._raise(rc)
-        d = {k: getattr(st, k) for k, _ in spg_stats._fields_ if k not in ("reserved",)}
+        d = {k: getattr(st, k) for k, _ in spg_stats._fields_}
         d["rows_symbolic"] = dict(zip(KIND_NAMES, list(st.rows_symbolic)[:st.n_kinds]))
         d["rows_numeric"] = dict(zip(KIND_NAMES, list(st.rows_numeric)[:st.n_kinds]))
         return d

@@ -482,13 +482,13 @@ static void rows_numeric_stats(spg_stats &o, const DevStats &hs, bool split, con
     if (!main) main = hs.kcount_num;
     long long heavy = 0;
     for (int kk = 0; kk < NK_PUBLIC; ++kk) o.rows_numeric[kk] = 0;
+    o.rows_scattered_numeric = 0;
     for (int kk = 0; kk < NK; ++kk) {
         const int pk = kk < NK_PUBLIC ? kk : K_WH;  // column-bucket rows count with the word hash
-        o.rows_numeric[pk] += main[kk];
-        if (split && kk != K_EMPTY) {
-            o.rows_numeric[pk] += hs.kcount_heavy[kk];
-            heavy += hs.kcount_heavy[kk];
-        }
+        const long long second = split && kk != K_EMPTY ? hs.kcount_heavy[kk] : 0;
+        o.rows_numeric[pk] += main[kk] + second;
+        if (kk >= NK_PUBLIC) o.rows_scattered_numeric += main[kk] + second;
+        heavy += second;
     }
     o.rows_numeric[K_EMPTY] -= heavy;
 }
@@ -812,7 +812,10 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     o.nnz_b_compressed = comp ? h->hkoff[2] : 0;
     o.n_kinds = NK_PUBLIC;
     int64_t maxrs = 0;
-    for (int kk = 0; kk < NK; ++kk) o.rows_symbolic[kk < NK_PUBLIC ? kk : K_HW] += hs3.kcount_sym[kk];
+    for (int kk = 0; kk < NK; ++kk) {
+        o.rows_symbolic[kk < NK_PUBLIC ? kk : K_HW] += hs3.kcount_sym[kk];
+        if (kk >= NK_PUBLIC) o.rows_scattered_symbolic += hs3.kcount_sym[kk];
+    }
     for (int kk = 0; kk < NK; ++kk) {
         if (kk != K_EMPTY) maxrs = std::max<int64_t>(maxrs, hs3.kmax_num[kk][1]);
         if (kk != K_EMPTY && split) maxrs = std::max<int64_t>(maxrs, hs3.kmax_heavy[kk][1]);
