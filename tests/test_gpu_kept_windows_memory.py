@@ -100,3 +100,27 @@ def test_given_up_for_the_next_plan():
         assert nnz == m and torch.equal(rp, I.row_ptr)
     finally:
         del hog
+
+
+@pytest.mark.parametrize("rows,wide", [(1020, 1020), (1030, 1030), (1030, 1)])
+def test_room_by_the_bound_and_by_the_exact_size(rows, wide):
+    """Rows times the widest window (32768 words) below 2^25 words, past it, and past it for one wide row only."""
+    import torch
+
+    n, lb, na, k = 400, 512, 66, 1 << 20
+    assert (rows * 32_768 > 1 << 25) == (rows > 1024)
+    B = synth.random_csr(n, k, np.full(n, lb), 1)
+    N = synth.random_csr(n, 90_000, np.full(n, lb), 2)  # B's second half: a narrow window
+    B = synth.Csr(2 * n, k, np.concatenate([B.row_ptr, B.nnz + N.row_ptr[1:]]), np.concatenate([B.col_idx, N.col_idx]),
+                  np.concatenate([B.values, N.values]))
+    for r in range(n):  # both ends of the window in every wide row
+        B.col_idx[B.row_ptr[r]], B.col_idx[B.row_ptr[r + 1] - 1] = 0, k - 1
+    rng = np.random.default_rng(3)
+    ci = np.stack([np.sort(rng.choice(n, na, replace=False)) + (0 if i < wide else n) for i in range(rows)])
+    A = synth.Csr(rows, 2 * n, np.arange(0, rows * na + 1, na, dtype=np.int64), ci.reshape(-1).astype(np.int32),
+                  rng.standard_normal(rows * na))
+    ref, S = oracle_ref(A, B)
+    got, h = run(A, B)
+    assert h.stats()["rows_numeric"]["dense_wg"] == rows
+    check_f64(ref, S, got)
+    torch.cuda.empty_cache()
