@@ -94,12 +94,6 @@ __device__ __forceinline__ int64_t lane_val(int64_t v, int src) {  // the lane's
     const uint32_t hi = __builtin_amdgcn_readlane((int)((uint64_t)v >> 32), src);
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d));
-    return v;
-}
-
 // body(row, b, e) for the wavefront's long rows, one at a time: its first row
 // of a step is r0, a row per `group` lanes, rp the row pointers.
 template <typename F>
@@ -708,18 +702,6 @@ __global__ __launch_bounds__(BLK) void k_rowinfo_fin(int nb, const long long *pa
     }
 }
 
-// Inclusive max-scan over the 64 lanes (values >= 0) with DPP lane moves;
-// lane 63 holds the wavefront maximum.
-__device__ __forceinline__ int wave_maxscan_dpp(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
-    return v;
-}
-
 // ------------------------------------------------------------------ classify
 // CL_R rows per lane, CR rows per workgroup (contiguous, so the per-workgroup
 // kind counts are the counts of the stable partition).  Two rows per lane: the
@@ -925,10 +907,6 @@ __global__ __launch_bounds__(CB) void k_classify(int64_t m, const int64_t *rflop
     }
 }
 
-// One workgroup over the nb classify workgroups: per kind the row total and
-// the maxima (into the phase's statistics), the kind offsets koff, and each
-// workgroup's count replaced by its exclusive offset (kinds in order, row order
-// within a kind).  Counts and offsets fit int32 (rows are int32).
 // ------------------------------------------------------------------ partition
 // Beyond PF_FEW classify workgroups, the compact counts are folded once by
 // one workgroup (k_part_fold) instead of by every partition workgroup, whose

@@ -205,11 +205,7 @@ hipError_t bwd_launch(const BwdArgs<VT> &a, const LaunchCfg &c) {
     int rmax = WAVE;
     while (rmax <= a.max_row && rmax < BW_LDS) rmax <<= 1;
     const size_t lds = (4 + sizeof(VT)) * (size_t)rmax;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bwd<VT, IX, U>, WAVE, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int grid = ((per_cu * c.cus) / XCDS) * XCDS;
-    if (grid < XCDS) grid = XCDS;
+    const int grid = resident_grid(k_bwd<VT, IX, U>, WAVE, lds, c.cus);
     hipLaunchKernelGGL((k_bwd<VT, IX, U>), dim3(grid), dim3(WAVE), lds, c.stream, a, rmax);
     return hipGetLastError();
 }

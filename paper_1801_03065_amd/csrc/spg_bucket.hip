@@ -6,8 +6,8 @@
 //
 //   1. every product (column, A value * B value) is loaded once into
 //      registers, U per lane, neighbouring lanes on neighbouring products
-//      (the owner of a product: run starts of the B rows marked in LDS and a
-//      max-scan), so no lane idles past the end of a B row;
+//      (the owner of a product: run starts of the B rows marked in LDS, counted
+//      on the marks), so no lane idles past the end of a B row;
 //   2. the row's column window is cut into as many equal buckets as the
 //      lanes hold products (a monotone map of the column); an LDS counter per
 //      bucket gives every product its place in the bucket, a scan gives each
@@ -17,6 +17,8 @@
 //      at when columns are spread evenly);
 //   4. products of one column are neighbours now: the first of them sums the
 //      run and writes the entry; without repeats the row is written as it is.
+//      (In the order of the bucket counter, which is free over the wavefronts of
+//      a row: sums can differ in their last bits from run to run.)
 //
 // Rows with columns clustered inside the window (a bucket of more than BK_SPLIT
 // products: power-law graphs) cut every bucket again in proportion to its
@@ -60,17 +62,6 @@ __device__ __forceinline__ RowDescB row_desc_b(int i, const int64_t *arp, const 
     d.wlo = w.x;
     d.nw = w.y - w.x + 1;
     return d;
-}
-
-// Inclusive max-scan over the 64 lanes (values >= 0) with DPP lane moves.
-__device__ __forceinline__ int bk_maxscan(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
-    return v;
 }
 
 // Hand-over of LDS data between the lanes of the workgroup.  Both forms wait
@@ -220,7 +211,7 @@ __global__ __launch_bounds__(WAVE * NW) __attribute__((amdgpu_waves_per_eu(4))) 
                 mx = max(mx, (int)cc[u]);
             }
             const int incs = wave_scan_dpp(sum);
-            int run = incs - sum, dp = __builtin_amdgcn_readlane(bk_maxscan(mx), WAVE - 1);
+            int run = incs - sum, dp = __builtin_amdgcn_readlane(wave_maxscan_dpp(mx), WAVE - 1);
             if (NW > 1) {
                 if (l == WAVE - 1) {
                     red[wv] = incs;
@@ -492,26 +483,21 @@ __global__ __launch_bounds__(WAVE * NW) void k_sym_bk(SymArgs a) {
     }
 }
 
+int grid_of(int resident, int64_t rows) {
+    return (int)std::min<int64_t>(resident, std::max<int64_t>(XCDS, (rows + XCDS - 1) / XCDS * XCDS));
+}
+
 template <int NW, int U>
 hipError_t sym_bk_u(const SymArgs &a, const LaunchCfg &c, int64_t rows) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sym_bk<NW, U>, WAVE * NW, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int64_t grid = std::min<int64_t>((int64_t)per_cu * c.cus, rows);
-    grid = std::max<int64_t>(XCDS, (grid + XCDS - 1) / XCDS * XCDS);
-    hipLaunchKernelGGL((k_sym_bk<NW, U>), dim3((unsigned)grid), dim3(WAVE * NW), 0, c.stream, a);
+    const int grid = grid_of(resident_grid(k_sym_bk<NW, U>, WAVE * NW, 0, c.cus), rows);
+    hipLaunchKernelGGL((k_sym_bk<NW, U>), dim3(grid), dim3(WAVE * NW), 0, c.stream, a);
     return hipGetLastError();
 }
 
 template <typename VT, int ACC, int NW, int U>
 hipError_t num_bk_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_num_bk<VT, ACC, NW, U>, WAVE * NW, 0) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    int64_t grid = std::min<int64_t>((int64_t)per_cu * c.cus, rows);
-    grid = std::max<int64_t>(XCDS, (grid + XCDS - 1) / XCDS * XCDS);
-    hipLaunchKernelGGL((k_num_bk<VT, ACC, NW, U>), dim3((unsigned)grid), dim3(WAVE * NW), 0, c.stream, a);
+    const int grid = grid_of(resident_grid(k_num_bk<VT, ACC, NW, U>, WAVE * NW, 0, c.cus), rows);
+    hipLaunchKernelGGL((k_num_bk<VT, ACC, NW, U>), dim3(grid), dim3(WAVE * NW), 0, c.stream, a);
     return hipGetLastError();
 }
 

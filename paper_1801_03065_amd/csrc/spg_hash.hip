@@ -604,16 +604,6 @@ __global__ __launch_bounds__(WG_BIG) void k_num_hl(NumArgs<VT> a) {
     }
 }
 
-template <typename K>
-inline int resident_grid(K kernel, int block, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = per_cu * cus;
-    g = (g / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 }  // namespace
 
 size_t lds_sym_hw(int ts) { return hw_layout(ts, 4, false).total; }

@@ -13,9 +13,9 @@ namespace spg {
 constexpr int WAVE = 64;  // CDNA wavefront width
 constexpr int XCDS = 8;   // accelerator complex dies on the MI355X
 constexpr int WG_BIG = 256;
-// Lanes of the bit-window workgroup kernels (one heavy row per workgroup):
-// their window (up to 128 KB of LDS) leaves room for one workgroup per CU, so
-// the workgroup is large to keep enough loads in flight.
+// Lanes of the window-wide numeric kernel (heavy rows of an unsorted B): its
+// window (up to 128 KB of LDS) leaves room for one workgroup per CU, so the
+// workgroup is large to keep enough loads in flight.
 constexpr int DG_WG = 1024;
 
 // Per row of B: number of entries, number of distinct column-set words
@@ -29,7 +29,8 @@ enum Kind : int {
     K_EMPTY = 0,  // no multiplications: row size 0
     K_DW = 1,     // bit-window dense accumulator, one wavefront per row
     K_HW = 2,     // LDS linear-probing hash, one wavefront per row
-    K_DG = 3,     // bit-window dense accumulator, one 256-lane workgroup per row, values in HBM
+    K_DG = 3,     // heavy rows, one workgroup per row: a bit window over the whole row (512 or 1024 lanes);
+                  // numeric in column segments held in LDS (512), or with values in HBM (1024, unsorted B)
     K_HL = 4,     // two-level hash: LDS level 1 + HBM level 2, one workgroup per row
     K_WH = 5,     // word hash + ordered summary, one wavefront per row (numeric)
     K_SR = 6,     // short rows: a team of T <= 64 lanes per row, several rows per wavefront
@@ -100,7 +101,12 @@ constexpr int SG_CUT = SG_CAP - 32;  // a segment starts at the word holding eac
 // -> 3.05 GB read beyond the L2, 1468 -> 1420 us; new values on 61^3 307 -> 279;
 // batch of 20 random products 2.11 -> 1.95 ms; R-MAT scale 16 6.64 -> 6.47.  Not
 // in k_sr: short rows are the intermediate of Galerkin products, which the next
-// product reads at once (100^3: 808 us, 824 with streamed stores).
+// product reads at once (100^3: 808 us, 824 with streamed stores).  There is no
+// line by size: with C read at once by the next call, streamed against ordinary
+// stores, FP64, 27 points on g^3: A*A then (A*A)*A 92 / 99 us (g = 20), 469 / 472
+// (32), 999 / 996 (40), 2872 / 2945 (56); A*A then A*(A*A) 80 / 85, 390 / 368, 803 /
+// 787, 2462 / 2492; eight random columns a row and the backward 43 / 43, 138 / 134,
+// 252 / 239, 716 / 748.
 template <typename T>
 __device__ __forceinline__ void store_c(T *p, T v) {
     __builtin_nontemporal_store(v, p);
@@ -146,7 +152,7 @@ struct SymArgs {
     const int64_t *plan_off;  // bit-window rows: where the row's (word, bits) pairs go
     const int32_t *plan_len;  // room for pairs per row (0: none stored)
     uint2 *plan;              // nullptr: no pairs stored
-    int b32;                  // nnz(B) < 2^30: B entries addressed with 32-bit byte offsets
+    int b32;                  // nnz(B) < 2^29: B addressed with 32-bit byte offsets (compressed B: 8-byte records)
     int64_t nnzb;             // nnz(B): gathers clamp their offsets to its last entry
     uint32_t *sgb;            // K_DG: the row's bit window is stored at sgb + sgb_off (nullptr: not kept)
     const int64_t *sgb_off;
@@ -276,6 +282,16 @@ __device__ __forceinline__ int wave_scan_dpp(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
     return v;
 }
+// Inclusive maximum over the lanes (values >= 0); lane 63 holds the wavefront's.
+__device__ __forceinline__ int wave_maxscan_dpp(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));  // row_shr:2
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));  // row_shr:4
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));  // row_shr:8
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return v;
+}
 __device__ __forceinline__ long long wave_incl_scan64(long long v) {
     const int l = lane_id();
 #pragma unroll
@@ -376,6 +392,16 @@ struct LaunchCfg {
     int grid;  // persistent workgroups (multiple of 8); 0 = all resident workgroups
     int cus;   // compute units of the device
 };
+
+// Workgroups of `block` lanes (lds: dynamic LDS bytes) that the device holds at
+// once, a multiple of the dies.
+template <typename K>
+inline int resident_grid(K kernel, int block, size_t lds, int cus) {
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    return std::max(XCDS, per_cu * cus / XCDS * XCDS);
+}
 
 // Per row of B: length, distinct column-set words, word window, sortedness
 // (uflag); columns out of [0, ncols) raise the malformed-input flag.

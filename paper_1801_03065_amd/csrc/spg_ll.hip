@@ -156,21 +156,12 @@ __global__ __launch_bounds__(WAVE) void k_num_ll(NumArgs<VT> a) {
     }
 }
 
-template <typename K>
-inline int resident_grid(K kernel, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, WAVE, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = (per_cu * cus / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 template <typename VT, int ACC, int LGG>
 hipError_t num_ll_g(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
     using S = typename Accum<VT, ACC>::store_t;
     constexpr int NG = WAVE >> LGG;
     const size_t lds = ll_layout(a.ts, a.r_max, NG, sizeof(S)).total;
-    int grid = c.grid > 0 ? c.grid : resident_grid(k_num_ll<VT, ACC, LGG>, lds, c.cus);
+    int grid = c.grid > 0 ? c.grid : resident_grid(k_num_ll<VT, ACC, LGG>, WAVE, lds, c.cus);
     const int64_t need = (rows + NG - 1) / NG;
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((need + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_num_ll<VT, ACC, LGG>), dim3(grid), dim3(WAVE), lds, c.stream, a);

@@ -373,22 +373,13 @@ __global__ __launch_bounds__(MK_CB) void k_mask_class(int64_t m, int64_t n, cons
     if (k) rows[(int64_t)(k - 1) * m + sb[k - 1] + my] = (int32_t)i;
 }
 
-template <typename K>
-inline int resident(K kernel, int block, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = (per_cu * cus / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 template <typename VT, typename IX, int NW, bool BIG>
 hipError_t mask_ix(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCfg &c) {
     int lg = 4;
     while ((1 << lg) < 2 * mmax) ++lg;
     const size_t lds = mk_layout(NW * WAVE, lg, mmax, BIG).total;
     const int64_t rows = a.nrows + (BIG ? a.nrows3 : 0);
-    int grid = BIG ? c.grid : resident(k_mask<VT, IX, NW, BIG>, NW * WAVE, lds, c.cus);
+    int grid = BIG ? c.grid : resident_grid(k_mask<VT, IX, NW, BIG>, NW * WAVE, lds, c.cus);
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((rows + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_mask<VT, IX, NW, BIG>), dim3(grid), dim3(NW * WAVE), lds, c.stream, a, lg, mmax, queue);
     return hipGetLastError();

@@ -26,7 +26,10 @@ namespace {
 
 constexpr int PL_U = 16;  // products per lane held in registers (fast path)
 // FP64 entries of B from which a wavefront takes its rows in chunks of four
-// (see k_num_pl): its 12-byte entries then exceed 200 MB.
+// (see k_num_pl): its 12-byte entries then exceed 200 MB.  27 points on g^3, new
+// values, chunks of four / single rows: 61^3 (5.9M entries) 282 / 275 us, 68^3 392 /
+// 378, 74^3 470 / 497, 80^3 702 / 707, 86^3 (16.8M) 883 / 885, 92^3 1080 / 1094, 100^3
+// 1392 / 1408, 110^3 1853 / 1879.
 constexpr int64_t PL_CH_NNZ = int64_t(1) << 24;
 
 // Staged A entry: one 16-byte LDS record, so a product reads its A value and
@@ -103,8 +106,8 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     // thirds), so chunks of four cut the traffic beyond the L2 (27-point A*A on
     // 100^3: by 44% before C was streamed past it) but let the wavefronts of a
     // die drift apart and leave some idle in small launches.  Measured, chunks
-    // of 4 / single rows: FP64 100^3 1409 / 1420 us, 61^3 301 / 292, 20^3 36 / 32;
-    // FP32 100^3 1410 / 1361, 61^3 340 / 321.
+    // of 4 / single rows: FP64 100^3 1392 / 1408 us, 61^3 282 / 275, 20^3 36 / 32 (more
+    // sizes at PL_CH_NNZ); FP32 100^3 1410 / 1361, 61^3 340 / 321.
     const Slice sl = xcd_slice(lo, hi, CH, 0);
 
     // Software pipeline over the wavefront's rows p, p+s, p+2s, ... (p+s: the
@@ -372,16 +375,6 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
         // gathers; the offsets are clamped into B whatever the records hold)
         gather(b ^ 1);
     }
-}
-
-template <typename K>
-inline int resident_grid(K kernel, int block, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = per_cu * cus;
-    g = (g / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
 }
 
 template <typename VT, int ACC, int LGS, int CH>

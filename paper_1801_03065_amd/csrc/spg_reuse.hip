@@ -382,19 +382,10 @@ __global__ __launch_bounds__(WAVE) void k_num_map(NumArgs<VT> a) {
     });
 }
 
-template <typename K>
-inline int resident_grid(K kernel, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, WAVE, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = (per_cu * cus / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 template <int LGT, int LGS>
 hipError_t posmap_ts(const NumArgs<double> &a, const int32_t *cci, const LaunchCfg &c, int64_t rows) {
     constexpr int NT = WAVE >> LGT;
-    int grid = resident_grid(k_posmap<LGT, LGS>, 0, c.cus);
+    int grid = resident_grid(k_posmap<LGT, LGS>, WAVE, 0, c.cus);
     const int64_t need = (rows + NT - 1) / NT;
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((need + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_posmap<LGT, LGS>), dim3(grid), dim3(WAVE), 0, c.stream, a, cci);
@@ -406,7 +397,7 @@ hipError_t num_map_ts(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
     using S = typename Accum<VT, ACC>::store_t;
     constexpr int NT = WAVE >> LGT;
     const size_t lds = map_layout(a.r_max, NT, sizeof(S)).total;
-    int grid = resident_grid(k_num_map<VT, ACC, LGT, LGS>, lds, c.cus);
+    int grid = resident_grid(k_num_map<VT, ACC, LGT, LGS>, WAVE, lds, c.cus);
     const int64_t need = (rows + NT - 1) / NT;
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((need + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_num_map<VT, ACC, LGT, LGS>), dim3(grid), dim3(WAVE), lds, c.stream, a);
@@ -442,7 +433,7 @@ hipError_t posmap_flat(NumArgs<double> a, const int32_t *cci, const LaunchCfg &c
     int r = 2 * WAVE;
     while (r <= a.r_max) r *= 2;
     a.r_max = r;
-    int grid = resident_grid(k_posmap_flat<IX, 4>, 4 * (size_t)r, c.cus);
+    int grid = resident_grid(k_posmap_flat<IX, 4>, WAVE, 4 * (size_t)r, c.cus);
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((rows + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_posmap_flat<IX, 4>), dim3(grid), dim3(WAVE), 4 * (size_t)r, c.stream, a, cci);
     return hipGetLastError();
@@ -451,7 +442,7 @@ hipError_t posmap_flat(NumArgs<double> a, const int32_t *cci, const LaunchCfg &c
 template <typename VT, int ACC, typename IX, int U>
 hipError_t map_flat_u(const NumArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
     const size_t lds = align16(sizeof(typename Accum<VT, ACC>::store_t) * (size_t)a.r_max);
-    int grid = resident_grid(k_map_flat<VT, ACC, IX, U>, lds, c.cus);
+    int grid = resident_grid(k_map_flat<VT, ACC, IX, U>, WAVE, lds, c.cus);
     grid = (int)std::min<int64_t>(grid, std::max<int64_t>(XCDS, ((rows + XCDS - 1) / XCDS) * XCDS));
     hipLaunchKernelGGL((k_map_flat<VT, ACC, IX, U>), dim3(grid), dim3(WAVE), lds, c.stream, a);
     return hipGetLastError();

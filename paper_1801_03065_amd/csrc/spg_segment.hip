@@ -54,8 +54,8 @@ namespace spg {
 namespace {
 
 constexpr int SG_U = 8;  // products per lane per round of the flat walks (loads in flight)
-// Lanes per workgroup (one heavy row).  LDS (~76 KB) allows two workgroups
-// per CU; 512 lanes rather than 256 double the loads in flight per CU for the
+// Lanes per workgroup (one heavy row).  LDS (47 to 67 KB) and registers allow two
+// workgroups per CU; 512 lanes rather than 256 double the loads in flight per CU for the
 // same LDS, with registers held to 128 (4 waves per SIMD).
 constexpr int SG_WG = 512;
 
@@ -477,25 +477,15 @@ hipError_t num_sg_impl(const NumArgs<VT> &a, const LaunchCfg &c) {
     return hipGetLastError();
 }
 
-template <typename K>
-int resident(K kernel, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, SG_WG, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = per_cu * cus;
-    g = (g / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 }  // namespace
 
 int sg_resident_grid(int acc, int acc2, bool dbl, int cus) {
-    if (dbl) return resident(k_num_sg<double, ACC_NATIVE, ACC_NATIVE, int64_t>, cus);
-    if (acc2 == ACC_WIDE && acc == ACC_NATIVE) return resident(k_num_sg<float, ACC_NATIVE, ACC_WIDE, int64_t>, cus);
-    if (acc2 == ACC_WIDE && acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_WIDE, int64_t>, cus);
-    if (acc == ACC_COMP) return resident(k_num_sg<float, ACC_COMP, ACC_COMP, int64_t>, cus);
-    if (acc == ACC_WIDE) return resident(k_num_sg<float, ACC_WIDE, ACC_WIDE, int64_t>, cus);
-    return resident(k_num_sg<float, ACC_NATIVE, ACC_NATIVE, int64_t>, cus);
+    if (dbl) return resident_grid(k_num_sg<double, ACC_NATIVE, ACC_NATIVE, int64_t>, SG_WG, 0, cus);
+    if (acc2 == ACC_WIDE && acc == ACC_NATIVE) return resident_grid(k_num_sg<float, ACC_NATIVE, ACC_WIDE, int64_t>, SG_WG, 0, cus);
+    if (acc2 == ACC_WIDE && acc == ACC_COMP) return resident_grid(k_num_sg<float, ACC_COMP, ACC_WIDE, int64_t>, SG_WG, 0, cus);
+    if (acc == ACC_COMP) return resident_grid(k_num_sg<float, ACC_COMP, ACC_COMP, int64_t>, SG_WG, 0, cus);
+    if (acc == ACC_WIDE) return resident_grid(k_num_sg<float, ACC_WIDE, ACC_WIDE, int64_t>, SG_WG, 0, cus);
+    return resident_grid(k_num_sg<float, ACC_NATIVE, ACC_NATIVE, int64_t>, SG_WG, 0, cus);
 }
 
 template <>

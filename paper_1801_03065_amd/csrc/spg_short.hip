@@ -43,7 +43,6 @@ struct SrArgs {
     int32_t *row_nnz;    // symbolic only
     int32_t *row_words;  // symbolic only (row size as the word bound)
     RowSet rs;
-    int lg_t;
     DevStats *st;
 };
 
@@ -97,13 +96,7 @@ __device__ __forceinline__ void team_sort(KEY &key, int q, int P) {
 
 // Largest value (>= 0) of the 64 lanes, uniform.
 __device__ __forceinline__ int sr_wave_max(int v) {
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
-    return __builtin_amdgcn_readlane(v, WAVE - 1);
+    return __builtin_amdgcn_readlane(wave_maxscan_dpp(v), WAVE - 1);
 }
 // Value of the team's last lane.
 template <int LG>
@@ -155,14 +148,14 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         abc = a.arp[ic];
         aec = a.arp[ic + 1];
     }
-    int jc = 0, lenc = 0;
+    int lenc = 0;
     int64_t b0c = 0;
     VT avc = VT(0);
     if (q < aec - abc) {
-        jc = a.aci[abc + q];
+        const int j = a.aci[abc + q];
         if (NUM) avc = a.aval[abc + q];
-        b0c = a.brp[jc];
-        lenc = (int)(a.brp[jc + 1] - b0c);
+        b0c = a.brp[j];
+        lenc = (int)(a.brp[j + 1] - b0c);
     }
     int in = row_of(g + sl.step);
     int64_t abn = 0, aen = 0;
@@ -323,7 +316,6 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         ic = in;
         abc = abn;
         aec = aen;
-        jc = jn;
         avc = avn;
         b0c = b0n;
         lenc = lenn;
@@ -334,20 +326,11 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     }
 }
 
-template <typename K>
-int sr_grid(K kernel, int cus, int64_t groups) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, WAVE, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int64_t g = (int64_t)per_cu * cus;
-    g = std::min<int64_t>(g, ((groups + XCDS - 1) / XCDS) * XCDS);
-    g = (g / XCDS) * XCDS;
-    return (int)(g < XCDS ? XCDS : g);
-}
-
 template <bool NUM, typename VT, int ACC, int LG, bool PACK>
 hipError_t sr_pack(const SrArgs<VT> &a, const LaunchCfg &c, int64_t rows) {
-    const int grid = c.grid > 0 ? c.grid : sr_grid(k_sr<NUM, VT, ACC, LG, PACK>, c.cus, rows >> (6 - LG));
+    const int64_t groups = (rows >> (6 - LG)) + XCDS - 1;
+    const int grid = c.grid > 0 ? c.grid : (int)std::min<int64_t>(resident_grid(k_sr<NUM, VT, ACC, LG, PACK>, WAVE, 0, c.cus),
+                                                                  std::max<int64_t>(XCDS, groups / XCDS * XCDS));
     hipLaunchKernelGGL((k_sr<NUM, VT, ACC, LG, PACK>), dim3(grid), dim3(WAVE), 0, c.stream, a);
     return hipGetLastError();
 }
@@ -370,7 +353,6 @@ hipError_t num_sr_impl(const NumArgs<VT> &n, int lg_t, const LaunchCfg &c, int64
     a.cval = n.cval;
     a.cbase_row = n.cbase_row;
     a.rs = n.rs;
-    a.lg_t = lg_t;
     a.st = n.st;
     const bool pack = n.b32 && n.ncols <= (int64_t(1) << 26);
     if (lg_t <= 3) return num_sr_lg<VT, ACC, 3>(a, pack, c, rows);
@@ -397,7 +379,6 @@ hipError_t launch_sym_sr(const SymArgs &s, int lg_t, const LaunchCfg &c, int64_t
     a.row_nnz = s.row_nnz;
     a.row_words = s.row_words;
     a.rs = s.rs;
-    a.lg_t = lg_t;
     a.st = s.st;
     a.cbase_row = -1;
     if (lg_t <= 3) return sym_sr_lg<3>(a, s.b32, c, rows);

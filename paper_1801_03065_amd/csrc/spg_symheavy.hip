@@ -225,13 +225,8 @@ __global__ __launch_bounds__(WG) void k_sym_dg(SymArgs a) {
 template <bool COMP, typename IX, int WG>
 hipError_t sym_dg_wg(const SymArgs &a, const LaunchCfg &c) {
     const size_t lds = sh_layout(a.nw_max, WG, sizeof(IX)).total;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sym_dg<COMP, IX, WG>, WG, lds) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    int grid = per_cu * c.cus;
-    if (c.grid > 0) grid = std::min(grid, c.grid);
-    grid = std::max(XCDS, grid / XCDS * XCDS);
+    int grid = resident_grid(k_sym_dg<COMP, IX, WG>, WG, lds, c.cus);
+    if (c.grid > 0) grid = std::max(XCDS, std::min(grid, c.grid) / XCDS * XCDS);
     hipLaunchKernelGGL((k_sym_dg<COMP, IX, WG>), dim3(grid), dim3(WG), lds, c.stream, a);
     return hipGetLastError();
 }

@@ -352,16 +352,6 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) vo
     }
 }
 
-template <typename K>
-inline int resident_grid(K kernel, int block, size_t lds, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int g = per_cu * cus;
-    g = (g / XCDS) * XCDS;
-    return g < XCDS ? XCDS : g;
-}
-
 template <typename VT, int ACC>
 hipError_t num_wh_impl(const NumArgs<VT> &a, const LaunchCfg &c) {
     const size_t lds = lds_num_wh(a.ts, a.nw_max, a.r_max, sizeof(typename Accum<VT, ACC>::store_t));
