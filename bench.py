@@ -44,9 +44,9 @@ TRAFFIC = {
     "kernel": "k_num_pl",
     "sources": ["paper_1801_03065_amd/csrc/spg_plan.hip", "paper_1801_03065_amd/csrc/spg_internal.hpp",
                 "paper_1801_03065_amd/csrc/spg_accum.hpp"],
-    "sha256": "b2da5714b7c246fdd93305f944677305a793844120bf9e16e494bfa975a8c55c",
-    "read_bytes": 2.8459e9,
-    "write_bytes": 1.6061e9,
+    "sha256": "75fe36063c42c62e8219c5762834f11e71879389d5f1fc67bfdc66cb79a69483",
+    "read_bytes": 2.8712e9,
+    "write_bytes": 1.6070e9,
 }
 
 

@@ -10,11 +10,11 @@
 // staged in LDS when they fit), sums dA(i,k) over the lanes of a run by a
 // segmented scan in FP64 and adds dB(k,j) with hardware atomics in HBM.
 //
-// Bound by latency (loads, then the search's LDS reads), so by the lanes and
-// searches in flight: U searches per lane advance together, and LDS is sized
-// by the longest row of C, so short rows leave room for 32 wavefronts per CU.
-// Backward of 7-point 64^3 times 16 random columns a row (2.9e7
-// multiplications, FP32): 273 us; with lane groups per B row, one search at a
+// Bound by the vector-memory path (its data unit 90% busy: a column and a value
+// loaded and an atomic sent per product) with the VALU at 69%.  U searches per
+// lane advance together, and LDS is sized by the longest row of C, so short rows
+// leave room for 32 wavefronts per CU.  Backward of 7-point 64^3 times 16 random
+// columns a row (2.9e7 multiplications, FP32): 273 us; with lane groups per B row, one search at a
 // time and 16 KB of LDS per wavefront it took 1050 us.  (Sums over a run by LDS
 // atomics would cost 190 cycles per 64 products: the lanes of a run share
 // one address.)

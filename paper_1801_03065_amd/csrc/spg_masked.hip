@@ -22,8 +22,9 @@
 // of the chip idle in a launch of their own.
 //
 // Bound by the latency of a product's column load and table read, so by
-// products in flight.  Triangles of an R-MAT graph, scale 18, 2.6M edges, 5.2e8
-// products: 2.0 ms in the two launches, 0.26 products a ps; with lane groups per B row, one load
+// products in flight: no unit is busy (VALU 31 to 36%, LDS 12 to 17, data unit 28
+// to 33; 50 to 61% of the wave cycles wait).  Triangles of an R-MAT graph, scale
+// 18, 2.6M edges, 5.2e8 products: 2.0 ms in the two launches, 0.26 products a ps; with lane groups per B row, one load
 // in flight and one wavefront for any row of up to 512 mask entries it took 22
 // ms (a group of 16 lanes waited for the longest of four B rows, and one
 // wavefront held rows of 1e6 products).

@@ -17,7 +17,8 @@
 // row's A entries and B extents load while the current row is processed.
 //
 // Bound by random lines of B past the L2 where B is large (1.5M rows of 7
-// random entries: symbolic 5.2 TB/s), else by latency.  Numeric, the same
+// random entries: 5.1 TB/s symbolic, 6.2 numeric), else by the vector-memory data
+// unit (Galerkin products on 100^3: 82 to 93% busy).  Numeric, the same
 // product: 1032 us with a hash of the products, sorted (column, slot) pairs
 // after it; 665 us now.  Galerkin products on 100^3, both: 394 -> 343 us; 7-point
 // 100^3: 699 -> 606 us.  (Symbolic, sorting took 428 us and the hash 379.)
