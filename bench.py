@@ -44,7 +44,7 @@ TRAFFIC = {
     "kernel": "k_num_pl",
     "sources": ["paper_1801_03065_amd/csrc/spg_plan.hip", "paper_1801_03065_amd/csrc/spg_internal.hpp",
                 "paper_1801_03065_amd/csrc/spg_accum.hpp"],
-    "sha256": "75fe36063c42c62e8219c5762834f11e71879389d5f1fc67bfdc66cb79a69483",
+    "sha256": "c98a4ea3ddfb98f74de371302280d1185db6ece209f38c29244fac63b27e5677",
     "read_bytes": 2.8712e9,
     "write_bytes": 1.6070e9,
 }

@@ -26,20 +26,41 @@ __device__ __forceinline__ int64_t rp_at(const RpCopy &c, int64_t i) {
     return c.is64 ? ((const int64_t *)c.src)[i] : (int64_t)((const int32_t *)c.src)[i];
 }
 // Both operands' row pointers in one launch: entries [0, a.n1) are A's, the
-// rest B's.
-__global__ __launch_bounds__(BLK) void k_copy_rp(RpCopy a, RpCopy b, int *bad) {
+// rest B's.  LEN: longest[0] becomes at least the longest row of B, longest[1] A's.
+template <bool LEN>
+__global__ __launch_bounds__(BLK) void k_copy_rp(RpCopy a, RpCopy b, int *bad, int *longest) {
     const int64_t tot = a.n1 + b.n1;
+    int lens[2] = {0, 0};
     for (int64_t t = (int64_t)blockIdx.x * BLK + threadIdx.x; t < tot; t += (int64_t)gridDim.x * BLK) {
         const bool isa = t < a.n1;
         const RpCopy &c = isa ? a : b;
         const int64_t i = isa ? t : t - a.n1;
         const int64_t v = rp_at(c, i);
-        if ((i == 0 && v != 0) || (i > 0 && v < rp_at(c, i - 1)) || (i == c.n1 - 1 && v != c.nnz))
-            atomicOr(bad, 1);
+        const int64_t before = i > 0 ? rp_at(c, i - 1) : 0;
+        if ((i == 0 && v != 0) || (i > 0 && v < before) || (i == c.n1 - 1 && v != c.nnz)) atomicOr(bad, 1);
+        if (LEN) {
+            const int len = (int)min(max(v - before, (int64_t)0), (int64_t)INT_MAX);
+            lens[0] = max(lens[0], isa ? 0 : len);
+            lens[1] = max(lens[1], isa ? len : 0);
+        }
         // the copy is clamped to [0, nnz]: every row range read through it is
         // empty or inside the arrays, so the analysis kernels that run before
         // the host sees the flag cannot read out of bounds
         c.dst[i] = min(max(v, (int64_t)0), c.nnz);
+    }
+    if (LEN) {  // one atomic per workgroup and operand
+        __shared__ int wmax[2][BLK / WAVE];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int len = wave_maxscan_dpp(lens[q]);
+            if (lane_id() == WAVE - 1) wmax[q][threadIdx.x / WAVE] = len;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            int len = 0;
+            for (int w = 0; w < BLK / WAVE; ++w) len = max(len, wmax[threadIdx.x][w]);
+            if (len > *(volatile int *)&longest[threadIdx.x]) atomicMax(&longest[threadIdx.x], len);
+        }
     }
 }
 
@@ -1247,9 +1268,14 @@ inline int grid_for(int64_t work, int per_block, int cap = 65536) {
 }  // namespace
 
 hipError_t launch_copy_rp(int64_t n1a, const void *srca, int is64a, int64_t nnza, int64_t *dsta, int64_t n1b,
-                          const void *srcb, int is64b, int64_t nnzb, int64_t *dstb, int *bad, hipStream_t s) {
+                          const void *srcb, int is64b, int64_t nnzb, int64_t *dstb, int *bad, hipStream_t s,
+                          int *longest) {
     const RpCopy a{srca, is64a, n1a, nnza, dsta}, b{srcb, is64b, n1b, nnzb, dstb};
-    hipLaunchKernelGGL(k_copy_rp, dim3(grid_for(n1a + n1b, BLK)), dim3(BLK), 0, s, a, b, bad);
+    // (with the maxima 1024 workgroups: the first of them, up to 2048 resident ones,
+    // find the counters at zero and queue on one address)
+    const dim3 g(grid_for(n1a + n1b, BLK, longest ? 1024 : 65536));
+    if (longest) hipLaunchKernelGGL(k_copy_rp<true>, g, dim3(BLK), 0, s, a, b, bad, longest);
+    else hipLaunchKernelGGL(k_copy_rp<false>, g, dim3(BLK), 0, s, a, b, bad, longest);
     return hipGetLastError();
 }
 

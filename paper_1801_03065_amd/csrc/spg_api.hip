@@ -1566,25 +1566,25 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
     HIPCHK(need(h, h->mk_arp, 8 * (m + 1)));
     HIPCHK(need(h, h->mk_brp, 8 * (n + 1)));
     HIPCHK(need(h, h->mk_mrp, 8 * (m + 1)));
-    HIPCHK(need(h, h->mk_rows, 12 * std::max<int64_t>(m, 1)));
-    HIPCHK(need(h, h->mk_cnt, 8 * sizeof(int)));
-    // [0..2] rows per kind, [3..5] longest mask row per kind, [6] bad input, [7] row queue
-    int *cnt = h->mk_cnt.as<int>(), *bad = cnt + 6;
+    HIPCHK(need(h, h->mk_rows, 4 * ML_N * std::max<int64_t>(m, 1)));
+    HIPCHK(need(h, h->mk_cnt, 16 * sizeof(int)));
+    // rows per list, longest mask row per list, bad input, row queue, longest rows of B and A
+    int *cnt = h->mk_cnt.as<int>(), *bad = cnt + 2 * ML_N, *queue = bad + 1, *longest = bad + 2;
     int32_t *rows = h->mk_rows.as<int32_t>();
-    HIPCHK(launch_fill_i32(cnt, 8, 0, st));
+    HIPCHK(launch_fill_i32(cnt, 16, 0, st));
     HIPCHK(launch_copy_rp(m + 1, A->row_ptr, A->rp_type == SPG_I64, A->nnz, h->mk_arp.as<int64_t>(), n + 1,
-                          B->row_ptr, B->rp_type == SPG_I64, B->nnz, h->mk_brp.as<int64_t>(), bad, st));
+                          B->row_ptr, B->rp_type == SPG_I64, B->nnz, h->mk_brp.as<int64_t>(), bad, st, longest));
     HIPCHK(launch_copy_rp(m + 1, M->row_ptr, M->rp_type == SPG_I64, M->nnz, h->mk_mrp.as<int64_t>(), 0, nullptr, 0,
                           0, nullptr, bad, st));
     if (M->nnz > 0) HIPCHK(launch_fill_i32((int32_t *)out, M->nnz * (int64_t)(sizeof(VT) / 4), 0, st));
     // (row pointers are clamped copies and out-of-range columns are skipped, so
     // this stays in bounds on malformed input)
     HIPCHK(launch_mask_class(m, n, h->mk_arp.as<int64_t>(), A->col_idx, h->mk_brp.as<int64_t>(),
-                             h->mk_mrp.as<int64_t>(), rows, cnt, st));
-    int *hc = (int *)(h->hkoff + 8);
-    HIPCHK(hipMemcpyAsync(hc, cnt, 7 * sizeof(int), hipMemcpyDeviceToHost, st));
+                             h->mk_mrp.as<int64_t>(), longest, rows, cnt, st));
+    int *hc = (int *)(h->hkoff + 8), *hbad = hc + 2 * ML_N;
+    HIPCHK(hipMemcpyAsync(hc, cnt, (2 * ML_N + 4) * sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (hc[6]) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: row_ptr out of range or not monotone");
+    if (*hbad) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: row_ptr out of range or not monotone");
     MaskArgs<VT> a{};
     a.arp = h->mk_arp.as<int64_t>();
     a.aci = A->col_idx;
@@ -1601,30 +1601,46 @@ static spg_status masked_impl(spg_handle h, const spg_csr *A, const spg_csr *B, 
     a.structural = structural;
     a.bad = bad;
     LaunchCfg lc{st, 0, h->cus};
-    if (hc[1] + hc[2] > 0) {  // workgroup rows, the heaviest first
-        a.rows = rows + m;
-        a.nrows = hc[1];
-        a.rows3 = rows + 2 * m;
-        a.nrows3 = hc[2];
-        if (hc[2] > 0) {
-            a.arena_cap = pow2_at_least(2 * (int64_t)hc[5], 64);
+    const MaskPlan plan = mask_plan(hc);
+    const MaskWalk mw = mask_group(hc[2 * ML_N + 2], hc[2 * ML_N + 3], m, A->nnz);
+    a.walk = mw.walk;
+    a.lg_gs = mw.lg_gs;
+    // the lists' rows into the launch's arguments; returns the longest mask row in LDS
+    auto take = [&](const int *lists, int count) {
+        int mmax = 0;
+        int64_t end = 0;
+        for (int q = 0; q < 4; ++q) {
+            if (q < count) {
+                a.rows[q] = rows + lists[q] * m;
+                end += hc[lists[q]];
+                if (lists[q] != ML_HBM) mmax = std::max(mmax, hc[ML_N + lists[q]]);
+            }
+            a.end[q] = end;
+        }
+        return mmax;
+    };
+    if (plan.wgs > 0) {  // workgroup rows, the longest first
+        const int mmax = take(plan.wg, plan.wgs);
+        if (hc[ML_HBM] > 0) {
+            a.nrows3 = hc[ML_HBM];
+            a.arena_cap = pow2_at_least(2 * (int64_t)hc[ML_N + ML_HBM], 64);
             lc.grid = 2 * h->cus / XCDS * XCDS;
-            a.arena_slices = std::min(hc[2], lc.grid);
+            a.arena_slices = (int)std::min<int64_t>(a.nrows3, lc.grid);
             HIPCHK(need(h, h->mk_arena, (size_t)12 * a.arena_cap * a.arena_slices));
             a.arena = h->mk_arena.p;
         }
-        HIPCHK(launch_mask<VT>(a, hc[4], cnt + 7, lc));
-    }
-    if (hc[0] > 0) {  // wavefront rows
-        a.rows = rows;
-        a.nrows = hc[0];
+        HIPCHK(launch_mask<VT>(a, mmax, queue, lc));
         a.nrows3 = 0;
-        HIPCHK(launch_mask<VT>(a, hc[3], nullptr, lc));
     }
-    HIPCHK(hipMemcpyAsync(hc + 6, bad, sizeof(int), hipMemcpyDeviceToHost, st));
+    for (int w = 0; w < 2; ++w)
+        if (plan.waves[w] > 0) {
+            const int mmax = take(plan.wave[w], plan.waves[w]);
+            HIPCHK(launch_mask<VT>(a, mmax, nullptr, lc));
+        }
+    HIPCHK(hipMemcpyAsync(hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (hc[6] & 1) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: a column index out of range");
-    if (hc[6]) return fail(h, SPG_ERR_INTERNAL, "masked product: arena too small");
+    if (*hbad & 1) return fail(h, SPG_ERR_INVALID_ARG, "malformed CSR: a column index out of range");
+    if (*hbad) return fail(h, SPG_ERR_INTERNAL, "masked product: arena too small");
     return SPG_OK;
 }
 

@@ -427,8 +427,10 @@ hipError_t launch_rowinfo(int64_t m, int64_t n, const int64_t *arp, const int32_
                           int selector, double cf_threshold, hipStream_t s);
 // Row pointers of A and B (int32 or int64) copied to int64, clamped to
 // [0, nnz], with a monotonicity / end check into *bad: one launch for both.
+// longest (nullable, zeroed): the longest rows of B and A.
 hipError_t launch_copy_rp(int64_t n1a, const void *srca, int is64a, int64_t nnza, int64_t *dsta, int64_t n1b,
-                          const void *srcb, int is64b, int64_t nnzb, int64_t *dstb, int *bad, hipStream_t s);
+                          const void *srcb, int is64b, int64_t nnzb, int64_t *dstb, int *bad, hipStream_t s,
+                          int *longest = nullptr);
 
 // Exclusive scan: out[0..n] (n+1 entries) of in[0..n), int64 result.
 // tmp must hold scan_tmp_elems(n) int64.
@@ -553,29 +555,48 @@ struct MaskArgs {
     const int64_t *mrp;
     const int32_t *mci;
     VT *out;               // nnz(M), M's entry order
-    const int32_t *rows;   // rows of this launch
-    int64_t nrows;
-    const int32_t *rows3;  // rows of kind 3 (taken first, workgroup launch)
-    int64_t nrows3;
+    const int32_t *rows[4];  // rows of this launch: up to four lists, taken one after the other
+    int64_t end[4];          // rows up to the end of each list
+    int64_t nrows3;          // the first rows whose table is in the arena (workgroup launch)
     int64_t n, k;          // A's columns < n, B's and M's < k
     int64_t nnzb;
     int structural;
-    void *arena;           // rows of kind 3: 12 B per slot, arena_slices slices
+    int walk, lg_gs;       // wavefront launches: MaskWalks, log2 of the lanes per B row
+    void *arena;           // 12 B per slot, arena_slices slices
     int64_t arena_cap;     // slots per slice (power of two >= 2 x longest mask row)
-    int arena_slices;      // min(rows of kind 3, workgroups of the launch)
+    int arena_slices;      // min(nrows3, workgroups of the launch)
     int *bad;              // bit 0: a column out of range, bit 1: arena too small
 };
-// Mask rows of a wavefront: length (its table and accumulators leave room for
-// 20 wavefronts per CU) and multiplications (a wavefront forms about 0.4 a ns,
-// so MK_F bounds a row at 20 us); length of a workgroup's mask row in LDS.
-constexpr int MW_MAX = 256, MK_F = 8192, MG_MAX = 2048;
-// rows: 3 lists of m; cnt: rows per kind (3), longest mask row per kind (3).
+// Lists of masked rows (k_mask_class), in this order in rows (m entries each) and
+// cnt (rows per list, then longest mask row per list).
+enum MaskList : int {
+    ML_SHORT = 0,      // up to MW_MAX mask entries and MK_LIGHT multiplications
+    ML_SHORT_MID = 1,  //   and MK_F multiplications
+    ML_LONG = 2,       // up to MW_LONG mask entries, the same
+    ML_LONG_MID = 3,
+    ML_WG = 4,         // up to MG_MAX mask entries: a workgroup, table in LDS
+    ML_HBM = 5,        // longer: a workgroup, table in the arena
+    ML_N = 6
+};
+enum MaskWalks : int { MK_FLAT = 0, MK_GROUPS = 1, MK_EITHER = 2 };
 hipError_t launch_mask_class(int64_t m, int64_t n, const int64_t *arp, const int32_t *aci, const int64_t *brp,
-                             const int64_t *mrp, int32_t *rows, int *cnt, hipStream_t s);
-// Without a queue: kind 1 (wavefront rows); with one (a zeroed counter): kinds 3
-// and 2.  mmax: longest mask row of kind 1 or 2; c.grid: workgroups (with kind 3).
+                             const int64_t *mrp, const int *longest, int32_t *rows, int *cnt, hipStream_t s);
+// Without a queue: a wavefront per row; with one (a zeroed counter): a workgroup.
+// mmax: longest mask row held in LDS; c.grid: workgroups (with arena rows).
 template <typename VT>
 hipError_t launch_mask(const MaskArgs<VT> &a, int mmax, int *queue, const LaunchCfg &c);
+// The launches of the counted lists (n rows each): the lists each one takes, in order.
+struct MaskPlan {
+    int wg[4], wgs;           // workgroup launch: lists
+    int wave[2][4], waves[2]; // up to two wavefront launches: lists
+};
+// How the wavefront launches walk a row's products, and log2 of the lanes per B row
+// (longest_b, longest_a: longest rows of B and A; m, nnza: A).
+struct MaskWalk {
+    int walk, lg_gs;
+};
+MaskWalk mask_group(int longest_b, int longest_a, int64_t m, int64_t nnza);
+MaskPlan mask_plan(const int *n);
 
 // Kinds whose rows get position maps: every row fits 2048 entries (16-bit ranks).
 constexpr int MAP_KINDS[] = {K_SR, K_DW, K_WH, K_HW, K_BK0, K_BK1, K_BK2, K_BK3, K_BK4};
