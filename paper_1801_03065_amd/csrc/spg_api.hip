@@ -82,6 +82,7 @@ struct spg_handle_s {
     bool compressed = false;
     double avg_len = 1, avg_len_c = 1;  // B entries (raw / compressed) read per A entry
     DevStats *hst = nullptr;            // pinned host copy of the device counters
+    bool flags_set = false;             // the statistics' flags on the device hold values (a symbolic phase began)
     int64_t *hkoff = nullptr;           // pinned totals: [0] nnz(C), [1] stored-structure pairs, [2] pairs of
                                         // compressed B, [3] mapped products, [4] kept window words, [5] error flags
     bool planned = false;               // the symbolic phase stored row structure (K_PL rows)
@@ -436,8 +437,9 @@ spg_status spg_check_errors(spg_handle h) {
     static_assert(offsetof(DevStats, overflow) == offsetof(DevStats, mismatch) + sizeof(int), "copied together");
     int *flags = (int *)(h->hkoff + 5);
     char *dev = (char *)h->dstats.p + offsetof(DevStats, mismatch);
-    HIPCHK(hipMemcpyAsync(flags, dev, 2 * sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    if (h->flags_set) HIPCHK(hipMemcpyAsync(flags, dev, 2 * sizeof(int), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
+    if (!h->flags_set) return SPG_OK;
     const int mism = flags[0], ovf = flags[1];
     if (mism || ovf) {
         HIPCHK(hipMemsetAsync(dev, 0, 2 * sizeof(int), h->stream));
@@ -856,6 +858,7 @@ spg_status spgemm_symbolic(spg_handle h, const spg_csr *A, const spg_csr *B, voi
     if ((s = plan_buffers(h, m, n, B->nnz)) != SPG_OK) return s;
     DevStats *dst = h->dstats.as<DevStats>();
     HIPCHK(launch_fill_i32((int32_t *)dst, (int64_t)(sizeof(DevStats) / 4), 0, st));
+    h->flags_set = true;
     int *bad = &dst->bad_input;
     // Row pointers are copied clamped to [0, nnz] and out-of-range columns of A
     // are skipped by the analysis, so the kernels that run before the first
@@ -1774,6 +1777,7 @@ extern "C" spg_status spgemm_batch_symbolic(spg_handle h, int32_t count, const s
     HIPCHK(need(h, bt.bci, 4 * std::max<int64_t>(NB, 1)));
     DevStats *dst = h->dstats.as<DevStats>();
     HIPCHK(hipMemsetAsync(dst, 0, sizeof(DevStats), st));
+    h->flags_set = true;
     BatchDesc *dev = nullptr;
     if ((s = upload_desc(h, bt.a, &dev)) != SPG_OK) return s;
     HIPCHK(launch_batch_struct(dev, count, std::max(bt.max_rows + 1, bt.max_nnza), h->arp64.as<int64_t>(),
