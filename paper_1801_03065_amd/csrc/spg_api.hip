@@ -731,10 +731,15 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     // the symbolic lists are the numeric ones and no classification runs
     // (two launches: 10 us at 4096 rows, 16 us at a million).
     const bool all_short = sel && !split && m > 0 && hs2.kcount_sym[K_SR] + hs2.kcount_sym[K_EMPTY] == m;
+    if (split) {
+        HIPCHK(need(h, h->kind_heavy, std::max<int64_t>(m, 1)));
+        HIPCHK(need(h, h->perm_heavy, 4 * std::max<int64_t>(m, 1)));
+        HIPCHK(need(h, h->koff_heavy, 8 * (NK + 1)));
+    }
     // The scan writes the caller's row pointers too where nothing can refuse the
     // product any more: entries that may pass an int32, and kinds whose scratch
-    // may run out, have them copied at the end (5 us).
-    const bool rp_now = !split && (c_rp64 || hs1.fm <= (unsigned long long)INT32_MAX) &&
+    // may run out, have them copied at the end (10 to 20 us).
+    const bool rp_now = (c_rp64 || hs1.fm <= (unsigned long long)INT32_MAX) &&
                         hs2.kcount_sym[K_HL] + hs2.kcount_sym[K_DG] == 0;
     ScanOut so;
     so.rp32 = rp_now && !c_rp64 ? (int32_t *)c_rp : nullptr;
@@ -766,9 +771,6 @@ static spg_status symbolic_core(spg_handle h, int64_t m, int64_t n, int64_t k, i
     }
     h->heavy_split = false;
     if (split) {  // FP64-accumulated rows: their own kind lists (FP64 accumulation in FP32 mode)
-        HIPCHK(need(h, h->kind_heavy, std::max<int64_t>(m, 1)));
-        HIPCHK(need(h, h->perm_heavy, 4 * std::max<int64_t>(m, 1)));
-        HIPCHK(need(h, h->koff_heavy, 8 * (NK + 1)));
         ClassParams ch = cp;
         ch.heavy = 1;
         HIPCHK(launch_classify(m, h->rflops.as<int64_t>(), h->rflopsc.as<int64_t>(), h->rwin.as<int2>(),
