@@ -274,8 +274,8 @@ __device__ __forceinline__ void flat_rows(const NumArgs<VT> &a, IX *rel, IX *off
 
 // Values of the launch's rows on their position maps.  Bound by latency, so by
 // wavefronts and loads in flight: r_max (the longest row of the launch) sizes
-// the LDS.  Batch of 48 random products, FP32 (6.1e8 products): 2.7 ms, its
-// data unit 76 to 91% busy; with lane groups per B row and one load in flight
+// the LDS.  Batch of 48 random products, FP32 (6.1e8 products): 2.5 ms, its
+// data unit 75 to 91% busy; with lane groups per B row and one load in flight
 // 3.7 ms.
 template <typename VT, int ACC, typename IX, int U>
 __global__ __launch_bounds__(WAVE) void k_map_flat(NumArgs<VT> a) {
